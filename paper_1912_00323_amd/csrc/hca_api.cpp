@@ -186,6 +186,28 @@ uint32_t env_hd_budget()
     return (uint32_t)std::min<long>(std::max<long>(64, std::atol(e)), 1l << 30);
 }
 
+// Candidates of a point's list that core marking on byte planes takes it to
+// in each pass, the last one to the end.  Short passes keep the tiles full of
+// points that still need it (54 axes, 3.85M points: core 86 ms with 16384 and
+// 131072, restarted, 55 ms with these), but each is three launches and ends
+// with its longest run, so below 2^18 points, where there are hardly runs
+// enough for the chip, one limit is all (16 axes, 200k points: 0.68 ms, 1.03
+// with passes from 1024 on).  A list holds at most n candidates.
+// HCA_HD_BUDGET=k: limits k and 8 k.
+void plan_hd_passes(Plan &P)
+{
+    P.hd_passes = 0;
+    if (std::getenv("HCA_HD_BUDGET")) {
+        P.hd_limit[P.hd_passes++] = P.hd_budget;
+        P.hd_limit[P.hd_passes++] = (uint32_t)std::min<uint64_t>(8ull * P.hd_budget, 1ull << 30);
+    } else if (P.n < (1u << 18)) {
+        if (P.n > 4 * kHdCoreBudget) P.hd_limit[P.hd_passes++] = kHdCoreBudget;
+    } else {
+        for (uint32_t c = 2048; c < P.n && c <= (1u << 17); c *= 4) P.hd_limit[P.hd_passes++] = c;
+    }
+    P.hd_limit[P.hd_passes++] = ~0u;
+}
+
 // HCA_CORE_LANES=0: cube-mode core marking with a wave per cube even for
 // d <= 2; HCA_CORE_BUDGET=k: candidates per lane before a point is deferred
 bool env_core_lanes()
@@ -589,11 +611,16 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
     cv.take<int32_t>((size_t)kBboxBlocks * 2 * kMaxDimHigh);
     if (P.hd) {
         P.hd_origin = cv.take<int32_t>(kMaxDimHigh);
+        P.hd_centre = cv.take<int32_t>(kMaxDimHigh);      // follows hd_origin without a gap
         P.hd_list = cv.take<uint32_t>((size_t)2 * n);
         P.rec = cv.take<uint32_t>((size_t)kRec * n);
         P.nrec = cv.take<uint8_t>(n);
         P.blist = P.hd_list + n;
-        P.spts16 = P.hd16 ? cv.take<uint32_t>((size_t)n * (P.sd / 2)) : nullptr;
+        if (P.hd_steps) {
+            P.planes = cv.take<int32_t>((size_t)n * 16 * P.hd_steps);
+            P.nnorm = cv.take<int32_t>(n);
+            P.hd_mask = cv.take<uint64_t>(((size_t)n + 63) / 64);
+        }
     } else if (env_record()) {
         P.rec = cv.take<uint32_t>((size_t)kRec * n);
         P.nrec = cv.take<uint8_t>(n);
@@ -602,6 +629,13 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
     const size_t ksz = Z.wide_keys ? 8 : 4;
     B.keys_a = cv.take<char>((size_t)n * ksz);
     B.keys_b = cv.take<char>((size_t)n * ksz);
+    if (P.hd) {
+        // the runs of core marking, in the keys' arrays (read last by the
+        // cube tables)
+        P.hd_run_mask = (uint64_t *)B.keys_a;
+        P.hd_run_at = (uint32_t *)B.keys_b;
+        P.hd_cnt = P.hd_run_at + n;
+    }
     B.vals_a = cv.take<uint32_t>(n);
     B.vals_b = cv.take<uint32_t>(n);
     // rows of one or two axes travel with the keys through the radix passes
@@ -637,7 +671,7 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
         P.pstart = cv.take<uint32_t>((size_t)1 << Z.pbits);
         P.pend = cv.take<uint32_t>((size_t)1 << Z.pbits);
     }
-    P.work = cv.take<uint32_t>((size_t)2 * P.work_cap);
+    P.work = P.hd ? nullptr : cv.take<uint32_t>((size_t)2 * P.work_cap);
     // the lane walk's point lists live in the worklist, unused until merging
     const bool lanes = P.core_lanes && 2ull * n <= P.work_cap;
     P.core_list = lanes ? P.work : nullptr;
@@ -660,6 +694,7 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
     P.scan_status = cv.take<uint64_t>((size_t)2 * Z.scan_tiles + 64);
     P.first = cv.take<uint32_t>(((size_t)n + 31) / 32);
     P.tile_status = cv.take<uint64_t>((size_t)Z.scan_tiles + 64);
+    P.hd_status = P.hd ? cv.take<uint64_t>(kHdPasses * ((size_t)n / (kWave * kBlock) + 1)) : nullptr;
     P.nbr_status = P.nbr_cap ? cv.take<uint64_t>((size_t)Z.scan_tiles + 64) : nullptr;
     *zero_bytes = cv.off - zstart;
     *zero_begin = (uint32_t *)(cv.base ? cv.base + zstart : nullptr);
@@ -774,9 +809,9 @@ void fill_stats(hca_ctx *ctx, const Plan &P, hca_stats *stats)
         stats->wide = P.wide;
         stats->dense_table = (int32_t)P.dense;
         stats->list_overflow = (int32_t)hc->nbr_overflow;
-    stats->packed_rows = P.spts16 != nullptr ? 1 : 0;
+    stats->packed_rows = P.planes != nullptr ? 1 : 0;
     stats->key_axes = P.hd ? (int32_t)P.kd : 0;
-    stats->core_rest = P.hd ? (int64_t)hc->hd_left : P.core_list ? (int64_t)hc->n_defer : 0;
+    stats->core_rest = P.hd ? (int64_t)hc->hd_left[0] : P.core_list ? (int64_t)hc->n_defer : 0;
 }
 
 // ---- more than kMaxDim axes ----------------------------------------------------
@@ -784,7 +819,7 @@ void fill_stats(hca_ctx *ctx, const Plan &P, hca_stats *stats)
 // origin of every axis (uploaded for the kernels) after them.
 constexpr size_t kPinnedOrigin = align256(std::max(sizeof(int32_t) * kBboxBlocks * 2 * kMaxDimHigh,
                                                    sizeof(Counters)));
-constexpr size_t kPinnedBytes = kPinnedOrigin + sizeof(int32_t) * kMaxDimHigh;
+constexpr size_t kPinnedBytes = kPinnedOrigin + 2 * sizeof(int32_t) * kMaxDimHigh;
 constexpr uint64_t kHdListMax = 1ull << 30;   // neighbour-list entries, at most
 
 // Init, sort, cube and group tables, lookup and neighbour lists; the host
@@ -800,8 +835,8 @@ void launch_hd_first(hca_ctx *ctx, Plan &P, const Sizes &Z)
     carve_ws(cv, P, B, Z, &zbeg, &zbytes);
     B.tickets = P.ctr->sort_tickets;
     launch_init(zbeg, zbytes / sizeof(uint32_t), P.dense ? P.table : nullptr, P.dense ? (1ull << Z.gbits) : 0, s);
-    (void)hipMemcpyAsync((void *)P.hd_origin, (char *)ctx->pinned + kPinnedOrigin, sizeof(int32_t) * P.d,
-                         hipMemcpyHostToDevice, s);
+    (void)hipMemcpyAsync((void *)P.hd_origin, (char *)ctx->pinned + kPinnedOrigin, 2 * sizeof(int32_t) * kMaxDimHigh,
+                         hipMemcpyHostToDevice, s);      // and hd_centre, carved right after it
     mark(ctx, HCA_PHASE_SORT, false);
     launch_sort_hd(P, B, s);
     mark(ctx, HCA_PHASE_SORT, true);
@@ -882,7 +917,11 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
     if (reach > (unsigned __int128)INT64_MAX)
         return fail(ctx, HCA_E_RANGE, "the squared spans of the axes add up to 2^63 or more");
     int32_t *org = (int32_t *)((char *)ctx->pinned + kPinnedOrigin);
-    for (int k = 0; k < d; k++) org[k] = (int32_t)mn[k];
+    std::memset(org, 0, 2 * sizeof(int32_t) * kMaxDimHigh);
+    for (int k = 0; k < d; k++) {
+        org[k] = (int32_t)mn[k];
+        org[kMaxDimHigh + k] = (int32_t)(mn[k] + (mx[k] - mn[k]) / 2);
+    }
 
     // 2. cube side, group side and key axes
     Plan P;
@@ -934,12 +973,13 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
     P.passes = sort_passes(P.key_bits, true);
     P.digit_bits = (P.key_bits + P.passes - 1) / P.passes;
     P.wide = reach >= ((unsigned __int128)1 << 31) ? 1 : 0;
-    // packed int16 rows when every span is below 2^15 and sums fit 32 bits
+    // byte planes when every span is below 2^15 and sums fit 32 bits
     // (HCA_PACKED=0 turns them off)
     bool narrow16 = !P.wide;
     for (int k = 0; k < d; k++) narrow16 = narrow16 && mx[k] - mn[k] < (1ll << 15);
     if (const char *e = std::getenv("HCA_PACKED")) narrow16 = narrow16 && std::strcmp(e, "0") != 0;
-    P.hd16 = narrow16 ? 1u : 0u;
+    P.hd_steps = !narrow16 ? 0u : d <= 32 ? 1u : 2u;
+    plan_hd_passes(P);
     P.list_w = 3;
     Sizes Z;
     plan_sizes(P, gbits, stats != nullptr && ctx->prof != -1, stats != nullptr, &Z);

@@ -20,18 +20,67 @@
 
 namespace hca {
 
-// A staged point in LDS: its int32 coordinates, then (packed form) its
-// coordinates less the origin as int16 pairs.
-constexpr int kOwnStride = kMaxDimHigh + kMaxDimHigh / 2;
+// A staged point in LDS: its int32 coordinates, then (plane form) its row of
+// byte planes and its negated squared norm.
+constexpr int kOwnPlanes = kMaxDimHigh, kOwnNorm = kMaxDimHigh + kMaxDimHigh / 2;
+constexpr int kOwnStride = kOwnNorm + 4;
 
-typedef short short2_t __attribute__((ext_vector_type(2)));
+// ---------------------------------------------------------------------------
+// Byte planes.  When every span is below 2^15 and the squared spans add up to
+// less than 2^31, a coordinate less its axis' centre is x = 256 h + l with
+// signed bytes h in [-64, 64] and l in [-128, 127], so a product of two
+// points is exact in four products of bytes,
+//   p.q = 2^16 h.h' + 2^8 (h.l' + l.h') + l.l',
+// each summed in 32 bits, and |p - q|^2 = |p|^2 + |q|^2 - 2 p.q (also below
+// 2^31; the sums in between may wrap).  That makes the distances of a set of
+// points from a set of candidates a contraction for the byte matrix units.
+//
+// A row holds two halves of KS chunks of high bytes and KS chunks of low ones
+// (KS = 1 up to 32 axes, else 2): chunk (half, step) has the 16 axes from
+// 32 step + 16 half on, which is what lane (column, half) feeds to step
+// `step` of a 32x32x32 matrix instruction.
+// ---------------------------------------------------------------------------
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 
-// acc + (a.lo - b.lo)^2 + (a.hi - b.hi)^2 for two packed int16 pairs (their
-// differences fit int16: every span is below 2^15).
-__device__ __forceinline__ int32_t sq_dot16(uint32_t a, uint32_t b, int32_t acc)
+// One thread per chunk: 16 axes of one row split into bytes, the row's norm
+// summed over its 2 KS chunks (neighbouring lanes).
+template <int KS>
+__global__ __launch_bounds__(kBlock) void k_hd_planes(Plan P)
 {
-    const short2_t d = __builtin_bit_cast(short2_t, a) - __builtin_bit_cast(short2_t, b);
-    return __builtin_amdgcn_sdot2(d, d, acc, false);
+    constexpr uint32_t C = 2 * KS;
+    const uint32_t sd = P.sd;
+    const uint64_t total = (uint64_t)P.n * C;
+    const uint32_t c = threadIdx.x % C, half = c / KS, step = c % KS, a0 = 32u * step + 16u * half;
+    for (uint64_t b = (uint64_t)blockIdx.x * kBlock; b < total; b += (uint64_t)gridDim.x * kBlock) {
+        const uint64_t t = b + threadIdx.x, r = min(t, total - 1) / C;
+        uint32_t hi[4], lo[4], norm = 0;
+#pragma unroll
+        for (int w = 0; w < 4; w++) {
+            const uint32_t a = a0 + 4 * w;
+            int4 v = make_int4(0, 0, 0, 0), o = v;
+            if (a < sd) {
+                v = *reinterpret_cast<const int4 *>(P.spts + r * sd + a);
+                o = *reinterpret_cast<const int4 *>(P.hd_centre + a);
+            }
+            const int32_t x[4] = {v.x - o.x, v.y - o.y, v.z - o.z, v.w - o.w};
+            hi[w] = lo[w] = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                hi[w] |= (uint32_t)(((x[i] + 128) >> 8) & 255) << (8 * i);
+                lo[w] |= (uint32_t)(x[i] & 255) << (8 * i);
+                norm += (uint32_t)(x[i] * x[i]);
+            }
+        }
+#pragma unroll
+        for (uint32_t o = 1; o < C; o <<= 1) norm += __shfl_xor(norm, o);
+        if (t < total) {
+            uint4 *row = reinterpret_cast<uint4 *>(P.planes) + r * (2 * C) + half * (2 * KS);
+            row[step] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            row[KS + step] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            if (c == 0) P.nnorm[r] = -(int32_t)norm;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -304,12 +353,13 @@ __device__ __forceinline__ void hd_stage(const Plan &P, uint32_t pc, uint32_t np
         const uint32_t k = i / sd, e = i - k * sd;
         own[k][e] = P.spts[(uint64_t)(pc + min(k, np - 1)) * sd + e];
     }
-    if (P.spts16) {
-        const uint32_t hw = sd >> 1;
-        for (uint32_t i = lane_id(); i < kPch * hw; i += kWave) {
-            const uint32_t k = i / hw, e = i - k * hw;
-            own[k][kMaxDimHigh + e] = (int32_t)P.spts16[(uint64_t)(pc + min(k, np - 1)) * hw + e];
+    if (P.planes) {
+        const uint32_t pw = 16u * P.hd_steps;             // words of a row of planes
+        for (uint32_t i = lane_id(); i < kPch * pw; i += kWave) {
+            const uint32_t k = i / pw, e = i - k * pw;
+            own[k][kOwnPlanes + e] = P.planes[(uint64_t)(pc + min(k, np - 1)) * pw + e];
         }
+        if (lane_id() < (uint32_t)kPch) own[lane_id()][kOwnNorm] = P.nnorm[pc + min(lane_id(), np - 1)];
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -317,12 +367,13 @@ __device__ __forceinline__ void hd_stage(const Plan &P, uint32_t pc, uint32_t np
 // The 8 rows at sorted positions pos[0..8) (wave-uniform) into LDS.
 __device__ __forceinline__ void hd_stage_at(const Plan &P, const uint32_t *pos, int32_t (*own)[kOwnStride])
 {
-    const uint32_t sd = P.sd, l = lane_id();
+    const uint32_t sd = P.sd, l = lane_id(), pw = 16u * P.hd_steps;
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int k = 0; k < kPch; k++) {
         if (l < sd) own[k][l] = P.spts[(uint64_t)pos[k] * sd + l];
-        if (P.spts16 && l < (sd >> 1)) own[k][kMaxDimHigh + l] = (int32_t)P.spts16[(uint64_t)pos[k] * (sd >> 1) + l];
+        if (P.planes && l < pw) own[k][kOwnPlanes + l] = P.planes[(uint64_t)pos[k] * pw + l];
+        if (P.planes && l == 0) own[k][kOwnNorm] = P.nnorm[pos[k]];
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -360,7 +411,7 @@ __device__ __forceinline__ int64_t hd_point_box_gap2(const int32_t *p, const int
 
 // Candidates of slots [first, first + 64): lane l resolves slot first + l.  A
 // group is dropped when it has no core point (need_core), when its box is
-// farther than eps from the query box qb or from every staged point in
+// farther than eps from the query box qb (null: not looked at) or from every staged point in
 // `mask`, or (skip_root != kNone) when all its core cubes already share the
 // root skip_root.  Returns the candidate count.
 __device__ __forceinline__ uint32_t hd_load_neighbours(const Plan &P, uint32_t g, const HdSrc &src, uint32_t first,
@@ -374,7 +425,7 @@ __device__ __forceinline__ uint32_t hd_load_neighbours(const Plan &P, uint32_t g
     if (j < src.slots) {
         const uint32_t G = hd_slot(P, g, src, j);
         const int32_t *gb = P.gbox + (uint64_t)G * 2 * sd;
-        bool keep = !(need_core && P.gcube[G] == kNone) && hd_box_gap2(qb, gb, sd, eps2) <= eps2;
+        bool keep = !(need_core && P.gcube[G] == kNone) && (!qb || hd_box_gap2(qb, gb, sd, eps2) <= eps2);
         if (keep && __popc(mask) > 1) {
             bool nearby = false;
 #pragma unroll
@@ -397,12 +448,12 @@ __device__ __forceinline__ uint32_t hd_load_neighbours(const Plan &P, uint32_t g
 }
 
 // Row forms, fixed per call by the host, one kernel instance each: 32-bit
-// sums of int32 rows, 64-bit sums, or packed int16 rows.
-constexpr int kRowNarrow = 0, kRowWide = 1, kRowPacked = 2;
+// sums of int32 rows, 64-bit sums, or byte planes of up to 32 or 64 axes.
+constexpr int kRowNarrow = 0, kRowWide = 1, kRowPlanes1 = 2, kRowPlanes2 = 3;
 
 __host__ __device__ inline int row_form(const Plan &P)
 {
-    return P.wide ? kRowWide : P.spts16 ? kRowPacked : kRowNarrow;
+    return P.wide ? kRowWide : !P.planes ? kRowNarrow : P.hd_steps == 1 ? kRowPlanes1 : kRowPlanes2;
 }
 
 // Squared distances from the candidate row at sorted position pos to the 8
@@ -430,33 +481,38 @@ __device__ __forceinline__ void hd_dist(const Plan &P, const int32_t (*own)[kOwn
         }
 #pragma unroll
         for (int k = 0; k < kPch; k++) dd[k] = acc[k];
-    } else if constexpr (ROW == kRowPacked) {
-        // packed int16 coordinates: two axes per subtract and dot step
-        const uint4 *prow = reinterpret_cast<const uint4 *>(P.spts16 + (uint64_t)pos * (P.sd >> 1));
-        const uint32_t n8 = P.sd >> 3;
-        uint4 v[kMaxDimHigh / 8];
+    } else if constexpr (ROW == kRowPlanes1 || ROW == kRowPlanes2) {
+        // four axes per byte dot product, four products per word of a plane
+        constexpr int KS = ROW == kRowPlanes1 ? 1 : 2;
+        const uint4 *prow = reinterpret_cast<const uint4 *>(P.planes) + (uint64_t)pos * (4 * KS);
+        uint4 v[4 * KS];
 #pragma unroll
-        for (int e = 0; e < kMaxDimHigh / 8; e++) {
-            v[e] = make_uint4(0, 0, 0, 0);
-            if ((uint32_t)e < n8) v[e] = prow[e];
+        for (int e = 0; e < 4 * KS; e++) v[e] = prow[e];
+        const int32_t nq = P.nnorm[pos];
+#pragma unroll
+        for (int k = 0; k < kPch; k++) {
+            int32_t hh = 0, hl = 0, ll = 0;
+#pragma unroll
+            for (int half = 0; half < 2; half++)
+#pragma unroll
+                for (int st = 0; st < KS; st++) {
+                    const int e = half * 2 * KS + st;
+                    const uint4 oh = reinterpret_cast<const uint4 *>(own[k] + kOwnPlanes)[e];
+                    const uint4 ol = reinterpret_cast<const uint4 *>(own[k] + kOwnPlanes)[e + KS];
+                    const uint32_t ch[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
+                    const uint32_t cl[4] = {v[e + KS].x, v[e + KS].y, v[e + KS].z, v[e + KS].w};
+                    const uint32_t ph[4] = {oh.x, oh.y, oh.z, oh.w}, pl[4] = {ol.x, ol.y, ol.z, ol.w};
+#pragma unroll
+                    for (int w = 0; w < 4; w++) {
+                        hh = __builtin_amdgcn_sdot4((int)ch[w], (int)ph[w], hh, false);
+                        hl = __builtin_amdgcn_sdot4((int)ch[w], (int)pl[w], hl, false);
+                        hl = __builtin_amdgcn_sdot4((int)cl[w], (int)ph[w], hl, false);
+                        ll = __builtin_amdgcn_sdot4((int)cl[w], (int)pl[w], ll, false);
+                    }
+                }
+            const uint32_t dot = ((((uint32_t)hh << 8) + (uint32_t)hl) << 8) + (uint32_t)ll;
+            dd[k] = -(int32_t)((uint32_t)own[k][kOwnNorm] + (uint32_t)nq + 2u * dot);
         }
-        int32_t acc[kPch];
-#pragma unroll
-        for (int k = 0; k < kPch; k++) acc[k] = 0;
-#pragma unroll
-        for (int e = 0; e < kMaxDimHigh / 8; e++) {
-            if ((uint32_t)e >= n8) continue;
-#pragma unroll
-            for (int k = 0; k < kPch; k++) {
-                const uint4 o = reinterpret_cast<const uint4 *>(own[k] + kMaxDimHigh)[e];
-                acc[k] = sq_dot16(v[e].x, o.x, acc[k]);
-                acc[k] = sq_dot16(v[e].y, o.y, acc[k]);
-                acc[k] = sq_dot16(v[e].z, o.z, acc[k]);
-                acc[k] = sq_dot16(v[e].w, o.w, acc[k]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kPch; k++) dd[k] = acc[k];
     } else {
         // the whole row in flight at once (one memory latency per candidate)
         int4 v[kMaxDimHigh / 4];
@@ -559,10 +615,8 @@ __device__ __forceinline__ void hd_tally(const Plan &P, bool in, uint32_t cell, 
 // First pass: chunks of 8 consecutive sorted points, each point looking at
 // up to P.hd_budget candidates; points still undecided are appended to
 // the list of the second pass.
-// The packed form is held to 96 registers (five waves per SIMD): some
-// spill, and the walk still gains from the extra wave.
 template <int ROW>
-__global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core(Plan P)
+__global__ __launch_bounds__(kBlock) void k_hd_core(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ __align__(16) int32_t s_own[kWavesPerBlock][kPch][kOwnStride];
@@ -615,7 +669,7 @@ __global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core(P
         const uint64_t um = __ballot(later);
         if (um) {
             uint32_t base = 0;
-            if (l == 0) base = atomicAdd(&P.ctr->hd_left, (uint32_t)__popcll(um));
+            if (l == 0) base = atomicAdd(P.ctr->hd_left, (uint32_t)__popcll(um));
             base = __shfl(base, 0);
             if (later) P.hd_list[base + __popcll(um & __lanemask_lt())] = pc + l;
         }
@@ -626,14 +680,14 @@ __global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core(P
 
 // Second pass: chunks of 8 points of the list, walked to the end.
 template <int ROW>
-__global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core_rest(Plan P)
+__global__ __launch_bounds__(kBlock) void k_hd_core_rest(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ __align__(16) int32_t s_own[kWavesPerBlock][kPch][kOwnStride];
     __shared__ int32_t s_qb[kWavesPerBlock][2 * kMaxDimHigh];
     __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave];
     const uint32_t w = wave_in_block(), l = lane_id();
-    const uint32_t nl = ld_agent32(&P.ctr->hd_left), minpts = (uint32_t)P.min_pts;
+    const uint32_t nl = ld_agent32(P.ctr->hd_left), minpts = (uint32_t)P.min_pts;
     const uint32_t all = (1u << kPch) - 1u;
     uint32_t lt = 0;
     const DynRange dr_ = dyn_range(P.ctr->dyn[kDynCoreRest], P.order);
@@ -674,6 +728,457 @@ __global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core_r
         hd_tally(P, in, cell, core, core ? P.sidx[q] : kNone);
     }
     flush_tests(P, kTestsCore, lt);
+}
+
+// ---------------------------------------------------------------------------
+// Core marking on byte planes: a wave takes 64 points (two blocks of 32 rows
+// of the matrix instruction) and streams candidates 32 at a time through the
+// matrix units.
+//
+// Bound: the matrix and vector rates together.  A tile of 32 rows and columns
+// costs four products per step of 32 axes (8 matrix instructions at 64 axes,
+// 256 cycles) and four vector instructions per result (about as many cycles),
+// which overlap between the two waves of a SIMD; the candidates' bytes (128
+// per 64 rows) are the next limit.  Both operands are read as the rows lie in
+// memory (a lane's chunk is 16 contiguous bytes) into registers one step of
+// 64 candidates ahead.  Sharing each candidate between four waves through
+// LDS, with a barrier per step, was slower (86 against 107 ms for the same
+// passes).  54 axes, 3.85M points, 1e11 pair tests: 653 ms with two packed
+// axes per vector dot product and 8 points per wave, 55 ms here.
+//
+// A row that needs no further neighbour (it reached minPts, or belongs to
+// another run) gets a limit that nothing meets, so hits are met at most a few
+// times per point and tile; each is counted through an LDS counter of its row.
+// ---------------------------------------------------------------------------
+constexpr int kTilePts = 64;
+// A run of at most this many points takes its own box to the neighbour list;
+// the box of more comes out close to the group's, which the list was built by.
+constexpr uint32_t kHdBoxRun = 16;
+
+// Box of the points at the lanes in `mask`, into qb[0, sd) and qb[sd, 2 sd).
+__device__ __forceinline__ void hd_rows_box(const Plan &P, uint32_t qpos, uint64_t mask, int32_t *qb)
+{
+    const uint32_t l = lane_id(), sd = P.sd, col = min(l, sd - 1);
+    int32_t lo = INT32_MAX, hi = INT32_MIN;
+    while (mask) {
+        const uint32_t q = (uint32_t)__ffsll((unsigned long long)mask) - 1;
+        mask &= mask - 1;
+        const int32_t v = P.spts[(uint64_t)lane_value(qpos, q) * sd + col];
+        lo = min(lo, v);
+        hi = max(hi, v);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (l < sd) {
+        qb[l] = lo;
+        qb[sd + l] = hi;
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Matrix row r of a lane's 16 results (its half of the wave gives the rest).
+__device__ __forceinline__ uint32_t tile_row(uint32_t r, uint32_t half) { return (r & 3u) + 8u * (r >> 2) + 4u * half; }
+
+// Candidates of two tiles of 32 columns: a lane holds its half of the row and
+// the negated norm of column l % 32 of each; lane l has the position of
+// candidate l of the 64.
+template <int KS>
+struct HdCols {
+    v4i b[2][2 * KS];
+    int32_t nq[2];
+    uint32_t pos;
+};
+
+// The slot that the last looked-up candidate fell in (wave-uniform): its
+// candidates [first, end) lie one after the other from sorted position beg.
+struct HdSlot {
+    uint32_t beg, first, end;
+};
+
+// Sorted positions of the candidates c0 .. c0 + 63 (the last one repeated).
+__device__ __forceinline__ uint32_t hd_positions(uint32_t c0, uint32_t total, HdSlot &slot, const uint32_t *s_beg,
+                                                 const uint32_t *s_pre)
+{
+    const uint32_t c = min(c0 + lane_id(), total - 1);
+    if (min(c0 + kWave, total) <= slot.end) return slot.beg + (c - slot.first);
+    const uint32_t ln = candidate_lane(c, s_pre);
+    const uint32_t pos = s_beg[ln] + (c - s_pre[ln]);
+    const uint32_t last = lane_value(ln, kWave - 1);
+    slot.beg = uniform(s_beg[last]);
+    slot.first = uniform(s_pre[last]);
+    slot.end = last == kWave - 1 ? total : uniform(s_pre[last + 1]);
+    return pos;
+}
+
+template <int KS>
+__device__ __forceinline__ HdCols<KS> hd_cols(const Plan &P, uint32_t c0, uint32_t total, HdSlot &slot,
+                                              const uint32_t *s_beg, const uint32_t *s_pre)
+{
+    const uint32_t l = lane_id();
+    HdCols<KS> t;
+    t.pos = hd_positions(c0, total, slot, s_beg, s_pre);
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const uint32_t pos = __shfl(t.pos, 32 * k + (l & 31u));
+        const v4i *row = reinterpret_cast<const v4i *>(P.planes) + (uint64_t)pos * (4 * KS) + (l >> 5) * (2 * KS);
+#pragma unroll
+        for (int e = 0; e < 2 * KS; e++) t.b[k][e] = row[e];
+        t.nq[k] = P.nnorm[pos];
+    }
+    return t;
+}
+
+// 2 p.q - |q|^2 for the 32 x 32 points p (rows) and candidates q (columns):
+// 16 results per lane.
+template <int KS>
+__device__ __forceinline__ void hd_tile(const v4i *a, const v4i *b, int32_t nq, int32_t *v)
+{
+    v16i hh = {0}, hl = {0}, ll = {0};
+#pragma unroll
+    for (int st = 0; st < KS; st++) {
+        hh = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[st], b[st], hh, 0, 0, 0);
+        hl = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[st], b[KS + st], hl, 0, 0, 0);
+        ll = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[KS + st], b[KS + st], ll, 0, 0, 0);
+        hl = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[KS + st], b[st], hl, 0, 0, 0);
+    }
+    // three shift-and-adds per result; the empty statements keep the compiler
+    // from regrouping them into five instructions
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        uint32_t t = ((uint32_t)hh[r] << 8) + (uint32_t)hl[r];
+        asm("" : "+v"(t));
+        t = (t << 8) + (uint32_t)ll[r];
+        asm("" : "+v"(t));
+        v[r] = (int32_t)((t << 1) + (uint32_t)nq);
+    }
+}
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v)
+{
+    return (uint64_t)uniform((uint32_t)(v >> 32)) << 32 | uniform((uint32_t)v);
+}
+
+// A wave's rows in LDS: neighbours found so far, the limit each row's results
+// are compared with, and the rows' sorted positions.
+struct HdRows {
+    uint32_t cnt[kTilePts];
+    int32_t lim[kTilePts];
+    uint32_t pos[kTilePts];
+};
+
+// The limits of row block b: result r of a lane belongs to row tile_row(r,
+// half), four consecutive rows for four consecutive results.
+__device__ __forceinline__ void hd_limits(const HdRows &R, int b, uint32_t half, int32_t *thr)
+{
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const int4 t = *reinterpret_cast<const int4 *>(&R.lim[32 * b + 8 * j + 4 * half]);
+        thr[4 * j] = t.x;
+        thr[4 * j + 1] = t.y;
+        thr[4 * j + 2] = t.z;
+        thr[4 * j + 3] = t.w;
+    }
+}
+
+// The hits of a tile of row block b, candidate `pos` per lane: every lane
+// with a hit takes the next place of its row and records the candidate
+// there; rows that reached minPts leave `act`.
+__device__ __forceinline__ void hd_hits(const Plan &P, HdRows &R, int b, const int32_t *v, int32_t *thr, uint32_t pos,
+                                        bool ok, uint64_t &act)
+{
+    const uint32_t l = lane_id(), half = l >> 5;
+    uint32_t rank[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        rank[r] = kNone;
+        if (ok && v[r] >= thr[r]) rank[r] = atomicAdd(&R.cnt[32 * b + tile_row(r, half)], 1u);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r++)
+        if (rank[r] < (uint32_t)kRec) P.rec[(uint64_t)R.pos[32 * b + tile_row(r, half)] * kRec + rank[r]] = pos;
+    __builtin_amdgcn_wave_barrier();
+    const uint64_t done = __ballot(R.cnt[l] >= (uint32_t)P.min_pts) & act;
+    if (done) {
+        act &= ~done;
+        if ((done >> l) & 1) R.lim[l] = INT32_MAX;
+        __builtin_amdgcn_wave_barrier();
+        hd_limits(R, b, half, thr);
+    }
+}
+
+// The rows of a wave: counters, limits (INT32_MAX where the row is not in
+// act) and positions.
+__device__ __forceinline__ void hd_rows_init(HdRows &R, uint64_t act, int32_t lim, uint32_t qpos, uint32_t cnt)
+{
+    const uint32_t l = lane_id();
+    __builtin_amdgcn_wave_barrier();
+    R.cnt[l] = cnt;
+    R.lim[l] = (act >> l) & 1 ? lim : INT32_MAX;
+    R.pos[l] = qpos;
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The rows of a wave's 64 points as matrix operands.
+template <int KS>
+__device__ __forceinline__ void hd_load_rows(const Plan &P, uint32_t qpos, v4i (&a)[2][2 * KS])
+{
+    const uint32_t l = lane_id();
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+        const uint32_t row = __shfl(qpos, 32 * b + (l & 31u));
+        const v4i *src = reinterpret_cast<const v4i *>(P.planes) + (uint64_t)row * (4 * KS) + (l >> 5) * (2 * KS);
+#pragma unroll
+        for (int e = 0; e < 2 * KS; e++) a[b][e] = src[e];
+    }
+}
+
+// The points of the lanes in `act` (all of group g) against the group and its
+// neighbours, from candidate `from` to candidate `upto` of that list (both
+// rounded up to where a step of 64 ends) or until each has minPts neighbours.
+// own_box: the list is thinned by the points' own box (and walked whole).
+// Returns the points that did not reach minPts; R.cnt has the neighbours.
+template <int KS>
+__device__ __forceinline__ uint64_t hd_tile_walk(const Plan &P, uint32_t g, uint64_t act, const v4i (&a)[2][2 * KS],
+                                                 HdRows &R, bool own_box, int32_t *qb, uint32_t *s_beg,
+                                                 uint32_t *s_pre, uint32_t &lt, uint32_t from, uint32_t upto,
+                                                 bool *cut)
+{
+    const uint32_t l = lane_id(), half = l >> 5;
+    int32_t thr[2][16];
+    hd_limits(R, 0, half, thr[0]);
+    hd_limits(R, 1, half, thr[1]);
+    const HdSrc src = hd_source(P, g, false);
+    uint32_t seen = 0;
+    for (uint32_t oc = 0; oc < src.slots && act && seen < upto; oc += kWave) {
+        const uint32_t total = uniform(hd_load_neighbours(P, g, src, oc, false, own_box ? qb : nullptr, nullptr, 0u,
+                                                          kNone, s_beg, s_pre));
+        const uint32_t skip = seen < from ? (from - seen + kWave - 1) / kWave * kWave : 0u;
+        if (skip >= total) {
+            seen += total;
+            continue;
+        }
+        seen += skip;
+        HdSlot slot = {0, 0, 0};
+        HdCols<KS> nxt = hd_cols<KS>(P, skip, total, slot, s_beg, s_pre);
+        for (uint32_t ci = skip; ci < total && act && seen < upto; ci += kWave) {
+            const HdCols<KS> t = nxt;
+            // the next 64 rows are on their way while these are tested
+            if (ci + kWave < total) nxt = hd_cols<KS>(P, ci + kWave, total, slot, s_beg, s_pre);
+            seen += min((uint32_t)kWave, total - ci);
+            lt += ci + l < total ? (uint32_t)__popcll(act) : 0u;
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                if (ci + 32u * k >= total) break;
+#pragma unroll
+                for (int b = 0; b < 2; b++) {
+                    if (!(uint32_t)(act >> (32 * b))) continue;
+                    int32_t v[16];
+                    hd_tile<KS>(a[b], t.b[k], t.nq[k], v);
+                    // |p - q|^2 <= eps^2 as 2 p.q - |q|^2 >= |p|^2 - eps^2
+                    bool any = false;
+#pragma unroll
+                    for (int r = 0; r < 16; r++) any |= v[r] >= thr[b][r];
+                    if (!__ballot(any)) continue;
+                    hd_hits(P, R, b, v, thr[b], __shfl(t.pos, 32 * k + (l & 31u)), ci + 32u * k + (l & 31u) < total, act);
+                }
+            }
+        }
+    }
+    *cut = act && seen >= upto;
+    return act;
+}
+
+// Core marking takes a few passes.  Each one takes its points to the next
+// limit of P.hd_limit (candidates of the point's list); those still undecided
+// are listed in order and go on from there in the next pass, so that the
+// points of a tile are ones that still need it.
+//
+// Points a pass starts from: pass 0 all sorted positions, then the lists.
+__device__ __forceinline__ uint32_t hd_pass_points(const Plan &P, uint32_t pass)
+{
+    return pass == 0 ? P.n : ld_agent32(P.ctr->hd_left + pass - 1);
+}
+__device__ __forceinline__ uint32_t *hd_pass_list(const Plan &P, uint32_t pass)
+{
+    return pass & 1u ? P.hd_list : P.blist;
+}
+__device__ __forceinline__ uint32_t hd_pass_point(const Plan &P, uint32_t pass, uint32_t i)
+{
+    return pass == 0 ? i : hd_pass_list(P, pass)[i];
+}
+
+// The units of a pass: runs of at most 64 consecutive points of one group
+// within 256 places of the pass' order (pass 0 decides the points of dense
+// cubes here).  Edge and noise points are often alone in their group: as
+// units of their own they spread over all waves, where a unit of 64 such
+// points would walk 64 lists one after the other.
+__global__ __launch_bounds__(kBlock) void k_hd_runs(Plan P, uint32_t pass)
+{
+    if (box_missed(P)) return;
+    __shared__ uint64_t s_first[kWavesPerBlock], s_todo[kWavesPerBlock + 1];
+    __shared__ uint32_t s_grp[kWavesPerBlock];
+    const uint32_t l = lane_id(), w = wave_in_block(), n = hd_pass_points(P, pass), minpts = (uint32_t)P.min_pts;
+    const bool last = pass + 1 == P.hd_passes;
+    for (uint32_t c0 = blockIdx.x * kBlock; c0 < n; c0 += gridDim.x * kBlock) {
+        const uint32_t i = c0 + threadIdx.x, q = hd_pass_point(P, pass, min(i, n - 1));
+        const bool in = i < n;
+        const uint32_t cell = P.cell_of[q], grp = P.group_of[cell];
+        const bool dense = pass == 0 && P.cell_start[cell + 1] - P.cell_start[cell] >= minpts;
+        if (pass == 0) {
+            if (in && dense) {
+                P.core[q] = 1;
+                P.nrec[q] = 0;
+            }
+            hd_tally(P, in, cell, dense, in && dense ? P.sidx[q] : kNone);
+        }
+        if (!last && l == 0 && in) st_agent(P.hd_mask + i / kWave, 0ull);
+        if (l == kWave - 1) s_grp[w] = grp;
+        __syncthreads();
+        const uint32_t up = __shfl_up(grp, 1), before = l ? up : w ? s_grp[w - 1] : ~grp;
+        const uint64_t firsts = __ballot(!in || grp != before), todo = __ballot(in && !dense);
+        if (l == 0) {
+            s_first[w] = firsts;
+            s_todo[w] = todo;
+            s_todo[kWavesPerBlock] = 0ull;
+        }
+        __syncthreads();
+        // the group's stretch of these 256 places: its first and end
+        uint64_t m = firsts & ((2ull << l) - 1ull);
+        uint32_t e = w;
+        while (!m && e > 0) m = s_first[--e];
+        const uint32_t head = m ? e * kWave + 63u - (uint32_t)__clzll((long long)m) : 0u;
+        m = l == kWave - 1 ? 0ull : firsts >> (l + 1) << (l + 1);
+        e = w;
+        while (!m && ++e < (uint32_t)kWavesPerBlock) m = s_first[e];
+        const uint32_t end = m ? e * kWave + (uint32_t)__ffsll((unsigned long long)m) - 1 : (uint32_t)kBlock;
+        // every 64th place of it starts a run
+        const bool start = in && (threadIdx.x - head) % kTilePts == 0;
+        const uint32_t len = min(end - threadIdx.x, (uint32_t)kTilePts);
+        uint64_t need = (todo >> l) | (l ? s_todo[w + 1] << (kWave - l) : 0ull);
+        if (len < (uint32_t)kTilePts) need &= (1ull << len) - 1ull;
+        const bool take = start && need;
+        const uint64_t hm = __ballot(take);
+        uint32_t base = 0;
+        if (l == 0 && hm) base = atomicAdd(P.ctr->hd_runs + pass, (uint32_t)__popcll(hm));
+        base = uniform(base);
+        if (take) {
+            const uint32_t at = base + __popcll(hm & __lanemask_lt());
+            P.hd_run_at[at] = i;
+            P.hd_run_mask[at] = need;
+        }
+        __syncthreads();
+    }
+}
+
+// Units are dealt to an XCD as one stretch of their order, so that its waves
+// walk the lists of few groups at a time and share the candidates in its L2;
+// a wave whose XCD has none left takes from the next one's.
+struct HdQueue {
+    uint32_t *cnt;
+    uint32_t xcd, left;
+};
+
+__device__ __forceinline__ uint32_t hd_next(HdQueue &d, uint32_t units)
+{
+    while (d.left) {
+        uint32_t i = 0;
+        if (lane_id() == 0) i = atomicAdd(d.cnt + d.xcd * kCounterStride, 1u);
+        i = uniform(i);
+        const uint32_t lo = (uint32_t)((uint64_t)units * d.xcd / 8u), hi = (uint32_t)((uint64_t)units * (d.xcd + 1) / 8u);
+        if (i < hi - lo) return lo + i;
+        d.xcd = (d.xcd + 1) & 7u;
+        d.left--;
+    }
+    return kNone;
+}
+
+template <int KS>
+__global__ __launch_bounds__(kBlock, 2) void k_hd_core_tiles(Plan P, uint32_t pass)
+{
+    if (box_missed(P)) return;
+    __shared__ __align__(16) HdRows s_rows[kWavesPerBlock];
+    __shared__ int32_t s_qb[kWavesPerBlock][2 * kMaxDimHigh];
+    __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave];
+    const uint32_t w = wave_in_block(), l = lane_id(), minpts = (uint32_t)P.min_pts;
+    const uint32_t runs = ld_agent32(P.ctr->hd_runs + pass);
+    const uint32_t from = pass ? P.hd_limit[pass - 1] : 0u, upto = P.hd_limit[pass];
+    const int32_t eps2 = (int32_t)min(P.eps2, (int64_t)INT32_MAX);
+    uint32_t lt = 0;
+    HdQueue queue = {P.ctr->dyn[pass & 1u ? kDynCoreRest : kDynCore], blockIdx.x & 7u, 8u};
+    for (uint32_t u; (u = hd_next(queue, runs)) != kNone;) {
+        u = unit_remap(u, runs, P.order);
+        const uint32_t i0 = uniform(P.hd_run_at[u]);
+        const uint64_t run = uniform64(P.hd_run_mask[u]);
+        const bool in = (run >> l) & 1;
+        // lanes past the run repeat its last point
+        const uint32_t tail = 63u - (uint32_t)__clzll((long long)run);
+        const uint32_t q = hd_pass_point(P, pass, i0 + min(l, tail));
+        const uint32_t cell = P.cell_of[q], g = uniform(P.group_of[cell]);
+        v4i a[2][2 * KS];
+        hd_load_rows<KS>(P, q, a);
+        HdRows &R = s_rows[w];
+        hd_rows_init(R, run, -P.nnorm[q] - eps2, q, pass ? P.hd_cnt[q] : 0u);
+        const bool own_box = pass == 0 && __popcll(run) <= kHdBoxRun;
+        if (own_box) hd_rows_box(P, q, run, s_qb[w]);
+        bool cut;
+        const uint64_t rem = hd_tile_walk<KS>(P, g, run, a, R, own_box, s_qb[w], s_beg[w], s_pre[w], lt, from,
+                                              own_box ? ~0u : upto, &cut);
+        // decided points get their flags and join their cubes' tallies,
+        // undecided ones are flagged, for k_hd_left to list in order
+        const uint64_t undec = cut ? rem : 0ull;
+        const bool later = (undec >> l) & 1;
+        const uint32_t cnt = R.cnt[l];
+        const bool core = in && cnt >= minpts;
+        if (in && !later) {
+            P.core[q] = core;
+            P.nrec[q] = (uint8_t)rec_count(cnt);
+        }
+        if (later) P.hd_cnt[q] = cnt;
+        if (undec && l == 0) {
+            const uint32_t sh = i0 % kWave;
+            unsigned long long *word = (unsigned long long *)P.hd_mask + i0 / kWave;
+            if (undec << sh) atomicOr(word, (unsigned long long)(undec << sh));
+            if (sh && undec >> (kWave - sh)) atomicOr(word + 1, (unsigned long long)(undec >> (kWave - sh)));
+        }
+        hd_tally(P, in, cell, core, core ? P.sidx[q] : kNone);
+    }
+    flush_tests(P, kTestsCore, lt);
+}
+
+// The points flagged by a pass, in its order, as the next pass' list.  A
+// tile of 256 words per block, taken by ticket, with a look-back over earlier
+// tiles; the pass' unit queues go back to zero for the pass after the next.
+__global__ __launch_bounds__(kBlock) void k_hd_left(Plan P, uint32_t pass)
+{
+    if (box_missed(P)) return;
+    __shared__ uint32_t s_scan[kWavesPerBlock], s_tile;
+    __shared__ uint64_t s_base;
+    if (blockIdx.x == 0 && threadIdx.x < 8)
+        st_agent32(P.ctr->dyn[pass & 1u ? kDynCoreRest : kDynCore] + threadIdx.x * kCounterStride, 0u);
+    const uint32_t n = hd_pass_points(P, pass), words = (n + kWave - 1) / kWave, tiles = (words + kBlock - 1) / kBlock;
+    uint64_t *status = P.hd_status + (uint64_t)pass * (((uint64_t)P.n + kWave * kBlock - 1) / (kWave * kBlock));
+    uint32_t *list = hd_pass_list(P, pass + 1);
+    while (true) {
+        if (threadIdx.x == 0) s_tile = atomicAdd(P.ctr->hd_tickets + pass, 1u);
+        __syncthreads();
+        const uint32_t tile = s_tile;
+        if (tile >= tiles) return;
+        const uint32_t word = tile * kBlock + threadIdx.x;
+        uint64_t m = word < words ? ld_agent(P.hd_mask + word) : 0ull;
+        uint32_t sum;
+        const uint32_t pre = block_exclusive_scan<uint32_t>((uint32_t)__popcll(m), s_scan, &sum);
+        if (threadIdx.x == 0) {
+            s_base = scan_lookback(status, tile, sum);
+            if (tile == tiles - 1) st_agent32(P.ctr->hd_left + pass, (uint32_t)s_base + sum);
+        }
+        __syncthreads();
+        uint32_t at = (uint32_t)s_base + pre;
+        while (m) {
+            const uint32_t i = word * kWave + (uint32_t)__ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
+            list[at++] = hd_pass_point(P, pass, i);
+        }
+        __syncthreads();
+    }
 }
 
 // First cube with a core point of every group (kNone: none).
@@ -1016,6 +1521,29 @@ void launch_hd_lists(const Plan &P, int blocks, hipStream_t s)
     launch_lists_back(P, blocks, s);
 }
 
+template <int KS>
+static void launch_hd_core_tiles(const Plan &P, hipStream_t s)
+{
+    const uint32_t words = (P.n + kTilePts - 1) / kTilePts;
+    // two waves fit a SIMD: 512 workgroups of four fill the chip
+    const int tb = (int)std::min<uint64_t>(512u, (((uint64_t)P.n + kWavesPerBlock - 1) / kWavesPerBlock + 7u) & ~7ull);
+    const int lb = (int)std::min<uint32_t>((words + kBlock - 1) / kBlock, 256u);
+    const int rb = (int)std::min<uint32_t>((P.n + kBlock - 1) / kBlock, 2048u);
+    for (uint32_t pass = 0; pass < P.hd_passes; pass++) {
+        hipLaunchKernelGGL(k_hd_runs, dim3(rb), dim3(kBlock), 0, s, P, pass);
+        hipLaunchKernelGGL(k_hd_core_tiles<KS>, dim3(tb), dim3(kBlock), 0, s, P, pass);
+        if (pass + 1 < P.hd_passes) hipLaunchKernelGGL(k_hd_left, dim3(lb), dim3(kBlock), 0, s, P, pass);
+    }
+}
+
+void launch_hd_planes(const Plan &P, hipStream_t s)
+{
+    const uint64_t chunks = (uint64_t)P.n * 2 * P.hd_steps;
+    const int pb = (int)std::min<uint64_t>((chunks + kBlock - 1) / kBlock, 4096);
+    if (P.hd_steps == 1) hipLaunchKernelGGL(k_hd_planes<1>, dim3(pb), dim3(kBlock), 0, s, P);
+    else hipLaunchKernelGGL(k_hd_planes<2>, dim3(pb), dim3(kBlock), 0, s, P);
+}
+
 void launch_hd_core(const Plan &P, int blocks, hipStream_t s)
 {
     switch (row_form(P)) {
@@ -1023,10 +1551,8 @@ void launch_hd_core(const Plan &P, int blocks, hipStream_t s)
         hipLaunchKernelGGL(k_hd_core<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P);
         hipLaunchKernelGGL(k_hd_core_rest<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P);
         break;
-    case kRowPacked:
-        hipLaunchKernelGGL(k_hd_core<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P);
-        hipLaunchKernelGGL(k_hd_core_rest<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P);
-        break;
+    case kRowPlanes1: launch_hd_core_tiles<1>(P, s); break;
+    case kRowPlanes2: launch_hd_core_tiles<2>(P, s); break;
     default:
         hipLaunchKernelGGL(k_hd_core<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
         hipLaunchKernelGGL(k_hd_core_rest<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
@@ -1041,7 +1567,8 @@ void launch_hd_merge(const Plan &P, int blocks, hipStream_t s)
     hipLaunchKernelGGL(k_hd_unify, dim3(blocks), dim3(kBlock), 0, s, P);
     switch (row_form(P)) {
     case kRowWide: hipLaunchKernelGGL(k_hd_merge<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P); break;
-    case kRowPacked: hipLaunchKernelGGL(k_hd_merge<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P); break;
+    case kRowPlanes1: hipLaunchKernelGGL(k_hd_merge<kRowPlanes1>, dim3(blocks), dim3(kBlock), 0, s, P); break;
+    case kRowPlanes2: hipLaunchKernelGGL(k_hd_merge<kRowPlanes2>, dim3(blocks), dim3(kBlock), 0, s, P); break;
     default: hipLaunchKernelGGL(k_hd_merge<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
     }
 }
@@ -1053,7 +1580,8 @@ void launch_hd_border(const Plan &P, int blocks, hipStream_t s)
     launch_border_list(P, s);
     switch (row_form(P)) {
     case kRowWide: hipLaunchKernelGGL(k_hd_border<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P); break;
-    case kRowPacked: hipLaunchKernelGGL(k_hd_border<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P); break;
+    case kRowPlanes1: hipLaunchKernelGGL(k_hd_border<kRowPlanes1>, dim3(blocks), dim3(kBlock), 0, s, P); break;
+    case kRowPlanes2: hipLaunchKernelGGL(k_hd_border<kRowPlanes2>, dim3(blocks), dim3(kBlock), 0, s, P); break;
     default: hipLaunchKernelGGL(k_hd_border<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
     }
 }

@@ -11,9 +11,9 @@ constexpr int kMaxDim = 8;                     // axes of the packed cube key
 constexpr int kMaxDimHigh = 64;                // axes of a point (more than 8: hashed cubes)
 constexpr int kRec = 16;                       // neighbours recorded per point by core marking
 // More than kMaxDim axes: candidates a point of the first core pass looks at
-// before it is left to the second pass (which walks chunks of such points
-// only); the host may lower it per call.
+// before it is left to the next pass; the host may lower it per call.
 constexpr uint32_t kHdCoreBudget = 16384;
+constexpr int kHdPasses = 6;                   // core passes on byte planes, at most
 // Cube mode for d <= 2: core marking with one lane per point of a sparse cube
 // when the cube-offset radius is at most kColR, each lane testing at most
 // kCoreLaneBudget candidates before a wave-wide walk takes its point over.
@@ -82,7 +82,9 @@ struct Counters {
     uint32_t nbr_overflow;      // groups whose neighbour list did not fit
     uint32_t hmask;             // hash slots in use - 1 (a power of two - 1)
     uint32_t nbr_ticket;        // tiles of the backward-list scan
-    uint32_t hd_left;           // more than kMaxDim axes: points left undecided by the first core pass
+    uint32_t hd_left[kHdPasses];    // more than kMaxDim axes: points left undecided by each core pass
+    uint32_t hd_runs[kHdPasses];    // runs of each core pass
+    uint32_t hd_tickets[kHdPasses]; // tiles of the scans of their lists
     uint32_t n_blist;           // non-core points left for the border walk (blist)
     uint32_t n_sparse;          // cube-mode points of cubes with fewer than minPts points (core_list)
     uint32_t n_defer;           // of those, points whose candidate budget ran out (core_defer)
@@ -158,6 +160,7 @@ struct Plan {
     uint32_t kd;
     uint8_t kdim[kMaxDim];
     const int32_t *hd_origin;   // [d] origin of every axis (hd)
+    const int32_t *hd_centre;   // [kMaxDimHigh] origin plus half the span, 0 past d (hd)
     // a call planned from the previous calls' box: the word its box
     // comparison writes (1: the box differs, and every kernel from core
     // marking on returns at once); null otherwise
@@ -167,8 +170,19 @@ struct Plan {
     uint8_t *nrec;              // [n] neighbours found when at most kRec (then all are recorded), else
                                 // kRec + 1; 0 for points of cubes with minPts points
     uint32_t *blist;            // [n] non-core points whose neighbours were not all recorded (with rec)
-    uint32_t hd16;              // packed rows wanted (hd, every span below 2^15 and 32-bit sums)
-    uint32_t *spts16;           // [n][sd / 2] sorted points less the origin as packed int16 pairs, or null
+    // byte planes of the sorted points (hd, every span below 2^15 and 32-bit
+    // sums; else null): rows of 16 hd_steps words, and the negated squared
+    // norms of the points less the centre
+    uint32_t hd_steps;          // 1 up to 32 axes, 2 above; 0: no planes
+    int32_t *planes;            // [n][16 hd_steps]
+    int32_t *nnorm;             // [n]
+    uint64_t *hd_mask;          // [ceil(n / 64)] points a pass of core marking left undecided
+    uint32_t *hd_run_at;        // [n] runs of a pass: place of the first point in the pass' order
+    uint64_t *hd_run_mask;      // [n] and which of the 64 points from there on belong to it
+    uint32_t *hd_cnt;           // [n] neighbours found so far of points left undecided
+    uint64_t *hd_status;        // look-back words of the lists
+    uint32_t hd_passes;         // core-marking passes, and the candidates of a point's list after each
+    uint32_t hd_limit[kHdPasses];
     // cube mode, one lane per point: the largest cube-offset radius R of the
     // call (of any data set in a batch), the candidates a lane tests before
     // it leaves the point to a wave-wide walk, and the two point lists
