@@ -84,50 +84,84 @@ __global__ __launch_bounds__(kBlock) void k_hd_planes(Plan P)
 }
 
 // ---------------------------------------------------------------------------
-// Point box of every group over all axes (lane e owns axis e), the backward
-// list counters cleared, and "no core cube yet" for every group.
+// Point box of every group over all axes.  Groups are very uneven (one point
+// to tens of thousands), so the points are cut into chunks of kBoxChunk and a
+// wave takes the boxes of the stretches of groups in its chunk; a group that
+// lies in several chunks is folded together with atomics.  (54 axes, 3.85M
+// points: 5.3 ms with a wave per group, 0.38 ms this way.)
 // ---------------------------------------------------------------------------
+constexpr uint32_t kBoxChunk = kWave;
+
+// Before it: backward list counters cleared, "no core cube yet" and "one
+// root" for every group, and an empty box for the groups of several chunks.
+__global__ __launch_bounds__(kBlock) void k_hd_group_init(Plan P)
+{
+    if (box_missed(P)) return;
+    const uint32_t sd = P.sd, ng = ld_agent32(&P.ctr->n_groups);
+    for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < ng; g += gridDim.x * kBlock) {
+        st_agent32(P.nbr_bcount + g, 0u);
+        st_agent32(P.nbr_bcursor + g, 0u);
+        st_agent32(P.gcube + g, kNone);
+        P.unified[g] = 1;
+        if (P.group_start[g] / kBoxChunk == (P.group_start[g + 1] - 1) / kBoxChunk) continue;
+        uint32_t *box = (uint32_t *)(P.gbox + (uint64_t)g * 2 * sd);
+        for (uint32_t e = 0; e < sd; e++) {
+            st_agent32(box + e, (uint32_t)INT32_MAX);
+            st_agent32(box + sd + e, (uint32_t)INT32_MIN);
+        }
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_hd_group_box(Plan P)
 {
     if (box_missed(P)) return;
-    const uint32_t l = lane_id(), sd = P.sd;
-    const uint32_t ng = ld_agent32(&P.ctr->n_groups);
+    // lane (row, axis): kWave / sd rows at a time
+    const uint32_t l = lane_id(), sd = P.sd, rows = kWave / sd, row = l / sd, axis = l - row * sd;
+    const bool in = row < rows;
+    const uint32_t chunks = (P.n + kBoxChunk - 1) / kBoxChunk;
     const WaveRange hca_wr_ = wave_range(P.order);
-    HCA_FOR_UNITS(g, ng) {
-        const uint32_t p0 = P.group_start[g], p1 = P.group_start[g + 1];
-        if (l < sd) {
+    HCA_FOR_UNITS(u, chunks) {
+        const uint32_t c0 = u * kBoxChunk, c1 = min(P.n, c0 + kBoxChunk);
+        const uint32_t pg = P.group_of[P.cell_of[min(c0 + l, c1 - 1)]];
+        const uint32_t pg0 = P.group_start[pg], pg1 = P.group_start[pg + 1];
+        for (uint32_t s = c0; s < c1;) {
+            const uint32_t g = lane_value(pg, s - c0), g0 = lane_value(pg0, s - c0), g1 = lane_value(pg1, s - c0);
+            const uint32_t e = min(g1, c1);
             int32_t lo = INT32_MAX, hi = INT32_MIN;
-            const int32_t *col = P.spts + l;
-            uint32_t q = p0;
-            // sixteen rows in flight at once
-            for (; q + 16 <= p1; q += 16) {
+            const int32_t *col = P.spts + axis;
+            uint32_t q = s + row;
+            // sixteen rows in flight per lane
+            for (; in && q + 15 * rows < e; q += 16 * rows) {
                 int32_t v[16];
 #pragma unroll
-                for (int u = 0; u < 16; u++) v[u] = col[(uint64_t)(q + u) * sd];
+                for (int i = 0; i < 16; i++) v[i] = col[(uint64_t)(q + i * rows) * sd];
 #pragma unroll
-                for (int u = 0; u < 16; u++) {
-                    lo = min(lo, v[u]);
-                    hi = max(hi, v[u]);
+                for (int i = 0; i < 16; i++) {
+                    lo = min(lo, v[i]);
+                    hi = max(hi, v[i]);
                 }
             }
-            for (; q + 4 <= p1; q += 4) {
-                const int32_t a = col[(uint64_t)q * sd], b = col[(uint64_t)(q + 1) * sd];
-                const int32_t c = col[(uint64_t)(q + 2) * sd], e = col[(uint64_t)(q + 3) * sd];
-                lo = min(lo, min(min(a, b), min(c, e)));
-                hi = max(hi, max(max(a, b), max(c, e)));
+            for (; in && q < e; q += rows) {
+                const int32_t v = col[(uint64_t)q * sd];
+                lo = min(lo, v);
+                hi = max(hi, v);
             }
-            for (; q < p1; q++) {
-                const int32_t a = col[(uint64_t)q * sd];
-                lo = min(lo, a);
-                hi = max(hi, a);
+            int32_t l0 = lo, h0 = hi;
+            for (uint32_t k = 1; k < rows; k++) {
+                l0 = min(l0, __shfl(lo, axis + k * sd));
+                h0 = max(h0, __shfl(hi, axis + k * sd));
             }
-            P.gbox[(uint64_t)g * 2 * sd + l] = lo;
-            P.gbox[(uint64_t)g * 2 * sd + sd + l] = hi;
-        }
-        if (l == 0) {
-            st_agent32(P.nbr_bcount + g, 0u);
-            st_agent32(P.nbr_bcursor + g, 0u);
-            st_agent32(P.gcube + g, kNone);
+            if (l < sd) {
+                int32_t *box = P.gbox + (uint64_t)g * 2 * sd;
+                if (g0 / kBoxChunk == (g1 - 1) / kBoxChunk) {
+                    box[l] = l0;
+                    box[sd + l] = h0;
+                } else {
+                    atomicMin(box + l, l0);
+                    atomicMax(box + sd + l, h0);
+                }
+            }
+            s = e;
         }
     }
 }
@@ -425,7 +459,9 @@ __device__ __forceinline__ uint32_t hd_load_neighbours(const Plan &P, uint32_t g
     if (j < src.slots) {
         const uint32_t G = hd_slot(P, g, src, j);
         const int32_t *gb = P.gbox + (uint64_t)G * 2 * sd;
-        bool keep = !(need_core && P.gcube[G] == kNone) && (!qb || hd_box_gap2(qb, gb, sd, eps2) <= eps2);
+        bool keep = !(need_core && P.gcube[G] == kNone);
+        if (keep && skip_root != kNone && P.unified[G] && uf_find(P.parent, P.gcube[G]) == skip_root) keep = false;
+        keep = keep && (!qb || hd_box_gap2(qb, gb, sd, eps2) <= eps2);
         if (keep && __popc(mask) > 1) {
             bool nearby = false;
 #pragma unroll
@@ -433,7 +469,6 @@ __device__ __forceinline__ uint32_t hd_load_neighbours(const Plan &P, uint32_t g
                 if (!nearby && (mask & (1u << k))) nearby = hd_point_box_gap2(own[k], gb, sd, eps2) <= eps2;
             keep = nearby;
         }
-        if (keep && skip_root != kNone && P.unified[G] && uf_find(P.parent, P.gcube[G]) == skip_root) keep = false;
         if (keep) {
             a = P.group_start[G];
             size = P.group_start[G + 1] - a;
@@ -1181,13 +1216,22 @@ __global__ __launch_bounds__(kBlock) void k_hd_left(Plan P, uint32_t pass)
     }
 }
 
-// First cube with a core point of every group (kNone: none).
+// First cube with a core point of every group (kNone: none).  A group's cubes
+// are consecutive, so only the first of a wave's core cubes in each group is
+// offered (an atomic per core cube had groups of 10^4 cubes queue up on one
+// address: 2.8 ms at 3.4M core cubes, 0.07 ms this way).
 __global__ __launch_bounds__(kBlock) void k_hd_gcore(Plan P)
 {
     if (box_missed(P)) return;
     const uint32_t nc = ld_agent32(&P.ctr->n_cells);
-    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < nc; c += gridDim.x * kBlock)
-        if (P.ncore[c]) atomicMin(P.gcube + P.group_of[c], c);
+    for (uint32_t base = blockIdx.x * kBlock; base < nc; base += gridDim.x * kBlock) {
+        const uint32_t c = base + threadIdx.x;
+        const bool core = c < nc && P.ncore[c] > 0;
+        const uint32_t g = core ? P.group_of[c] : kNone;
+        const uint64_t earlier = __ballot(core) & __lanemask_lt();
+        const uint32_t prev = __shfl(g, earlier ? 63 - __clzll((long long)earlier) : 0);
+        if (core && (!earlier || prev != g)) atomicMin(P.gcube + g, c);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,11 +1311,12 @@ __global__ __launch_bounds__(kBlock) void k_hd_merge(Plan P)
     const DynRange dr_ = dyn_range(P.ctr->dyn[kDynMerge], P.order);
     HCA_FOR_UNITS_DYN(u, (n + kPch - 1) / kPch, dr_) {
         const uint32_t pc = u * kPch, np = min((uint32_t)kPch, n - pc);
-        const bool core = l < np && P.core[pc + l];
-        const uint32_t live = (uint32_t)__ballot(core) & all;
-        if (!live) continue;
+        bool core = l < np && P.core[pc + l];
         const uint32_t cell = core ? P.cell_of[pc + l] : kNone;
         const uint32_t grp = core ? P.group_of[cell] : kNone;
+        core = core && P.groot[grp];
+        const uint32_t live = (uint32_t)__ballot(core) & all;
+        if (!live) continue;
         uint32_t ck[kPch];
 #pragma unroll
         for (int k = 0; k < kPch; k++) ck[k] = lane_value(cell, k);
@@ -1337,26 +1382,45 @@ __global__ __launch_bounds__(kBlock) void k_link_recorded(Plan P)
     }
 }
 
-// Before the walk: whether all core cubes of each group share one root
-// (one wave per group; the group's cubes are consecutive).
+// Before the walk: whether all core cubes of each group share one root (a
+// thread per cube; the flag starts as "yes").
 __global__ __launch_bounds__(kBlock) void k_hd_unify(Plan P)
 {
     if (box_missed(P)) return;
-    const uint32_t l = lane_id();
-    const uint32_t ng = ld_agent32(&P.ctr->n_groups);
+    const uint32_t nc = ld_agent32(&P.ctr->n_cells);
+    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < nc; c += gridDim.x * kBlock) {
+        if (!P.ncore[c]) continue;
+        const uint32_t g = P.group_of[c], first = P.gcube[g];
+        if (c != first && uf_find(P.parent, c) != uf_find(P.parent, first)) P.unified[g] = 0;
+    }
+}
+
+// Then the groups whose points have to walk at all (groot = 1): not when the
+// group's core cubes and those of every group after it in its list share one
+// root.  On blobs the recorded pairs have joined nearly everything, and the
+// walk is left with the few groups at the seams (54 axes, 3.85M points: merge
+// 36.9 ms with every core point walking, 4.5 ms this way).
+__global__ __launch_bounds__(kBlock) void k_hd_need(Plan P)
+{
+    if (box_missed(P)) return;
+    const uint32_t l = lane_id(), ng = ld_agent32(&P.ctr->n_groups);
     const WaveRange hca_wr_ = wave_range(P.order);
     HCA_FOR_UNITS(g, ng) {
-        const uint32_t first = P.gcube[g];
-        bool unified = first != kNone;
-        if (unified) {
-            const uint32_t r0 = uf_find(P.parent, first), c1 = P.group_cell[g + 1];
-            for (uint32_t cb = first; cb < c1 && unified; cb += kWave) {
-                const uint32_t c = cb + l;
-                const bool other = c < c1 && P.ncore[c] > 0 && uf_find(P.parent, c) != r0;
-                unified = __ballot(other) == 0;
+        const uint32_t first = uniform(P.gcube[g]);
+        bool need = false;
+        if (first != kNone) {
+            need = !P.unified[g];
+            const uint32_t r = uf_find(P.parent, first), at = P.nbr_start[g], cnt = P.nbr_count[g];
+            for (uint32_t j = 0; j < cnt && !need; j += kWave) {
+                bool other = false;
+                if (j + l < cnt) {
+                    const uint32_t G = P.nbr[at + j + l], f = P.gcube[G];
+                    other = f != kNone && !(P.unified[G] && uf_find(P.parent, f) == r);
+                }
+                need = __ballot(other) != 0;
             }
         }
-        if (l == 0) P.unified[g] = unified;
+        if (l == 0) P.groot[g] = need;
     }
 }
 
@@ -1507,6 +1571,8 @@ void launch_link_recorded(const Plan &P, hipStream_t s)
 
 void launch_hd_lists(const Plan &P, int blocks, hipStream_t s)
 {
+    const int ib = (int)std::min<uint64_t>((P.n + kBlock - 1) / kBlock, 1024);
+    hipLaunchKernelGGL(k_hd_group_init, dim3(ib), dim3(kBlock), 0, s, P);
     hipLaunchKernelGGL(k_hd_group_box, dim3(blocks), dim3(kBlock), 0, s, P);
     switch (P.kd) {
     case 1: hipLaunchKernelGGL(k_hd_lists<1>, dim3(blocks), dim3(kBlock), 0, s, P); break;
@@ -1564,7 +1630,9 @@ void launch_hd_core(const Plan &P, int blocks, hipStream_t s)
 void launch_hd_merge(const Plan &P, int blocks, hipStream_t s)
 {
     launch_link_recorded(P, s);
-    hipLaunchKernelGGL(k_hd_unify, dim3(blocks), dim3(kBlock), 0, s, P);
+    const int cb = (int)std::min<uint64_t>((P.n + kBlock - 1) / kBlock, 2048);
+    hipLaunchKernelGGL(k_hd_unify, dim3(cb), dim3(kBlock), 0, s, P);
+    hipLaunchKernelGGL(k_hd_need, dim3(blocks), dim3(kBlock), 0, s, P);
     switch (row_form(P)) {
     case kRowWide: hipLaunchKernelGGL(k_hd_merge<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P); break;
     case kRowPlanes1: hipLaunchKernelGGL(k_hd_merge<kRowPlanes1>, dim3(blocks), dim3(kBlock), 0, s, P); break;
