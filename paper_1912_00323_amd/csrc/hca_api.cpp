@@ -398,6 +398,11 @@ struct hca_ctx {
     uint32_t *check_host = nullptr, *check_dev = nullptr;   // the comparison's flag (mapped, coherent)
     uint32_t *miss_dev = nullptr;     // the same flag in device memory, for the kernels from core marking on
     int64_t reuse_calls = 0, reuse_reruns = 0;
+    // the last call that the all-pairs path gave back to the general one
+    // (not tried again for the same shape and radius)
+    uint32_t back_n = 0;
+    int32_t back_d = 0;
+    int64_t back_eps2 = 0;
     void *io = nullptr;               // staging for hca_cluster_host
     size_t io_size = 0;
     void *aligned = nullptr;          // rows of a call whose points are off their vector alignment
@@ -820,6 +825,7 @@ void fill_stats(hca_ctx *ctx, const Plan &P, hca_stats *stats)
 constexpr size_t kPinnedOrigin = align256(std::max(sizeof(int32_t) * kBboxBlocks * 2 * kMaxDimHigh,
                                                    sizeof(Counters)));
 constexpr size_t kPinnedBytes = kPinnedOrigin + 2 * sizeof(int32_t) * kMaxDimHigh;
+constexpr size_t kSmallReport = 16;            // word of the mapped flags that an all-pairs call reports from
 constexpr uint64_t kHdListMax = 1ull << 30;   // neighbour-list entries, at most
 
 // Init, sort, cube and group tables, lookup and neighbour lists; the host
@@ -1018,6 +1024,108 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
     return HCA_OK;
 }
 
+// ---- small calls -----------------------------------------------------------------
+// Points up to which a call is clustered by all pairs (hca_small.hip), by
+// where the two paths meet on blobs (us, grid against all pairs: 1-D 8k 126,
+// 103, 12k 127, 137; 2-D 12k 177, 144, 16k 178, 193; 3-D 16k 343, 226; 4-D 16k
+// 476, 265; 8-D 16k 417, 292, wide distances 439, 474; 16-D 16k 656, 227).  Any
+// of the general path's test knobs keeps a call on that path; HCA_SMALL=k: up
+// to k points (0: never).
+uint32_t small_limit(int32_t d)
+{
+    for (const char *e : {"HCA_SEARCH", "HCA_RECORD", "HCA_PREFIX", "HCA_HD_BUDGET", "HCA_CORE_LANES", "HCA_CORE_BUDGET",
+                          "HCA_SORT_THREADS", "HCA_SORT_TILE", "HCA_MERGE_SPLIT", "HCA_ORDER", "HCA_REPS",
+                          "HCA_CUBE_LISTS", "HCA_LIST_SLAB", "HCA_WAVE_BLOCKS", "HCA_HASH_BITS", "HCA_PACKED"})
+        if (std::getenv(e)) return 0;
+    if (const char *e = std::getenv("HCA_SMALL")) return (uint32_t)std::min<long>(std::max(0l, std::atol(e)), kSmallMax);
+    return d == 1 ? 8192u : d == 2 || (d >= 5 && d <= kMaxDim) ? 12288u : kSmallMax;
+}
+
+// A small call by all pairs.  *taken is false when the data are left to the
+// general path (nothing was written then).  No host round trip but the final
+// wait; the box and the verdict come back through mapped memory.
+hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, int64_t eps2, int32_t min_pts,
+                     int32_t *labels, uint8_t *core_out, bool *taken)
+{
+    *taken = false;
+    hipStream_t s = ctx->stream;
+    HCA_HIP(hipSetDevice(ctx->device), "hipSetDevice");
+    SmallArgs A;
+    std::memset(&A, 0, sizeof A);
+    A.pts = points;
+    A.n = n;
+    A.np = (n + kWave - 1) / kWave * kWave;
+    A.d = d;
+    A.min_pts = min_pts;
+    A.eps2 = eps2;
+    A.side = std::max<uint64_t>(1, isqrt_u64((uint64_t)eps2 / (uint64_t)d));
+    A.boxes = std::min<uint32_t>(kSmallBoxes, (n * (uint32_t)d + 4 * kBlock - 1) / (4 * kBlock));
+    A.labels = labels;
+    A.core_out = core_out;
+    A.report = ctx->check_dev + kSmallReport;
+    const size_t ks = d <= kMaxDim ? 0 : d <= 32 ? 1 : 2;
+    auto carve = [&](char *base) {
+        Carver cv{base};
+        A.partial = cv.take<int32_t>((size_t)kSmallBoxes * 2 * d);
+        A.cnt = cv.take<uint32_t>(A.np);
+        A.parent = cv.take<uint32_t>(A.np);
+        A.near = cv.take<uint32_t>(A.np);
+        A.planes = cv.take<int32_t>((size_t)A.np * 16 * ks);
+        A.nnorm = cv.take<int32_t>(ks ? A.np : 0);
+        A.lim = cv.take<int32_t>(ks ? A.np : 0);
+        A.adj = cv.take<uint32_t>((size_t)((n + 31) / 32) * A.np);
+        return cv.off;
+    };
+    hca_status st = workspace(ctx, carve(nullptr));
+    if (st) return st;
+    carve(ws_base(ctx));
+    // up to eight axes the box takes part in plan reuse as that of any call
+    const bool ahead = d <= kMaxDim && ctx->reuse && ctx->box_armed && !ctx->fixed && ctx->box_n == n && ctx->box_d == d;
+    if (ahead) {
+        A.planned = 1;
+        for (int k = 0; k < d; k++) {
+            A.expect.mn[k] = ctx->box_mn[k];
+            A.expect.mx[k] = ctx->box_mx[k];
+        }
+    }
+    launch_small(A, s);
+    HCA_HIP(hipGetLastError(), "kernel launch");
+    HCA_HIP(hipStreamSynchronize(s), "clustering sync");
+    const uint32_t *report = ctx->check_host + kSmallReport;
+    const uint32_t verdict = __atomic_load_n(report, __ATOMIC_ACQUIRE);
+    if (ahead) {
+        ctx->reuse_calls++;
+        if (verdict) {
+            // planned from another box: run again from its own
+            ctx->box_armed = false;
+            ctx->reuse_reruns++;
+            if (verdict == 1) return run_small(ctx, points, n, d, eps2, min_pts, labels, core_out, taken);
+        }
+    }
+    if (verdict) {
+        ctx->back_n = n;
+        ctx->back_d = d;
+        ctx->back_eps2 = eps2;
+        return HCA_OK;
+    }
+    *taken = true;
+    if (!ahead && d <= kMaxDim) {
+        const int32_t *box = (const int32_t *)report + 1;
+        bool same = ctx->box_have && ctx->box_n == n && ctx->box_d == d;
+        for (int k = 0; k < d; k++) same = same && ctx->box_mn[k] == box[k] && ctx->box_mx[k] == box[d + k];
+        ctx->box_armed = same;
+        ctx->box_have = true;
+        ctx->box_n = n;
+        ctx->box_d = d;
+        for (int k = 0; k < d; k++) {
+            ctx->box_mn[k] = box[k];
+            ctx->box_mx[k] = box[d + k];
+        }
+    }
+    for (float &ms : ctx->phase_ms) ms = 0.f;
+    return HCA_OK;
+}
+
 hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, double eps,
                int32_t min_pts, int32_t *labels, uint8_t *core_out, hca_stats *stats)
 {
@@ -1032,16 +1140,27 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
         return fail(ctx, HCA_E_INVAL, "points and labels must be aligned to 4 bytes (int32)");
     if (stats) std::memset(stats, 0, sizeof *stats);
     if (n64 == 0) return HCA_OK;
+    // rows are read with 8- or 16-byte vector loads when d is 2, 4 or 8
+    const uintptr_t row_align = d == 2 ? 8 : (d == 4 || d == 8) ? 16 : 4;
+    if (n64 <= (int64_t)kSmallMax && ctx->exact && !stats && ctx->prof == -1 && ctx->check_dev &&
+        n64 <= (int64_t)small_limit(d) && !(ctx->fixed && (uintptr_t)points % row_align)) {
+        int64_t eps2;
+        exact_eps2(eps, &eps2);
+        if (!(ctx->back_n == (uint32_t)n64 && ctx->back_d == d && ctx->back_eps2 == eps2)) {
+            bool taken;
+            const hca_status st = run_small(ctx, points, (uint32_t)n64, d, eps2, min_pts, labels, core_out, &taken);
+            if (st || taken) return st;
+        }
+    }
     if (d > kMaxDim) return run_hd(ctx, points, (uint32_t)n64, d, eps, min_pts, labels, core_out, stats);
     const uint32_t n = (uint32_t)n64;
     const int32_t *const points_in = points;
     hipStream_t s = ctx->stream;
     HCA_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     {
-        // rows are read with 8- or 16-byte vector loads when d is 2, 4 or 8:
-        // rows that start off that alignment are first copied to an aligned
-        // staging buffer on the stream
-        const uintptr_t need = d == 2 ? 8 : (d == 4 || d == 8) ? 16 : 4;
+        // rows that start off their vector alignment are first copied to an
+        // aligned staging buffer on the stream
+        const uintptr_t need = row_align;
         if ((uintptr_t)points % need && ctx->fixed)
             return fail(ctx, HCA_E_INVAL, "without allocation, points must be aligned to 8 bytes (d = 2) or 16 "
                                           "bytes (d = 4, 8)");

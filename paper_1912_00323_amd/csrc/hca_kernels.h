@@ -55,6 +55,32 @@ void launch_link_recorded(const Plan &P, hipStream_t s);
 // the non-core points whose neighbours were not all recorded into P.blist
 void launch_border_list(const Plan &P, hipStream_t s);
 
+// small calls by all pairs (hca_small.hip)
+constexpr uint32_t kSmallMax = 16384;          // points, at most
+constexpr uint32_t kSmallBoxes = 32;           // blocks of the box pass
+struct SmallArgs {
+    const int32_t *pts;         // [n][d] input order
+    uint32_t n, np;             // points; rounded up to a multiple of 64
+    int32_t d;
+    int32_t min_pts;
+    int64_t eps2;
+    uint64_t side;              // cube side of the general path (d <= kMaxDim)
+    uint32_t planned;           // compare the box with expect (d <= kMaxDim)
+    BoxExpect expect;
+    uint32_t boxes;
+    int32_t *partial;           // [boxes][2][d]
+    uint32_t *adj;              // [ceil(n / 32)][np] bit k of word w of point i: point 32 w + k within eps
+    uint32_t *cnt;              // [np] neighbours
+    uint32_t *parent;           // [np] union-find over the core points
+    uint32_t *near;             // [np] the point itself if core, else its nearest core neighbour, or kNone
+    int32_t *planes;            // d > kMaxDim: byte planes, negated norms and limits
+    int32_t *nnorm, *lim;
+    int32_t *labels;
+    uint8_t *core_out;          // or null
+    uint32_t *report;           // host memory: verdict, then the box [2][d] (d <= kMaxDim)
+};
+void launch_small(const SmallArgs &A, hipStream_t s);
+
 // batches: stage the data sets of one dimension d <= 4 contiguously (rows and
 // their data set, read from each data set's own rows) and take their bounding
 // boxes; labels back to each data set's own array
