@@ -398,10 +398,10 @@ struct hca_ctx {
     uint32_t *check_host = nullptr, *check_dev = nullptr;   // the comparison's flag (mapped, coherent)
     uint32_t *miss_dev = nullptr;     // the same flag in device memory, for the kernels from core marking on
     int64_t reuse_calls = 0, reuse_reruns = 0;
-    // the last call that the all-pairs path gave back to the general one
-    // (not tried again for the same shape and radius)
-    uint32_t back_n = 0;
-    int32_t back_d = 0;
+    // the dimension and radius of the last call that the all-pairs path gave
+    // back to the general one, and how many more calls of that kind go there
+    // straight away
+    int32_t back_d = 0, back_left = 0;
     int64_t back_eps2 = 0;
     void *io = nullptr;               // staging for hca_cluster_host
     size_t io_size = 0;
@@ -1103,7 +1103,7 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
         }
     }
     if (verdict) {
-        ctx->back_n = n;
+        ctx->back_left = 64;
         ctx->back_d = d;
         ctx->back_eps2 = eps2;
         return HCA_OK;
@@ -1146,7 +1146,9 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
         n64 <= (int64_t)small_limit(d) && !(ctx->fixed && (uintptr_t)points % row_align)) {
         int64_t eps2;
         exact_eps2(eps, &eps2);
-        if (!(ctx->back_n == (uint32_t)n64 && ctx->back_d == d && ctx->back_eps2 == eps2)) {
+        if (ctx->back_left > 0 && ctx->back_d == d && ctx->back_eps2 == eps2) {
+            ctx->back_left--;
+        } else {
             bool taken;
             const hca_status st = run_small(ctx, points, (uint32_t)n64, d, eps2, min_pts, labels, core_out, &taken);
             if (st || taken) return st;
