@@ -659,8 +659,7 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
     P.parent = cv.take<uint32_t>(n);
     P.gcube = cv.take<uint32_t>(n);
     P.unified = cv.take<uint8_t>(n);
-    P.tile_start = cv.take<uint32_t>(n);
-    P.groot = P.tile_start;             // free once the intra-group tiles are linked
+    P.groot = cv.take<uint32_t>(n);
     P.group_of = cv.take<uint32_t>(n);
     if (P.nbr_cap) {
         P.nbr_count = cv.take<uint32_t>(n);
@@ -684,6 +683,9 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
     P.rep_chunks = lanes ? P.work + 2 * (size_t)n : nullptr;
 
     P.owner = cv.take<uint32_t>(n);
+    // 2 d <= 16 words per 64 positions fit the owners' n words (which take
+    // whole 256-byte blocks, so also for a single chunk)
+    P.cbox = (int32_t *)P.owner;
     P.cmin = cv.take<uint32_t>(n);
     P.minmem = cv.take<uint32_t>(n);
     P.wrank = cv.take<uint32_t>(((size_t)n + 31) / 32);
@@ -698,7 +700,6 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
     B.status = cv.take<uint64_t>((size_t)P.passes * Z.sort_tiles * kRadix);
     P.scan_status = cv.take<uint64_t>((size_t)2 * Z.scan_tiles + 64);
     P.first = cv.take<uint32_t>(((size_t)n + 31) / 32);
-    P.tile_status = cv.take<uint64_t>((size_t)Z.scan_tiles + 64);
     P.hd_status = P.hd ? cv.take<uint64_t>(kHdPasses * ((size_t)n / (kWave * kBlock) + 1)) : nullptr;
     P.nbr_status = P.nbr_cap ? cv.take<uint64_t>((size_t)Z.scan_tiles + 64) : nullptr;
     *zero_bytes = cv.off - zstart;

@@ -2060,13 +2060,20 @@ __global__ __launch_bounds__(kBlock) void k_merge_exact(Plan P)
 // two cubes.  Pairs of unified groups are handled as they are found; the
 // others are queued and spread over all waves.
 // ---------------------------------------------------------------------------
-// Intra-group pairs are cut into 64 x 64 tiles of points.  Groups of one cube
-// need none (a cube is one union-find node); a group of one chunk (at most 64
-// points) is one tile, taken by the wave that takes the group; the tiles of
-// larger groups are dealt to all waves so that a group of thousands of points
-// does not rest on one wave.  Groups beyond kTileMaxChunks chunks (8192
-// points) are linked cube pair by cube pair in k_merge_big, whose work grows
-// with their cubes rather than their points.
+// The sorted positions are cut into chunks of 64, and each chunk's core
+// points get a box (lo > hi: none).  Linking takes the rows of a chunk against
+// the columns of other chunks, 64 chunk boxes at a time, and visits the
+// chunks within eps of the rows' box only; of those, only the rows within
+// eps of the chunk's box.  Points lie in cube order, so a chunk is small
+// against a group, and most tiles of a pair of large groups fall away.
+// Before, every 64 x 64 tile was walked row by row, and a pair of groups that
+// never touch was one wave's work (5-D, 1.2M points: intra 0.99 -> 0.21 ms, pairs
+// between groups 2.43 -> 0.06 ms).
+//
+// Groups of one cube need no links of their own (a cube is one union-find
+// node).  Groups beyond kTileMaxChunks chunks (8192 points) are linked cube
+// pair by cube pair in k_merge_big, whose work grows with their cubes rather
+// than their points.
 constexpr uint32_t kTileMaxChunks = 128;
 
 // Chunks of group g's points when it has at least two cubes, else 0.
@@ -2076,139 +2083,205 @@ __device__ __forceinline__ uint32_t group_chunks(const Plan &P, uint32_t g)
     return (P.group_start[g + 1] - P.group_start[g] + kWave - 1) / kWave;
 }
 
-// Tiles of group g dealt to all waves (groups of 2..kTileMaxChunks chunks).
-__device__ __forceinline__ uint32_t dealt_tiles(uint32_t nc)
-{
-    return nc < 2 || nc > kTileMaxChunks ? 0 : nc * (nc + 1) / 2;
-}
-
-// Exclusive prefix of the tile counts over groups; the total goes to the
-// counters.
-__global__ __launch_bounds__(kBlock) void k_tile_scan(Plan P, uint64_t *status, uint32_t *ticket)
+template <int D, bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_core_box(Plan P)
 {
     if (box_missed(P)) return;
-    __shared__ uint32_t s_red[kBlock / kWave];
-    __shared__ uint32_t s_tile, s_excl;
-    const uint32_t t = threadIdx.x;
-    const uint32_t ng = ld_agent32(&P.ctr->n_groups);
-    if (t == 0) s_tile = atomicAdd(ticket, 1u);
-    __syncthreads();
-    const uint32_t tile = s_tile, base = tile * kScanTile, g0 = base + t * kScanItems;
-    // kScanItems consecutive groups per thread: one block scan per tile
-    uint32_t f[kScanItems];
-    uint32_t local = 0, big = 0;
+    const uint32_t l = lane_id(), chunks = (P.n + kWave - 1) / kWave;
+    for (uint32_t c = blockIdx.x * kWavesPerBlock + wave_in_block(); c < chunks; c += gridDim.x * kWavesPerBlock) {
+        const uint32_t q = c * kWave + l;
+        const bool core = q < P.n && P.core[q];
+        const Pt<D> p = load_pt<D>(P.spts, min(q, P.n - 1));
+        int32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < kScanItems; j++) {
-        const uint32_t nc = g0 + j < ng ? group_chunks(P, g0 + j) : 0u;
-        f[j] = dealt_tiles(nc);
-        big += nc > kTileMaxChunks;
-        local += f[j];
+        for (int e = 0; e < D; e++) {
+            const int32_t lo = wave_min(core ? p.x[e] : INT32_MAX), hi = wave_max(core ? p.x[e] : INT32_MIN);
+            if (l == (uint32_t)e) mine = lo;
+            if (l == (uint32_t)(D + e)) mine = hi;
+        }
+        if (l < 2u * D) P.cbox[(uint64_t)c * (2 * D) + l] = mine;
     }
-    if (big) atomicAdd(&P.ctr->n_big_groups, big);
-    uint32_t agg;
-    const uint32_t before = block_exclusive_scan<uint32_t>(local, s_red, &agg);
-    if (t < kWave) {
-        const uint32_t e = (uint32_t)scan_lookback_wave(status, tile, agg);
-        if (t == 0) s_excl = e;
-    }
-    __syncthreads();
-    uint32_t run = s_excl + before;
-#pragma unroll
-    for (int j = 0; j < kScanItems; j++) {
-        if (g0 + j < ng) P.tile_start[g0 + j] = run;
-        run += f[j];
-    }
-    if (t == 0 && base + kScanTile >= ng) st_agent32(&P.ctr->n_tiles, s_excl + agg);
 }
 
-// One 64 x 64 tile of a group's point pairs, rows [i0, i0 + 64) against
-// columns [j0, j0 + 64) of the group's points [a0, a1), by one wave.  Lane l
-// holds point l of the column chunk and its cube's root; the row chunk's
-// points sit in LDS and are visited one at a time.  A pair within eps links
-// its two cubes only when the cached roots differ; roots are refreshed after
-// any link.
-template <int D, bool WIDE>
-__device__ __forceinline__ void group_tile(const Plan &P, uint32_t a0, uint32_t a1, uint32_t i0, uint32_t j0,
-                                           int32_t (*s_pt)[D], uint32_t &lt)
+// Squared gap between the box (lo, hi) and the chunk box b = [lo: D][hi: D].
+template <int D>
+__device__ __forceinline__ int64_t chunk_gap2(const int32_t *lo, const int32_t *hi, const int32_t *b)
+{
+    int64_t acc = 0;
+#pragma unroll
+    for (int e = 0; e < D; e++) {
+        const int64_t gap = max((int64_t)b[e] - hi[e], (int64_t)lo[e] - b[D + e]);
+        if (gap > 0) acc += gap * gap;
+    }
+    return acc;
+}
+
+// Core pairs of the rows [ra0, ra1) of group GA (at most 64 sorted positions)
+// and the columns [rb0, rb1) of GB (another group, or later positions of the
+// same one).  A unified group (ua, ub) stands as one node, its first core cube.
+// When both are, their two roots decide: equal means nothing to do, otherwise
+// the first pair within eps joins them and ends the search (so does a pair
+// that another wave found).  Otherwise every pair within eps links its two
+// nodes unless their cached roots already agree.
+// BOXES false: all columns are walked as they lie (small pairs, for which the
+// boxes cost more than they save, in a kernel that has no registers to spare
+// for them).
+constexpr uint32_t kFewColumns = 2 * kWave;
+template <int D, bool WIDE, bool BOXES>
+__device__ __forceinline__ void link_rows(const Plan &P, uint32_t GA, uint32_t GB, bool ua, bool ub, uint32_t ra0, uint32_t ra1,
+                          uint32_t rb0, uint32_t rb1, int32_t (*s_pt)[D], uint32_t &lt)
 {
     const uint32_t l = lane_id();
-    const uint32_t qi = i0 + l, qj = j0 + l;
-    const bool core_i = qi < a1 && P.core[qi];
-    const bool core_j = qj < a1 && P.core[qj];
+    const uint32_t ga = ua ? P.gcube[GA] : kNone, gb = ub ? P.gcube[GB] : kNone;
+    const bool single = ua && ub;
+    if (single && uf_find(P.parent, ga) == uf_find(P.parent, gb)) return;
+    const uint32_t qi = ra0 + l;
+    const bool core_i = qi < ra1 && P.core[qi];
     const uint64_t mi = __ballot(core_i);
-    if (!mi || !__ballot(core_j)) return;
-    const uint32_t cube_i = core_i ? P.cell_of[qi] : kNone;
-    const uint32_t cube_j = core_j ? P.cell_of[qj] : kNone;
-    const Pt<D> pi = load_pt<D>(P.spts, core_i ? qi : a0);
-    const Pt<D> pj = load_pt<D>(P.spts, core_j ? qj : a0);
+    if (!mi) return;
+    const Pt<D> pi = load_pt<D>(P.spts, core_i ? qi : ra0);
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int e = 0; e < D; e++) s_pt[l][e] = pi.x[e];
     __builtin_amdgcn_wave_barrier();
-    uint32_t root_i = core_i ? uf_find(P.parent, cube_i) : kNone;
-    uint32_t root_j = core_j ? uf_find(P.parent, cube_j) : kNone;
-    {
-        // nothing to link when every cube of the tile already has one root
-        const uint32_t r0 = __shfl(root_i, __ffsll((unsigned long long)mi) - 1);
-        if (!__ballot((core_i && root_i != r0) || (core_j && root_j != r0))) {
-            __builtin_amdgcn_wave_barrier();
-            return;
-        }
-    }
-    uint64_t rows = mi;
-    while (rows) {
-        const uint32_t r = __ffsll((unsigned long long)rows) - 1;
-        rows &= rows - 1;
-        const uint32_t cr = __shfl(cube_i, r);
-        const uint32_t rr = __shfl(root_i, r);
-        Pt<D> pr;
+    // a few columns are walked as they lie, without the boxes
+    const bool few = !BOXES || rb1 - rb0 <= kFewColumns;
+    QBox<D> rows_box;
+    if (!few) {
 #pragma unroll
-        for (int e = 0; e < D; e++) pr.x[e] = s_pt[r][e];
-        lt += core_j;
-        const bool hit = core_j && cube_j > cr && within<D, WIDE>(pr, pj, P.eps2);
-        const bool need = hit && root_j != rr;
-        if (__ballot(need)) {
-            if (need) uf_union(P.parent, cr, cube_j);
-            root_j = core_j ? uf_find(P.parent, cube_j) : kNone;
-            root_i = core_i ? uf_find(P.parent, cube_i) : kNone;
+        for (int e = 0; e < D; e++) {
+            rows_box.lo[e] = wave_min(core_i ? pi.x[e] : INT32_MAX);
+            rows_box.hi[e] = wave_max(core_i ? pi.x[e] : INT32_MIN);
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    // node of each row point and its root (one lookup for a unified group)
+    const uint32_t node_i = single || !core_i ? kNone : (ua ? ga : P.cell_of[qi]);
+    uint32_t root_i = kNone;
+    if (!single) root_i = ua ? uf_find(P.parent, ga) : (core_i ? uf_find(P.parent, node_i) : kNone);
+    const uint32_t first = few ? 0u : rb0 / kWave, last = few ? (rb1 - rb0 - 1) / kWave : (rb1 - 1) / kWave;
+    for (uint32_t c0 = first; c0 <= last; c0 += kWave) {
+        bool ok = c0 + l <= last;
+        if (ok && !few) {
+            const int32_t *b = P.cbox + (uint64_t)(c0 + l) * (2 * D);
+            ok = b[0] <= b[D] && chunk_gap2<D>(rows_box.lo, rows_box.hi, b) <= P.eps2;
+        }
+        uint64_t chunks = __ballot(ok);
+        while (chunks) {
+            const uint32_t c = c0 + (uint32_t)__ffsll((unsigned long long)chunks) - 1;
+            chunks &= chunks - 1;
+            const uint32_t qj = (few ? rb0 : 0u) + c * kWave + l;
+            const bool core_j = qj >= rb0 && qj < rb1 && P.core[qj];
+            const uint64_t mj = __ballot(core_j);
+            uint64_t rows = mi;
+            if (!few) {
+                if (single && uf_find(P.parent, ga) == uf_find(P.parent, gb)) return;
+                rows = __ballot(core_i && chunk_gap2<D>(pi.x, pi.x, P.cbox + (uint64_t)c * (2 * D)) <= P.eps2);
+            }
+            if (!mj || !rows) continue;
+            const uint32_t node_j = single || !core_j ? kNone : (ub ? gb : P.cell_of[qj]);
+            uint32_t root_j = kNone;
+            if (!single) {
+                root_j = ub ? uf_find(P.parent, gb) : (core_j ? uf_find(P.parent, node_j) : kNone);
+                // columns of one root: rows of that root have nothing to link
+                const uint32_t r0 = __shfl(root_j, (uint32_t)__ffsll((unsigned long long)mj) - 1);
+                if (!__ballot(core_j && root_j != r0)) rows &= __ballot(root_i != r0);
+                if (!rows) continue;
+            }
+            const Pt<D> pj = load_pt<D>(P.spts, core_j ? qj : rb0);
+            while (rows) {
+                const uint32_t r = __ffsll((unsigned long long)rows) - 1;
+                rows &= rows - 1;
+                Pt<D> pr;
+#pragma unroll
+                for (int e = 0; e < D; e++) pr.x[e] = s_pt[r][e];
+                lt += core_j;
+                const bool hit = core_j && within<D, WIDE>(pr, pj, P.eps2);
+                if (single) {
+                    if (__ballot(hit)) {
+                        if (l == 0) uf_union(P.parent, ga, gb);
+                        return;
+                    }
+                    continue;
+                }
+                const uint32_t nr = __shfl(node_i, r), rr = __shfl(root_i, r);
+                const bool need = hit && root_j != rr;
+                const uint64_t nm = __ballot(need);
+                if (nm) {
+                    if (ub) {
+                        // one node on the GB side: a single union suffices
+                        if (l == __ffsll((unsigned long long)nm) - 1) uf_union(P.parent, nr, gb);
+                    } else if (need) {
+                        uf_union(P.parent, nr, node_j);
+                    }
+                    root_j = ub ? uf_find(P.parent, gb) : (core_j ? uf_find(P.parent, node_j) : kNone);
+                    root_i = ua ? uf_find(P.parent, ga) : (core_i ? uf_find(P.parent, node_i) : kNone);
+                }
+            }
+        }
+    }
 }
 
-// Groups of one chunk: one wave per group, its single tile.  Larger groups:
-// their tiles (prefix in tile_start) dealt one per wave.
+// Links inside groups, a wave per chunk: the pairs within the chunk (all its
+// groups at once), then its last group's points against that group's later
+// chunks (only the last group can have any).
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_merge_tiles(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ int32_t s_pt[kWavesPerBlock][kWave][D];
-    const uint32_t w = wave_in_block();
-    const uint32_t ng = ld_agent32(&P.ctr->n_groups);
-    const uint32_t total = ld_agent32(&P.ctr->n_tiles);
+    const uint32_t w = wave_in_block(), l = lane_id(), chunks = (P.n + kWave - 1) / kWave;
     uint32_t lt = 0;
     const WaveRange hca_wr_ = wave_range(P.order);
-    HCA_FOR_UNITS(g, ng) {
-        if (group_chunks(P, g) != 1) continue;
-        const uint32_t a0 = P.group_start[g], a1 = P.group_start[g + 1];
-        group_tile<D, WIDE>(P, a0, a1, a0, a0, s_pt[w], lt);
-    }
-    HCA_FOR_UNITS(u, total) {
-        // group: last g with tile_start[g] <= u
-        uint32_t lo = 0, hi = ng;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (P.tile_start[mid] <= u) lo = mid; else hi = mid;
+    HCA_FOR_UNITS(c, chunks) {
+        const uint32_t q = c * kWave + l;
+        const bool in = q < P.n;
+        const uint32_t cube = P.cell_of[min(q, P.n - 1)], grp = P.group_of[cube];
+        const bool big = group_chunks(P, grp) > kTileMaxChunks;
+        const uint64_t starts = __ballot(in && big && P.group_start[grp] == q);
+        if (starts && l == 0) atomicAdd(&P.ctr->n_big_groups, (uint32_t)__popcll(starts));
+        const bool core = in && !big && P.core[q];
+        const uint64_t live = __ballot(core);
+        if (!live) continue;
+        uint32_t root = core ? uf_find(P.parent, cube) : kNone;
+        // a group's points are neighbours in the chunk: it has something to
+        // link when some two core points in a row have different roots
+        const uint64_t earlier = live & __lanemask_lt();
+        const uint32_t prev = earlier ? 63u - (uint32_t)__clzll((long long)earlier) : 0u;
+        const uint32_t pg = __shfl(grp, prev), pr0 = __shfl(root, prev);
+        uint64_t open = __ballot(core && earlier && pg == grp && pr0 != root), rows = 0;
+        while (open) {
+            const uint64_t of = __ballot(core && grp == lane_value(grp, (uint32_t)__ffsll((unsigned long long)open) - 1));
+            rows |= of;
+            open &= ~of;
         }
-        const uint32_t g = lo;
-        const uint32_t a0 = P.group_start[g], a1 = P.group_start[g + 1];
-        const uint32_t nc = (a1 - a0 + kWave - 1) / kWave;
-        // row ci, column cj >= ci of the upper triangle
-        const uint32_t t = u - P.tile_start[g];
-        uint32_t ci = (uint32_t)((2.0f * nc + 1.0f - sqrtf((2.0f * nc + 1.0f) * (2.0f * nc + 1.0f) - 8.0f * t)) * 0.5f);
-        while (ci > 0 && ci * nc - ci * (ci - 1) / 2 > t) ci--;
-        while ((ci + 1) * nc - (ci + 1) * ci / 2 <= t) ci++;
-        const uint32_t cj = ci + (t - (ci * nc - ci * (ci - 1) / 2));
-        group_tile<D, WIDE>(P, a0, a1, a0 + ci * kWave, a0 + cj * kWave, s_pt[w], lt);
+        const Pt<D> p = load_pt<D>(P.spts, core ? q : c * kWave);
+        if (rows) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int e = 0; e < D; e++) s_pt[w][l][e] = p.x[e];
+            __builtin_amdgcn_wave_barrier();
+        }
+        while (rows) {
+            const uint32_t r = __ffsll((unsigned long long)rows) - 1;
+            rows &= rows - 1;
+            const uint32_t rg = lane_value(grp, r), rc = lane_value(cube, r);
+            const bool other = core && grp == rg && cube > rc && root != lane_value(root, r);
+            if (!__ballot(other)) continue;
+            Pt<D> pr;
+#pragma unroll
+            for (int e = 0; e < D; e++) pr.x[e] = s_pt[w][r][e];
+            lt += other;
+            const bool need = other && within<D, WIDE>(pr, p, P.eps2);
+            if (__ballot(need)) {
+                if (need) uf_union(P.parent, rc, cube);
+                root = core ? uf_find(P.parent, cube) : kNone;
+            }
+        }
+        const uint32_t c1 = (c + 1) * kWave;
+        if (c1 >= P.n) continue;
+        const uint32_t g = lane_value(grp, kWave - 1), g0 = uniform(P.group_start[g]), g1 = uniform(P.group_start[g + 1]);
+        if (g1 > c1 && !lane_value((uint32_t)big, kWave - 1))
+            link_rows<D, WIDE, true>(P, g, g, false, false, max(g0, c * kWave), c1, c1, g1, s_pt[w], lt);
     }
     flush_tests(P, kTestsIntra, lt);
 }
@@ -2229,7 +2302,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_big(Plan P)
 {
     if (box_missed(P)) return;
     const uint32_t l = lane_id();
-    if (ld_agent32(&P.ctr->n_big_groups) == 0) return;      // counted by k_tile_scan
+    if (ld_agent32(&P.ctr->n_big_groups) == 0) return;      // counted by k_merge_tiles
     const uint32_t nc = ld_agent32(&P.ctr->n_cells);
     const uint64_t fmask = (1ull << P.bm) - 1ull;
     uint32_t lt = 0;
@@ -2305,109 +2378,27 @@ __global__ __launch_bounds__(kBlock) void k_merge_unify(Plan P)
     }
 }
 
-// Core pairs of groups GA x GB, rows [ra0, ra1) of GA against columns
-// [rb0, rb1) of GB (sorted positions), in 64 x 64 tiles: 64 row points staged
-// in LDS are visited one at a time against 64 column points in the lanes.  A
-// unified group stands as one node (its first core cube).  When both groups
-// are unified, their two roots decide: equal means nothing to do, otherwise
-// the first pair within eps joins them and ends the search.  Otherwise every
-// pair within eps links its two nodes unless their cached roots already
-// agree; a tile whose nodes all share one root is skipped.
-template <int D, bool WIDE>
-__device__ void link_pair(const Plan &P, uint32_t GA, uint32_t GB, bool ua, bool ub, uint32_t ra0,
-                          uint32_t ra1, uint32_t rb0, uint32_t rb1, int32_t (*s_pt)[D], uint32_t &lt)
-{
-    const uint32_t l = lane_id();
-    const uint32_t ga = P.gcube[GA], gb = P.gcube[GB];
-    const bool single = ua && ub;
-    if (single && uf_find(P.parent, ga) == uf_find(P.parent, gb)) return;
-    for (uint32_t ia = ra0; ia < ra1; ia += kWave) {
-        const uint32_t qi = ia + l;
-        const bool core_i = qi < ra1 && P.core[qi];
-        const uint64_t mi = __ballot(core_i);
-        if (!mi) continue;
-        const Pt<D> pi = load_pt<D>(P.spts, core_i ? qi : ra0);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int e = 0; e < D; e++) s_pt[l][e] = pi.x[e];
-        __builtin_amdgcn_wave_barrier();
-        // node of each row point and its root (one lookup for a unified group)
-        const uint32_t node_i = single || !core_i ? kNone : (ua ? ga : P.cell_of[qi]);
-        uint32_t root_i = kNone;
-        if (!single) root_i = ua ? uf_find(P.parent, ga) : (core_i ? uf_find(P.parent, node_i) : kNone);
-        for (uint32_t jb = rb0; jb < rb1; jb += kWave) {
-            const uint32_t qj = jb + l;
-            const bool core_j = qj < rb1 && P.core[qj];
-            if (!__ballot(core_j)) continue;
-            const uint32_t node_j = single || !core_j ? kNone : (ub ? gb : P.cell_of[qj]);
-            uint32_t root_j = kNone;
-            if (!single) {
-                root_j = ub ? uf_find(P.parent, gb) : (core_j ? uf_find(P.parent, node_j) : kNone);
-                const uint32_t r0 = __shfl(root_i, __ffsll((unsigned long long)mi) - 1);
-                if (!__ballot((core_i && root_i != r0) || (core_j && root_j != r0))) continue;
-            }
-            const Pt<D> pj = load_pt<D>(P.spts, core_j ? qj : rb0);
-            uint64_t rows = mi;
-            while (rows) {
-                const uint32_t r = __ffsll((unsigned long long)rows) - 1;
-                rows &= rows - 1;
-                Pt<D> pr;
-#pragma unroll
-                for (int e = 0; e < D; e++) pr.x[e] = s_pt[r][e];
-                lt += core_j;
-                const bool hit = core_j && within<D, WIDE>(pr, pj, P.eps2);
-                if (single) {
-                    if (__ballot(hit)) {
-                        if (l == 0) uf_union(P.parent, ga, gb);
-                        return;
-                    }
-                    continue;
-                }
-                const uint32_t nr = __shfl(node_i, r), rr = __shfl(root_i, r);
-                const bool need = hit && root_j != rr;
-                const uint64_t nm = __ballot(need);
-                if (nm) {
-                    if (ub) {
-                        // one node on the GB side: a single union suffices
-                        if (l == __ffsll((unsigned long long)nm) - 1) uf_union(P.parent, nr, gb);
-                    } else if (need) {
-                        uf_union(P.parent, nr, node_j);
-                    }
-                    root_j = ub ? uf_find(P.parent, gb) : (core_j ? uf_find(P.parent, node_j) : kNone);
-                    root_i = ua ? uf_find(P.parent, ga) : (core_i ? uf_find(P.parent, node_i) : kNone);
-                }
-            }
-        }
-    }
-}
+// Group-pair work in the worklist: 4 words each (GA, GB, chunk of GA's points,
+// unused); region r owns entries [r * cap, (r + 1) * cap).
+__device__ __forceinline__ uint32_t pair_cap(const Plan &P) { return P.work_cap / 2 / kWorkRegions; }
 
-// Group-pair work in the worklist: 4 words each (GA, GB, row tile, column
-// tile), row tile kNone for a whole pair of unified groups; region r owns
-// entries [r * cap, (r + 1) * cap).
-__device__ __forceinline__ uint32_t pair_tile_cap(const Plan &P) { return P.work_cap / 2 / kWorkRegions; }
-
-template <int D, bool WIDE>
-__device__ __forceinline__ void link_tile(const Plan &P, uint32_t GA, uint32_t GB, uint32_t ti, uint32_t tj,
-                                          int32_t (*s_pt)[D], uint32_t &lt)
+// The points of group GA in chunk c against all of group GB.
+template <int D, bool WIDE, bool BOXES>
+__device__ __forceinline__ void link_chunk(const Plan &P, uint32_t GA, uint32_t GB, uint32_t c, int32_t (*s_pt)[D],
+                                           uint32_t &lt)
 {
     const uint32_t a0 = P.group_start[GA], a1 = P.group_start[GA + 1];
-    const uint32_t b0 = P.group_start[GB], b1 = P.group_start[GB + 1];
-    if (ti == kNone) {                                   // a whole pair of unified groups
-        link_pair<D, WIDE>(P, GA, GB, true, true, a0, a1, b0, b1, s_pt, lt);
-        return;
-    }
-    const uint32_t ra0 = a0 + ti * kWave, rb0 = b0 + tj * kWave;
-    link_pair<D, WIDE>(P, GA, GB, P.unified[GA], P.unified[GB], ra0, min(a1, ra0 + kWave), rb0,
-                       min(b1, rb0 + kWave), s_pt, lt);
+    link_rows<D, WIDE, BOXES>(P, GA, GB, P.unified[GA], P.unified[GB], max(a0, c * kWave), min(a1, (c + 1) * kWave),
+                       P.group_start[GB], P.group_start[GB + 1], s_pt, lt);
 }
 
 // Inter: each group GA with core points walks its neighbour groups GB > GA
 // that have core points and whose box comes within eps of GA's core points.
 // When both groups are unified, their roots are compared on the spot; a
 // small pair with different roots is searched right away.  The other pairs
-// go to the worklist cut into 64 x 64 tiles, so that a pair of large groups
-// is spread over many waves (tiles past a full region are linked on the
-// spot).
+// go to the worklist, one entry per chunk of the smaller group, so that a pair
+// of large groups is spread over many waves (entries past a full region are
+// linked on the spot).
 constexpr uint32_t kInlineTiles = 4;
 
 // Held to 128 registers (four waves per SIMD): a few spill, and the walk
@@ -2419,7 +2410,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
     __shared__ int32_t s_pt[kWavesPerBlock][kWave][D];
     const uint32_t w = wave_in_block(), l = lane_id();
     const uint32_t region = (blockIdx.x * kWavesPerBlock + w) % kWorkRegions;
-    const uint32_t cap = pair_tile_cap(P);
+    const uint32_t cap = pair_cap(P);
     uint32_t lt = 0;
     const uint32_t ng = ld_agent32(&P.ctr->n_groups);
     const DynRange dr_ = dyn_range(P.ctr->dyn[kDynMerge], P.order);
@@ -2431,7 +2422,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
         const uint64_t gkey = P.group_key[GA];
         // bounding box of GA's core points
         const uint32_t a0 = P.group_start[GA], a1 = P.group_start[GA + 1];
-        const uint32_t nta = (a1 - a0 + kWave - 1) / kWave;
+        const uint32_t ca = a0 / kWave, nta = (a1 - 1) / kWave - ca + 1;        // its chunks
         QBox<D> qb;
 #pragma unroll
         for (int e = 0; e < D; e++) { qb.lo[e] = INT32_MAX; qb.hi[e] = INT32_MIN; }
@@ -2449,7 +2440,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
         const uint32_t slots = src.lists ? 1 + src.fcount : src.slots;
         for (uint32_t oc = 1; oc < slots; oc += kWave) {
             const uint32_t j = oc + l;
-            uint32_t GB = kNone, tiles = 0, ntb = 1;
+            uint32_t GB = kNone, tiles = 0, cb = 0, ntb = 1;
             bool both = false;
             if (j < slots) {
                 uint64_t nk = ~0ull;
@@ -2474,8 +2465,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
                     GB = kNone;
                 }
                 if (GB != kNone) {
-                    ntb = (P.group_start[GB + 1] - P.group_start[GB] + kWave - 1) / kWave;
-                    tiles = nta * ntb;
+                    const uint32_t b0 = P.group_start[GB], b1 = P.group_start[GB + 1];
+                    cb = b0 / kWave;
+                    ntb = (b1 - 1) / kWave - cb + 1;
+                    tiles = ((a1 - a0 + kWave - 1) / kWave) * ((b1 - b0 + kWave - 1) / kWave);
                     if (ua && P.unified[GB]) {
                         both = true;
                         if (uf_find(P.parent, ga) == uf_find(P.parent, P.gcube[GB])) GB = kNone;
@@ -2487,14 +2480,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
             while (now) {
                 const uint32_t src_lane = __ffsll((unsigned long long)now) - 1;
                 const uint32_t gb = __shfl(GB, src_lane);
-                link_pair<D, WIDE>(P, GA, gb, true, true, a0, a1, P.group_start[gb], P.group_start[gb + 1],
-                                   s_pt[w], lt);
+                for (uint32_t ra = a0; ra < a1; ra += kWave)
+                    link_rows<D, WIDE, false>(P, GA, gb, true, true, ra, min(a1, ra + kWave), P.group_start[gb],
+                                       P.group_start[gb + 1], s_pt[w], lt);
                 now &= now - 1;
             }
             if (both && tiles <= kInlineTiles) GB = kNone;
-            // the rest: one worklist entry per 64 x 64 tile, or one for a whole
-            // pair of unified groups (its search ends at the first hit)
-            const uint32_t want = GB == kNone ? 0u : both ? 1u : tiles;
+            // the rest: a worklist entry per chunk of the group with fewer
+            const uint32_t want = GB == kNone ? 0u : min(nta, ntb);
             const uint32_t inc = wave_inclusive_scan(want);
             const uint32_t total = lane_value(inc, kWave - 1);
             if (!total) continue;
@@ -2506,23 +2499,21 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
                 const uint32_t src_lane = __ffsll((unsigned long long)m) - 1;
                 m &= m - 1;
                 const uint32_t gb = __shfl(GB, src_lane), nt = __shfl(want, src_lane);
-                const uint32_t nb_t = __shfl(ntb, src_lane);
                 const uint32_t first = base + __shfl(inc, src_lane) - nt;
-                const bool whole = __shfl((uint32_t)both, src_lane) != 0;
+                const bool by_b = __shfl(ntb, src_lane) < nta;
+                const uint32_t g_rows = by_b ? gb : GA, g_cols = by_b ? GA : gb, c0 = by_b ? __shfl(cb, src_lane) : ca;
                 for (uint32_t t0 = 0; t0 < nt; t0 += kWave) {
                     const uint32_t t = t0 + l;
-                    const uint32_t ti = t / nb_t, tj = t - ti * nb_t;
                     const bool mine = t < nt;
                     const uint32_t slot = first + t;
                     if (mine && slot < cap)
-                        *(uint4 *)(P.work + 4ull * ((uint64_t)region * cap + slot)) =
-                            make_uint4(GA, gb, whole ? kNone : ti, tj);
-                    // region full: link those tiles here
+                        *(uint4 *)(P.work + 4ull * ((uint64_t)region * cap + slot)) = make_uint4(g_rows, g_cols, c0 + t, 0u);
+                    // region full: link those here
                     uint64_t sp = __ballot(mine && slot >= cap);
                     while (sp) {
                         const uint32_t sl = __ffsll((unsigned long long)sp) - 1;
                         sp &= sp - 1;
-                        link_tile<D, WIDE>(P, GA, gb, whole ? kNone : __shfl(ti, sl), __shfl(tj, sl), s_pt[w], lt);
+                        link_chunk<D, WIDE, false>(P, g_rows, g_cols, c0 + t0 + sl, s_pt[w], lt);
                     }
                 }
             }
@@ -2531,7 +2522,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
     flush_tests(P, kTestsMerge, lt);
 }
 
-// The queued tiles, one per wave at a time over all waves.
+// The queued entries, one per wave at a time over all waves.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_merge_pairs(Plan P)
 {
@@ -2539,7 +2530,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_pairs(Plan P)
     __shared__ uint32_t s_pre[kWavesPerBlock][kWorkRegions];
     __shared__ int32_t s_pt[kWavesPerBlock][kWave][D];
     const uint32_t w = wave_in_block(), l = lane_id();
-    const uint32_t cap = pair_tile_cap(P);
+    const uint32_t cap = pair_cap(P);
     const uint32_t cnt = min(ld_agent32(P.ctr->work_count + l * kCounterStride), cap);
     const uint32_t inc = wave_inclusive_scan(cnt);
     s_pre[w][l] = inc - cnt;
@@ -2550,7 +2541,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_pairs(Plan P)
     HCA_FOR_UNITS(it, items) {
         const uint32_t r = candidate_lane(it, s_pre[w]);
         const uint4 e = *(const uint4 *)(P.work + 4ull * ((uint64_t)r * cap + (it - s_pre[w][r])));
-        link_tile<D, WIDE>(P, e.x, e.y, e.z, e.w, s_pt[w], lt);
+        link_chunk<D, WIDE, true>(P, e.x, e.y, e.z, s_pt[w], lt);
     }
     flush_tests(P, kTestsMerge, lt);
 }
@@ -3130,8 +3121,7 @@ void launch_merge_intra(const Plan &P, int blocks, hipStream_t s)
 {
     if (P.m == 1) return;
     if (P.rec) launch_link_recorded(P, s);
-    const uint32_t tiles = (P.n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_tile_scan, dim3(tiles), dim3(kBlock), 0, s, P, P.tile_status, &P.ctr->tile_ticket);
+    HCA_DISPATCH_DW(k_core_box, P, blocks, s);
     HCA_DISPATCH_DW(k_merge_tiles, P, blocks, s);
     HCA_DISPATCH_DW(k_merge_big, P, blocks, s);
     HCA_DISPATCH_DW(k_merge_unify, P, blocks, s);

@@ -77,8 +77,6 @@ struct Counters {
     uint32_t scan_tickets[4];   // tile tickets of the device-wide scans
     uint32_t pad_tally[2];      // (core and noise counts: see tally)
     uint32_t n_clusters;
-    uint32_t n_tiles;           // intra-group point tiles
-    uint32_t tile_ticket;
     uint32_t nbr_overflow;      // groups whose neighbour list did not fit
     uint32_t hmask;             // hash slots in use - 1 (a power of two - 1)
     uint32_t nbr_ticket;        // tiles of the backward-list scan
@@ -232,8 +230,9 @@ struct Plan {
     uint32_t *parent;           // [n] union-find over cubes
     uint32_t *gcube;            // [n] group -> first cube with a core point, kNone if none
     uint8_t *unified;           // [n] group -> its core cubes share one union-find root
-    uint32_t *groot;            // [n] group -> that root when unified (snapshot after intra linking), else kNone; in tile_start's array
-    uint32_t *tile_start;       // [n] group -> first intra-group tile
+    uint32_t *groot;            // [n] group -> that root when unified (snapshot after intra linking), else kNone (m > 1)
+    int32_t *cbox;              // [ceil(n / 64)][2][d] box of the core points of every 64 sorted positions (m > 1;
+                                // in owner, free until borders)
     // group mode: the non-empty neighbour groups of each group (self
     // excluded) that can hold a point within eps of one of its points.  Each
     // wave fills its own slab of nbr_cap / waves entries; a group whose list
@@ -267,7 +266,6 @@ struct Plan {
     uint32_t seg_shift;
     SegParam *seg;              // [nseg]
     const uint32_t *seg_of;     // [n] staged row -> data set
-    uint64_t *tile_status;      // look-back words of the tile scan
     uint32_t *work;             // [2 * work_cap] cube pairs for exact tests
     uint32_t work_cap;          // multiple of kWorkRegions
     uint32_t want_stats;        // count core and noise points
