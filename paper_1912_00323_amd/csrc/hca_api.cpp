@@ -592,20 +592,38 @@ void plan_sizes(Plan &P, uint32_t gbits, bool count_work, bool want_stats, Sizes
 }
 
 // Neighbour lists from prefix ranges: the groups sharing the group-key
-// prefix of the first d/2 axes are consecutive, so the lists can scan them
-// (when that prefix takes at most 26 bits and its table at most 32 entries
-// per point, or 2^20: a batch's data-set bits sit above the prefix; the table
+// prefix of the first axes are consecutive, so the lists can scan them (when
+// that prefix takes at most 26 bits and its table at most 32 entries per
+// point, or 2^20: a batch's data-set bits sit above the prefix; the table
 // is written only where groups exist, so its size costs memory, not
 // traffic; HCA_PREFIX=0 turns it off).
-void plan_prefix(Plan &P, uint32_t gbits, Sizes *Z, const Tune *t = nullptr)
+// The prefix spans half the axes, or more while at least four groups' offsets
+// fit a wave (27 offsets of three axes in the groups' three cells per axis,
+// 25 of two in the cubes' five): the more axes, the shorter the ranges (5-D,
+// 1.2M points, lists with a prefix of 2, 3 and 4 axes: 390, 244 and 371 us;
+// 3-D, 1M points, half the axes and 2: 487 and 169).  Data that reach past
+// 46340 units along two axes or more keep half the axes and whole ranges
+// (far: list_far's 32-bit sum can wrap there and keep far groups), and so do
+// calls without the memory for the larger table (half).
+void plan_prefix(Plan &P, uint32_t gbits, bool far, Sizes *Z, const Tune *t = nullptr, bool half = false)
 {
     Z->pbits = 0;
     const bool want = t && t->prefix >= 0 ? t->prefix != 0 : env_prefix();
     if (!P.nbr_cap || P.d < 2 || P.hd || !want) return;
-    P.pshift = P.goff[P.d / 2 - 1];
-    const uint32_t pbits = gbits - P.pshift;
-    if (pbits <= 26 && (1ull << pbits) <= std::max<uint64_t>(32ull * P.n, 1ull << 20))
-        Z->pbits = std::max<uint32_t>(1, pbits);
+    auto fits = [&](int axes, uint64_t most) {
+        uint64_t offsets = 1;
+        for (int k = 0; k < axes; k++) offsets *= P.list_w;
+        const uint32_t pbits = gbits - P.goff[axes - 1];
+        return offsets <= most && pbits <= 26 && (1ull << pbits) <= std::max<uint64_t>(32ull * P.n, 1ull << 20);
+    };
+    int axes = P.d / 2;
+    if (!fits(axes, 2 * kWave - 1)) return;
+    P.pnarrow = !(far && !P.wide);
+    if (P.pnarrow && !half)
+        while (axes + 1 < P.d && fits(axes + 1, kWave / 2)) axes++;
+    P.paxes = (uint32_t)axes;
+    P.pshift = P.goff[axes - 1];
+    Z->pbits = std::max<uint32_t>(1, gbits - P.pshift);
 }
 
 // The device workspace of one launch sequence (the first bytes hold the
@@ -1282,9 +1300,11 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
     P.sd = (uint32_t)d;
     uint32_t gbits = 0;
     int64_t span_max = 0;
+    int far_axes = 0;
     for (int k = d - 1; k >= 0; k--) {
         P.origin[k] = (int32_t)mn[k];
         const uint64_t span = (uint64_t)(mx[k] - mn[k]);
+        far_axes += span > 46340;
         span_max = std::max<int64_t>(span_max, (int64_t)span);
         const uint64_t cmax = span / (uint64_t)G.side;
         P.gmax[k] = (uint32_t)(cmax / G.m);
@@ -1318,11 +1338,16 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
     plan_core_lanes(P, G.radius);
     Sizes Z;
     plan_sizes(P, gbits, stats != nullptr && ctx->prof != -1, stats != nullptr, &Z);
-    plan_prefix(P, gbits, &Z);
+    plan_prefix(P, gbits, far_axes >= 2, &Z);
     P.pts = points;
     P.labels = labels;
     P.core_out = core_out;
     st = workspace(ctx, ws_bytes(P, Z));
+    if (st && P.paxes > (uint32_t)d / 2) {
+        plan_prefix(P, gbits, far_axes >= 2, &Z, nullptr, true);
+        ctx->err.clear();
+        st = workspace(ctx, ws_bytes(P, Z));
+    }
     if (st) return st;
     if (ahead) {
         // this call's box, into the workspace as sized for the whole call,
@@ -1401,6 +1426,7 @@ struct BatchGroup {
     // layout of the packed key shared by the data sets (from their boxes)
     uint32_t gw[kMaxDim] = {};
     bool wide = false;
+    bool far = false;                   // some data set reaches past 46340 units along two axes
     uint32_t cubes_axis = 1;            // largest cube count along an axis of any data set
     Tune tune;                          // knobs of its launch sequence
     std::string tune_key;               // what the autotuner's cache knows it by
@@ -1592,14 +1618,18 @@ hca_status batch_layout(hca_ctx *ctx, BatchGroup &g, const char *hb, const Batch
     const int d = g.d;
     const uint32_t *box = (const uint32_t *)(hb + g.h_box);
     uint64_t cmax[kMaxDim] = {};
+    g.far = false;
     for (size_t i = 0; i < g.par.size(); i++) {
         SegParam &sp = g.par[i];
         if (sets[g.segs[i]].n == 0) continue;
+        int far_axes = 0;
         for (int k = 0; k < d; k++) {
             const int32_t lo = (int32_t)(~box[i * 2 * d + k] ^ 0x80000000u);
             const int32_t hi = (int32_t)(box[i * 2 * d + d + k] ^ 0x80000000u);
             const int64_t span = (int64_t)hi - lo;
             if (span >= (1ll << 30)) return fail(ctx, HCA_E_RANGE, "coordinate span >= 2^30 along an axis");
+            far_axes += span > 46340;
+            g.far |= far_axes >= 2;
             sp.origin[k] = lo;
             cmax[k] = std::max<uint64_t>(cmax[k], (uint64_t)span / (uint64_t)sp.side);
         }
@@ -1660,7 +1690,7 @@ void batch_plan(BatchGroup &g, char *db, const Tune *t)
     P.list_w = cube_list_width(d, rmax, P.n_off, t);
     plan_core_lanes(P, rmax, t);
     plan_sizes(P, P.key_bits, false, false, &g.Z, t);
-    plan_prefix(P, P.key_bits, &g.Z, t);
+    plan_prefix(P, P.key_bits, g.far, &g.Z, t);
 }
 
 hca_status run_sets(hca_ctx *ctx, const BatchSet *sets, int32_t nseg)

@@ -492,137 +492,190 @@ constexpr int kListBatch = 4;        // lookups in flight per lane
 
 constexpr int kListHalf = 128;       // offset combinations per half of the axes, at most
 
-// Append the forward entries (G > g, point boxes within eps) in the wave's
-// slab; a group that does not fit is marked and counted by the caller.
-template <int D>
-__device__ __forceinline__ void list_append(const Plan &P, uint32_t G, const QBox<D> &qb, int64_t eps2,
-                                            uint32_t &at, uint32_t end, bool &fits)
+// With prefix ranges a wave takes several groups at once, a lane per group and
+// forward offset of the prefix's axes (for the zero offset the groups after
+// the own one in its prefix; offsets nearest first, so that lists start with
+// near groups).  A lane whose offset can hold a point within eps reads the
+// range of groups with that prefix; a range of more than kRangeCut groups is
+// narrowed to the groups within R of the own one along the next axis.  The
+// ranges of all lanes are then scanned together, and a group is kept when its
+// point box comes within eps.  A group with a longer range than twice the
+// offsets of the other axes (at least 64) is left to the halves of the axes.
+// One group per wave took a chain of some five dependent loads and an LDS
+// pass per group with few of its lanes in use.
+constexpr uint32_t kRangeCut = 16;
+constexpr int kListPack = 8;         // groups per wave, at most
+
+// Offset components of forward combination f of the first pa axes (axis 0 the
+// most significant digit), a byte per axis; f = 0 is the zero offset.
+__device__ __forceinline__ uint32_t forward_offset(uint32_t f, uint32_t pa, uint32_t W, uint32_t all, uint32_t *norm)
 {
-    if (G != kNone) {
-        const QBox<D> ob = load_gbox<D>(P, G);
-        bool far;
-        if (P.wide) {
-            int64_t acc = 0;
-#pragma unroll
-            for (int e = 0; e < D; e++) {
-                const int64_t gap = max((int64_t)ob.lo[e] - qb.hi[e], (int64_t)qb.lo[e] - ob.hi[e]);
-                acc += gap > 0 ? gap * gap : 0;
-            }
-            far = acc > eps2;
-        } else {
-            // The host's narrow-distance bound covers pairs within the
-            // stencil's reach, but a prefix-range scan also meets groups far
-            // beyond it: each gap is clamped to 46341 (whose square already
-            // exceeds any int32 eps^2) and the sum saturates at 2^31, so the
-            // test stays exact without overflowing.
-            uint32_t acc = 0;
-#pragma unroll
-            for (int e = 0; e < D; e++) {
-                const int32_t gap = max(max(ob.lo[e] - qb.hi[e], qb.lo[e] - ob.hi[e]), 0);
-                const uint32_t gc = min((uint32_t)gap, 46341u);
-                acc = min(acc + __umul24(gc, gc), 0x80000000u);
-            }
-            far = acc > (uint32_t)min(eps2, (int64_t)INT32_MAX);
-        }
-        if (far) G = kNone;
+    uint32_t v = all / 2 + f, o = 0, nn = 0;
+    for (uint32_t e = pa; e-- > 0;) {
+        const int c = (int)(v % W) - (int)(W >> 1);
+        v /= W;
+        o |= (uint32_t)(c & 255) << (8 * e);
+        nn += (uint32_t)(c * c);
     }
-    const uint64_t m = __ballot(G != kNone);
-    const uint32_t k = (uint32_t)__popcll(m);
-    if (at + k > end) fits = false;
-    if (fits && G != kNone) {
-        P.nbr[at + __popcll(m & __lanemask_lt())] = G;
-        atomicAdd(P.nbr_bcount + G, 1u);
-    }
-    if (fits) at += k;
+    *norm = nn;
+    return o;
 }
 
-// With prefix ranges: for every first-half offset that can hold a point
-// within eps and points forwards (or is zero), the groups of its prefix are
-// scanned instead of looking up each second-half offset; a group is kept
-// when its point box comes within eps (which also bounds each of its
-// second-half offsets to R) and, for a zero first half, when its second half
-// points forwards.  Returns false, with nothing written, when a range is
-// longer than twice the second-half offsets, at least 64 (then the offsets
-// are looked up).
-
+// Can the group box at b (lo, hi) hold a point farther than eps from the box
+// q?  32-bit when the host has shown that every tested pair's squared
+// distance fits: that bound covers pairs within the stencil's reach, but a
+// prefix range also meets groups far beyond it, so each gap is clamped to
+// 46341 (whose square already exceeds any int32 eps^2) and the sum saturates
+// at 2^31.
 template <int D>
-__device__ __forceinline__ bool list_by_prefix(const Plan &P, uint32_t g, uint64_t gkey, const QBox<D> &qb,
-                                               const Geo<D> &geo, uint32_t ng, int NA, uint32_t *s_pre,
-                                               uint32_t *s_rs, int8_t *s_ga, uint32_t &at, uint32_t end,
-                                               uint32_t &overflow, int NB)
+__device__ __forceinline__ bool list_far(const Plan &P, const QBox<D> &ob, const QBox<D> &qb, int64_t eps2)
 {
-    constexpr int DA = D / 2;
-    const uint32_t l = lane_id();
-    const uint64_t gpre = gkey >> P.pshift;
-    const uint32_t scan_max = max(64u, 2u * (uint32_t)NB);
-    uint32_t tot = 0;
-    bool big = false;
-    for (int i0 = 0; i0 < NA; i0 += kWave) {
-        const int i = i0 + (int)l;
-        uint32_t size = 0, rs = 0;
-        int8_t sg = 0;
-        if (i < NA) {
-            sg = half_sign<DA>(P, (uint32_t)i);
-            if (sg >= 0 && half_gap2<D, DA>(P, gkey, 0, (uint32_t)i, qb, geo) != INT64_MAX) {
-                const uint64_t pr = gpre + (uint64_t)(half_key_delta<DA>(P, 0, (uint32_t)i) >> P.pshift);
+    if (P.wide) {
+        int64_t acc = 0;
+#pragma unroll
+        for (int e = 0; e < D; e++) {
+            const int64_t gap = max((int64_t)ob.lo[e] - qb.hi[e], (int64_t)qb.lo[e] - ob.hi[e]);
+            acc += gap > 0 ? gap * gap : 0;
+        }
+        return acc > eps2;
+    }
+    uint32_t acc = 0;
+#pragma unroll
+    for (int e = 0; e < D; e++) {
+        const int32_t gap = max(max(ob.lo[e] - qb.hi[e], qb.lo[e] - ob.hi[e]), 0);
+        const uint32_t gc = min((uint32_t)gap, 46341u);
+        acc = min(acc + __umul24(gc, gc), 0x80000000u);
+    }
+    return acc > (uint32_t)min(eps2, (int64_t)INT32_MAX);
+}
+
+// The forward lists of groups [g0, g0 + pack): lane l takes offset l % nf of
+// group g0 + l / nf.  s_off and s_kd hold the offsets and their key
+// differences.  Returns the groups (a bit each) left to the halves of the axes.
+template <int D>
+__device__ __forceinline__ uint32_t list_by_prefix(const Plan &P, uint32_t g0, uint32_t ng, uint32_t nf, uint32_t pack,
+                                                   uint32_t scan_max, const uint32_t *s_off, const int64_t *s_kd,
+                                                   uint32_t *s_pre, uint32_t *s_rs, uint32_t *s_sub,
+                                                   int32_t (*s_box)[2 * D], int64_t *s_eps2, uint32_t &at,
+                                                   uint32_t end, uint32_t &overflow)
+{
+    const uint32_t l = lane_id(), sub = l / nf, f = l - sub * nf, g = g0 + sub;
+    const bool in = sub < pack && g < ng;
+    uint32_t rs = 0, size = 0, length = 0;
+    __builtin_amdgcn_wave_barrier();
+    if (in) {
+        const uint64_t gkey = P.group_key[g];
+        const Geo<D> geo = cube_geo<D>(P, gkey);
+        const QBox<D> qb = load_gbox<D>(P, g);
+        if (f == 0) {
+#pragma unroll
+            for (int e = 0; e < D; e++) {
+                s_box[sub][e] = qb.lo[e];
+                s_box[sub][D + e] = qb.hi[e];
+            }
+            s_eps2[sub] = geo.eps2;
+        }
+        const uint32_t off = s_off[f];
+        int64_t acc = 0;
+        bool near = true;
+#pragma unroll
+        for (int e = 0; e < (D < 4 ? D : 4); e++) {
+            if ((uint32_t)e >= P.paxes) break;
+            const int64_t g2 = axis_gap2<D>(P, gkey, e, (int)(int8_t)(off >> (8 * e)), qb.lo[e], qb.hi[e], geo);
+            near &= g2 >= 0;
+            acc += g2;
+        }
+        if (near && acc <= geo.eps2) {
+            const uint64_t pr = (gkey + (uint64_t)s_kd[f]) >> P.pshift;
+            if (f == 0) {
+                rs = g + 1;
+                size = P.pend[pr] - rs;
+                if (!P.pnarrow) length = P.pend[pr] - P.pstart[pr];
+            } else {
                 const uint32_t a = P.pstart[pr];
                 if (a < ng && (P.group_key[a] >> P.pshift) == pr) {
                     rs = a;
                     size = P.pend[pr] - a;
                 }
             }
+            if (size > kRangeCut && P.pnarrow) {
+                // first groups with a key of at least ka and kb
+                const uint32_t x = P.paxes, sh = P.goff[x];
+                const int64_t c = (int64_t)((gkey >> sh) & ((1ull << P.gw[x]) - 1ull)), R = (int64_t)(P.list_w >> 1);
+                const uint64_t ka = (pr << P.pshift) + ((uint64_t)max(c - R, (int64_t)0) << sh);
+                const uint64_t kb = (pr << P.pshift) + ((uint64_t)(min(c + R, (int64_t)P.gmax[x]) + 1) << sh);
+                uint32_t la = rs, ha = rs + size, lb = rs, hb = rs + size;
+                while (la < ha || lb < hb) {
+                    const uint32_t ma = (la + ha) >> 1, mb = (lb + hb) >> 1;
+                    const uint64_t va = P.group_key[la < ha ? ma : rs], vb = P.group_key[lb < hb ? mb : rs];
+                    if (la < ha) { if (va < ka) la = ma + 1; else ha = ma; }
+                    if (lb < hb) { if (vb < kb) lb = mb + 1; else hb = mb; }
+                }
+                rs = la;
+                size = lb - la;
+            }
+            length = max(length, size);
         }
-        big |= size > scan_max;
-        const uint32_t inc = wave_inclusive_scan(size);
-        __builtin_amdgcn_wave_barrier();
-        if (i < NA) {
-            s_pre[i] = tot + inc - size;
-            s_rs[i] = rs;
-            s_ga[i] = sg;
-        }
-        tot += lane_value(inc, kWave - 1);
     }
-    if (__ballot(big)) return false;
-    if (l == 0) s_pre[NA] = tot;
+    // groups with an over-long range: none of their ranges is scanned
+    uint32_t big = 0;
+    uint64_t bm = __ballot(length > scan_max);
+    while (bm) {
+        big |= 1u << lane_value(sub, __ffsll((unsigned long long)bm) - 1);
+        bm &= bm - 1;
+    }
+    if (in && (big >> sub & 1u)) size = 0;
+    const uint32_t inc = wave_inclusive_scan(size);
+    s_pre[l] = inc - size;
+    s_rs[l] = rs;
+    s_sub[l] = sub;
     __builtin_amdgcn_wave_barrier();
-    const uint32_t start = at;
+    const uint32_t tot = lane_value(inc, kWave - 1), start = at;
+    uint32_t mine = 0;                  // lane s: entries of group g0 + s
     bool fits = true;
     for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
         const uint32_t t = t0 + l;
-        uint32_t G = kNone;
+        uint32_t G = kNone, s = 0;
         if (t < tot) {
-            int lo = 0, hi = NA;                          // last i with s_pre[i] <= t
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (s_pre[mid] <= t) lo = mid; else hi = mid;
-            }
-            const uint32_t c = s_rs[lo] + (t - s_pre[lo]);
-            bool ok = true;
-            if (s_ga[lo] == 0) {                          // zero first half: the second must point forwards
-                const uint64_t ck = P.group_key[c];
-                int lead = 0;
+            const uint32_t ln = candidate_lane(t, s_pre);
+            G = s_rs[ln] + (t - s_pre[ln]);
+            s = s_sub[ln];
+            QBox<D> qb;
 #pragma unroll
-                for (int e = DA; e < D; e++) {
-                    const uint64_t mask = (1ull << P.gw[e]) - 1ull;
-                    const int64_t dlt = (int64_t)((ck >> P.goff[e]) & mask) - (int64_t)((gkey >> P.goff[e]) & mask);
-                    if (lead == 0) lead = dlt > 0 ? 1 : (dlt < 0 ? -1 : 0);
-                }
-                ok = lead > 0;
+            for (int e = 0; e < D; e++) {
+                qb.lo[e] = s_box[s][e];
+                qb.hi[e] = s_box[s][D + e];
             }
-            if (ok) G = c;
+            if (list_far<D>(P, load_gbox<D>(P, G), qb, s_eps2[s])) G = kNone;
         }
-        list_append<D>(P, G, qb, geo.eps2, at, end, fits);
+        // candidates lie group after group, so each group's entries do too
+        const uint64_t m = __ballot(G != kNone);
+        const uint32_t k = (uint32_t)__popcll(m);
+        if (at + k > end) fits = false;
+        if (fits && G != kNone) {
+            P.nbr[at + __popcll(m & __lanemask_lt())] = G;
+            atomicAdd(P.nbr_bcount + G, 1u);
+        }
+        if (fits) at += k;
+        uint64_t rest = m;
+        while (rest) {
+            const uint32_t s0 = lane_value(s, __ffsll((unsigned long long)rest) - 1);
+            const uint64_t ms = __ballot(s == s0) & m;
+            if (l == s0) mine += (uint32_t)__popcll(ms);
+            rest &= ~ms;
+        }
     }
-    __builtin_amdgcn_wave_barrier();
-    if (l == 0) {
-        P.nbr_start[g] = start;
-        P.nbr_count[g] = fits ? at - start : kNone;
+    const uint32_t before = wave_inclusive_scan(mine) - mine;
+    const bool own = l < pack && g0 + l < ng && !(big >> l & 1u);
+    if (own) {
+        P.nbr_start[g0 + l] = start + before;
+        P.nbr_count[g0 + l] = fits ? mine : kNone;
     }
     if (!fits) {
         at = start;
-        overflow++;
+        overflow += (uint32_t)__popcll(__ballot(own));
     }
-    return true;
+    return big;
 }
 
 // Forward lists, one wave per group: only offsets that lead to a larger key
@@ -638,7 +691,10 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
     __shared__ int8_t s_ga[kWavesPerBlock][kListHalf], s_gb[kWavesPerBlock][kListHalf];
     __shared__ int64_t s_ka[kWavesPerBlock][kListHalf], s_kb[kWavesPerBlock][kListHalf];
     __shared__ uint32_t s_pre[kWavesPerBlock][kListHalf + 1];
-    __shared__ uint32_t s_rs[kWavesPerBlock][kListHalf];
+    // the prefix ranges' offsets, and the boxes of a wave's groups
+    __shared__ uint32_t s_off[kWave], s_norm[kWave], s_rs[kWavesPerBlock][kWave], s_sub[kWavesPerBlock][kWave];
+    __shared__ int64_t s_kd[kWave], s_eps2[kWavesPerBlock][kListPack];
+    __shared__ int32_t s_box[kWavesPerBlock][kListPack][2 * D];
     int64_t(*s_in)[kListHalf] = s_ka;     // unsorted sums, before the key offsets
     int NA = 1, NB = 1;
     for (int e = 0; e < DA; e++) NA *= (int)P.list_w;
@@ -650,16 +706,42 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
     uint32_t at = (blockIdx.x * kWavesPerBlock + w) * slab;
     const uint32_t end = at + slab;
     uint32_t overflow = 0;
+    // forward offsets of the prefix's axes, nearest first
+    uint32_t nf = 0, pack = 1, scan_max = 0;
+    if (P.pstart) {
+        uint32_t all = 1, others = 1;
+        for (uint32_t e = 0; e < P.paxes; e++) all *= P.list_w;
+        for (uint32_t e = P.paxes; e < (uint32_t)D; e++) others *= P.list_w;
+        nf = (all + 1) / 2;
+        pack = min((uint32_t)kListPack, kWave / nf);
+        scan_max = max(64u, 2u * others);
+        uint32_t off = 0, norm = 0, rank = 0;
+        if (threadIdx.x < nf) {
+            off = forward_offset(threadIdx.x, P.paxes, P.list_w, all, &norm);
+            s_norm[threadIdx.x] = norm;
+        }
+        __syncthreads();
+        if (threadIdx.x < nf) {
+            for (uint32_t f = 0; f < nf; f++) rank += s_norm[f] < norm || (s_norm[f] == norm && f < threadIdx.x);
+            int64_t kd = 0;
+            for (uint32_t e = 0; e < P.paxes; e++) kd += (int64_t)(int8_t)(off >> (8 * e)) * (int64_t)(1ull << P.goff[e]);
+            s_off[rank] = off;
+            s_kd[rank] = kd;
+        }
+        __syncthreads();
+    }
     const DynRange dr_ = dyn_range(P.ctr->dyn[kDynLists], P.order);
-    HCA_FOR_UNITS_DYN(g, ng, dr_) {
+    HCA_FOR_UNITS_DYN(u, (ng + pack - 1) / pack, dr_) {
+      uint32_t left = 1;
+      if (P.pstart)
+          left = list_by_prefix<D>(P, u * pack, ng, nf, pack, scan_max, s_off, s_kd, s_pre[w], s_rs[w], s_sub[w],
+                                   s_box[w], s_eps2[w], at, end, overflow);
+      while (left) {
+        const uint32_t g = u * pack + (__ffs(left) - 1);
+        left &= left - 1;
         const uint64_t gkey = P.group_key[g];
         const Geo<D> geo = cube_geo<D>(P, gkey);
         const QBox<D> qb = load_gbox<D>(P, g);
-        if constexpr (DA >= 1) {
-            if (P.pstart && list_by_prefix<D>(P, g, gkey, qb, geo, ng, NA, s_pre[w], s_rs[w], s_ga[w], at, end,
-                                              overflow, NB))
-                continue;
-        }
         // both halves' gap sums, sorted ascending, with their signs
         for (int i = l; i < NA; i += kWave) s_in[w][i] = half_gap2<D, DA>(P, gkey, 0, i, qb, geo);
         __builtin_amdgcn_wave_barrier();
@@ -761,6 +843,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
             at = start;
             overflow++;
         }
+      }
     }
     if (l == 0 && overflow) atomicAdd(&P.ctr->nbr_overflow, overflow);
 }
@@ -823,6 +906,20 @@ __device__ __forceinline__ uint32_t candidate_pos(uint32_t c, uint32_t total, co
     if (c >= total) return 0;
     const uint32_t ln = candidate_lane(c, s_pre);
     return s_beg[ln] + (c - s_pre[ln]);
+}
+
+// Order of a lane's box by its gap to the box q: the smaller the nearer, the
+// lane number in the low six bits, never kNone.
+template <int D>
+__device__ __forceinline__ uint32_t near_rank(const QBox<D> &b, const QBox<D> &q)
+{
+    float acc = 0.f;
+#pragma unroll
+    for (int e = 0; e < D; e++) {
+        const float gap = (float)max(max((int64_t)b.lo[e] - q.hi[e], (int64_t)q.lo[e] - b.hi[e]), (int64_t)0);
+        acc += gap * gap;
+    }
+    return (__float_as_uint(acc) & ~63u) | lane_id();
 }
 
 // Neighbour counts of the chunk points not yet flagged in `done`, over group
@@ -2440,7 +2537,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
         const uint32_t slots = src.lists ? 1 + src.fcount : src.slots;
         for (uint32_t oc = 1; oc < slots; oc += kWave) {
             const uint32_t j = oc + l;
-            uint32_t GB = kNone, tiles = 0, cb = 0, ntb = 1;
+            uint32_t GB = kNone, tiles = 0, cb = 0, ntb = 1, rank = kNone;
             bool both = false;
             if (j < slots) {
                 uint64_t nk = ~0ull;
@@ -2476,14 +2573,18 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
                 }
             }
             // small pairs of unified groups: searched right away
-            uint64_t now = __ballot(GB != kNone && both && tiles <= kInlineTiles);
-            while (now) {
-                const uint32_t src_lane = __ffsll((unsigned long long)now) - 1;
+            // (point boxes are kept whenever lists are built; nearest first)
+            if (GB != kNone && both && tiles <= kInlineTiles)
+                rank = P.nbr_cap ? near_rank<D>(load_gbox<D>(P, GB), qb) : l;
+            while (true) {
+                const uint32_t next = wave_min(rank);
+                if (next == kNone) break;
+                const uint32_t src_lane = next & 63u;
                 const uint32_t gb = __shfl(GB, src_lane);
                 for (uint32_t ra = a0; ra < a1; ra += kWave)
                     link_rows<D, WIDE, false>(P, GA, gb, true, true, ra, min(a1, ra + kWave), P.group_start[gb],
                                        P.group_start[gb + 1], s_pt[w], lt);
-                now &= now - 1;
+                if (l == src_lane) rank = kNone;
             }
             if (both && tiles <= kInlineTiles) GB = kNone;
             // the rest: a worklist entry per chunk of the group with fewer

@@ -246,7 +246,8 @@ struct Plan {
     // group mode: the groups sharing a prefix of the first d/2 axes (the key
     // above bit pshift) are consecutive; pstart / pend give the range of
     // each prefix (valid when group_key[pstart[p]] >> pshift == p), or null
-    uint32_t pshift;
+    uint32_t pshift, paxes;     // (the prefix spans the first paxes axes)
+    uint32_t pnarrow;           // long ranges are narrowed along the next axis
     uint32_t *pstart;           // [2^pbits]
     uint32_t *pend;             // [2^pbits]
     uint32_t *nbr_count;        // [n] forward entries

@@ -1,0 +1,43 @@
+"""GPU parity of the neighbour lists built from prefix ranges, several groups
+per wave, against the oracle: group counts around the packs of a wave, ranges
+that are narrowed along the next axis, and ranges too long to be scanned."""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import pytest
+
+import test_gpu
+from paper_1912_00323_amd.datagen import make_blobs, quantise
+from test_gpu import ctx  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def lattice(rng, d, axes, per_axis, step):
+    """Points scattered by up to step / 4 around a lattice over the last axes."""
+    grid = np.stack(np.meshgrid(*[np.arange(per_axis)] * axes, indexing="ij"), -1).reshape(-1, axes) * step
+    pts = rng.integers(0, step // 4 + 1, size=(2 * len(grid), d))
+    pts[:, d - axes:] += np.repeat(grid, 2, 0)
+    return pts[rng.permutation(len(pts))].astype(np.int32)
+
+
+@pytest.mark.parametrize("d", [3, 4, 5, 6, 7, 8])
+def test_prefix_packs(ctx, d, monkeypatch):  # noqa: F811
+    monkeypatch.setenv("HCA_SMALL", "0")
+    eps = 100.0
+    for mode in ("cube", "group") if d < 5 else ("group",):
+        monkeypatch.setenv("HCA_SEARCH", mode)
+        # few groups: packs of a wave left part empty
+        for n in (1, 3, 7, 8, 9, 64, 65, 700):
+            rng = np.random.default_rng(31 * n + d)
+            test_gpu.check(ctx, rng.integers(0, 700, size=(n, d)).astype(np.int32), eps, 2, f"{mode} few")
+        # columns of more groups than a range is scanned whole, and planes of
+        # more than are scanned at all
+        for axes, per_axis in ((1, 900), (2, 45)):
+            for step in (1.4 * eps, 0.75 * eps):
+                rng = np.random.default_rng(axes + d)
+                test_gpu.check(ctx, lattice(rng, d, axes, per_axis, int(step)), eps, 3, f"{mode} lattice {axes}")
+        pts = quantise(make_blobs(np.random.default_rng(d), 4000, d, 5, 0.03, 0.2), 12)
+        test_gpu.check(ctx, pts, 0.025 * math.sqrt(2 * d) * 2 ** 12, 5, f"{mode} blobs")
