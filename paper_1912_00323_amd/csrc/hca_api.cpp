@@ -229,6 +229,11 @@ uint32_t env_core_budget()
 // core_budget candidates (64 over column ranges; 512 over lists, where a
 // sparse point's neighbourhood spans a few hundred cubes) before a wider
 // walk takes its point over.
+// Groups of several cubes: eight lanes per point and 256 candidates, against
+// one wave per four points (us, 5-D 1.2M points 804 -> 516, 8-D 500k 417 -> 320,
+// 6-D 400k 327 -> 170, 4-D 1M 272 -> 136); up to five axes and 2^18 points the
+// chunks stay, whose waves finish sooner when there are few (5-D 100k 97, the
+// lanes 121).
 void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
 {
     P.radius = (uint32_t)std::max(0, radius);
@@ -238,7 +243,10 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
         if (P.list_w == 0 && P.d <= 2 && radius <= kColR) P.core_lanes = 1;
         else if (P.list_w != 0 && P.d >= 3 && P.d <= 4) P.core_lanes = 2;
     }
-    P.core_budget = std::getenv("HCA_CORE_BUDGET") || P.core_lanes != 2 ? env_core_budget() : 512u;
+    if (P.m > 1 && !P.hd && want && (P.d > 5 || P.n >= (1u << 18))) P.core_lanes = 3;
+    P.core_budget = std::getenv("HCA_CORE_BUDGET") || P.core_lanes < 2 ? env_core_budget()
+                    : P.core_lanes == 2                                ? 512u
+                                                                       : 256u;
 }
 
 // Radix passes for a key of key_bits bits, digits no wider than the key
@@ -775,7 +783,7 @@ void launch_sequence(hca_ctx *ctx, Plan &P, const Sizes &Z, char *base = nullptr
     mark(ctx, HCA_PHASE_CELLS, true);
     // neighbour-group lists, core points, representatives, merging, border
     // points, labels
-    if (P.nbr_cap) {
+    if (P.nbr_cap || P.m > 1) {
         mark(ctx, HCA_PHASE_LISTS, false);
         launch_lists(P, wb, s);
         mark(ctx, HCA_PHASE_LISTS, true);
@@ -835,7 +843,7 @@ void fill_stats(hca_ctx *ctx, const Plan &P, hca_stats *stats)
         stats->list_overflow = (int32_t)hc->nbr_overflow;
     stats->packed_rows = P.planes != nullptr ? 1 : 0;
     stats->key_axes = P.hd ? (int32_t)P.kd : 0;
-    stats->core_rest = P.hd ? (int64_t)hc->hd_left[0] : P.core_list ? (int64_t)hc->n_defer : 0;
+    stats->core_rest = P.hd ? (int64_t)hc->hd_left[0] : P.core_list && P.m == 1 ? (int64_t)hc->n_defer : 0;
 }
 
 // ---- more than kMaxDim axes ----------------------------------------------------

@@ -373,6 +373,78 @@ __device__ __forceinline__ int64_t half_key_delta(const Plan &P, int first, uint
 // wave appends to its own slab; when a group does not fit, every group is
 // searched over the stencil instead.
 
+// Point boxes of the chunks of 64 sorted positions (lo > hi: none), of all
+// points or of the core points only.
+template <int D, bool CORE>
+__device__ __forceinline__ void store_chunk_boxes(const Plan &P)
+{
+    const uint32_t l = lane_id(), chunks = (P.n + kWave - 1) / kWave;
+    for (uint32_t c = blockIdx.x * kWavesPerBlock + wave_in_block(); c < chunks; c += gridDim.x * kWavesPerBlock) {
+        const uint32_t q = c * kWave + l;
+        const bool in = q < P.n && (!CORE || P.core[q]);
+        const Pt<D> p = load_pt<D>(P.spts, min(q, P.n - 1));
+        int32_t mine = 0;
+#pragma unroll
+        for (int e = 0; e < D; e++) {
+            const int32_t lo = wave_min(in ? p.x[e] : INT32_MAX), hi = wave_max(in ? p.x[e] : INT32_MIN);
+            if (l == (uint32_t)e) mine = lo;
+            if (l == (uint32_t)(D + e)) mine = hi;
+        }
+        if (l < 2u * D) P.cbox[(uint64_t)c * (2 * D) + l] = mine;
+    }
+}
+
+// The range of groups of every prefix (groups are numbered in key order, so
+// each prefix's groups are consecutive), and in group mode the boxes of all
+// chunks of sorted points.  Entries of prefixes absent from this call keep
+// stale values, which the readers reject (the group at pstart has another
+// prefix).
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_group_prep(Plan P)
+{
+    if (P.m > 1) store_chunk_boxes<D, false>(P);
+    if (!P.pstart) return;
+    const uint32_t ng = ld_agent32(&P.ctr->n_groups);
+    for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < ng; g += gridDim.x * kBlock) {
+        const uint64_t p = P.group_key[g] >> P.pshift;
+        if (g == 0 || (P.group_key[g - 1] >> P.pshift) != p) P.pstart[p] = g;
+        if (g + 1 == ng || (P.group_key[g + 1] >> P.pshift) != p) P.pend[p] = g + 1;
+    }
+}
+
+// Box of the points (or, with the boxes of k_core_box, the core points) at
+// the positions [p0, p1) of one wave's group: the boxes of the chunks inside,
+// and the points (mask: which of them count) of the chunks that straddle its
+// ends.  Thousands of points of a dense group, point after point, were the
+// tail of the kernels that need it.
+template <int D, bool CORE>
+__device__ __forceinline__ QBox<D> group_chunks_box(const Plan &P, uint32_t p0, uint32_t p1)
+{
+    const uint32_t l = lane_id();
+    QBox<D> b;
+#pragma unroll
+    for (int e = 0; e < D; e++) { b.lo[e] = INT32_MAX; b.hi[e] = INT32_MIN; }
+    const uint32_t c0 = (p0 + kWave - 1) / kWave, c1 = p1 / kWave;          // whole chunks [c0, c1)
+    const uint32_t h1 = c0 < c1 ? c0 * kWave : p1, t0 = c0 < c1 ? c1 * kWave : p1;
+    for (uint32_t part = 0; part < 2; part++) {
+        const uint32_t q1 = part ? p1 : h1;
+        for (uint32_t q = (part ? t0 : p0) + l; q < q1; q += kWave) {
+            if (CORE && !P.core[q]) continue;
+            const Pt<D> v = load_pt<D>(P.spts, q);
+#pragma unroll
+            for (int e = 0; e < D; e++) { b.lo[e] = min(b.lo[e], v.x[e]); b.hi[e] = max(b.hi[e], v.x[e]); }
+        }
+    }
+    for (uint32_t c = c0 + l; c < c1; c += kWave) {
+        const int32_t *x = P.cbox + (uint64_t)c * (2 * D);
+#pragma unroll
+        for (int e = 0; e < D; e++) { b.lo[e] = min(b.lo[e], x[e]); b.hi[e] = max(b.hi[e], x[D + e]); }
+    }
+#pragma unroll
+    for (int e = 0; e < D; e++) { b.lo[e] = wave_min(b.lo[e]); b.hi[e] = wave_max(b.hi[e]); }
+    return b;
+}
+
 // Point box of every group, and the backward counters cleared.  A wave takes
 // eight groups at a time, eight lanes each: every lane folds every eighth
 // point of its group, three exchanges within the eight lanes combine them,
@@ -439,23 +511,10 @@ __global__ __launch_bounds__(kBlock) void k_group_box(Plan P)
             const uint32_t src = __ffsll((unsigned long long)big) - 1;
             big &= big - 1;
             const uint32_t gb = __shfl(g, src);
-            const QBox<D> bb = group_points_box<D>(P, P.group_start[gb], P.group_start[gb + 1]);
+            const uint32_t b0 = P.group_start[gb], b1 = P.group_start[gb + 1];
+            const QBox<D> bb = P.m > 1 ? group_chunks_box<D, false>(P, b0, b1) : group_points_box<D>(P, b0, b1);
             if (l < (uint32_t)D) store_gbox<D>(P, gb, bb, l);
         }
-    }
-}
-
-// Group mode: the range of groups of every prefix of the first d/2 axes
-// (groups are numbered in key order, so each prefix's groups are
-// consecutive).  Entries of prefixes absent from this call keep stale
-// values, which the readers reject (the group at pstart has another prefix).
-__global__ __launch_bounds__(kBlock) void k_prefix_ranges(Plan P)
-{
-    const uint32_t ng = ld_agent32(&P.ctr->n_groups);
-    for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < ng; g += gridDim.x * kBlock) {
-        const uint64_t p = P.group_key[g] >> P.pshift;
-        if (g == 0 || (P.group_key[g - 1] >> P.pshift) != p) P.pstart[p] = g;
-        if (g + 1 == ng || (P.group_key[g + 1] >> P.pshift) != p) P.pend[p] = g + 1;
     }
 }
 
@@ -922,6 +981,19 @@ __device__ __forceinline__ uint32_t near_rank(const QBox<D> &b, const QBox<D> &q
     return (__float_as_uint(acc) & ~63u) | lane_id();
 }
 
+// Squared gap between the box (lo, hi) and the chunk box b = [lo: D][hi: D].
+template <int D>
+__device__ __forceinline__ int64_t chunk_gap2(const int32_t *lo, const int32_t *hi, const int32_t *b)
+{
+    int64_t acc = 0;
+#pragma unroll
+    for (int e = 0; e < D; e++) {
+        const int64_t gap = max((int64_t)b[e] - hi[e], (int64_t)lo[e] - b[D + e]);
+        if (gap > 0) acc += gap * gap;
+    }
+    return acc;
+}
+
 // Neighbour counts of the chunk points not yet flagged in `done`, over group
 // g and its neighbour groups, until each reaches minPts (then its bit is
 // set).  Returns the updated mask.  With P.rec and a chunk position pc
@@ -931,7 +1003,7 @@ template <int D, bool WIDE, int NP = kPch>
 __device__ __forceinline__ uint32_t count_walk(const Plan &P, uint32_t g, uint64_t gkey, const Pt<D> *pp,
                                                uint32_t done, uint32_t *cnt, uint32_t *s_beg,
                                                uint32_t *s_pre, uint32_t &lt, const Geo<D> &geo,
-                                               uint32_t pc = kNone, const uint32_t *qpos = nullptr)
+                                               uint32_t (*s_chunk)[kWave], uint32_t pc = kNone, const uint32_t *qpos = nullptr)
 {
     const bool record = P.rec != nullptr && (pc != kNone || qpos != nullptr);
     const uint32_t l = lane_id();
@@ -940,7 +1012,38 @@ __device__ __forceinline__ uint32_t count_walk(const Plan &P, uint32_t g, uint64
     const QBox<D> qb = chunk_box<D, NP>(pp, ~done);
     const NbrSrc src = nbr_source(P, g);
     for (uint32_t oc = 0; oc < src.slots && done != all; oc += kWave) {
-        const uint32_t total = load_neighbours<D>(P, g, gkey, src, oc, 0, false, qb, s_beg, s_pre, geo);
+      uint32_t total = load_neighbours<D>(P, g, gkey, src, oc, 0, false, qb, s_beg, s_pre, geo);
+      // Search groups of more than a chunk of points: their chunks in place of
+      // the groups, those within eps of the box only (a dense group holds
+      // thousands of points, most of them far from any one of its
+      // neighbours' points)
+      const uint32_t a = s_beg[l], size = (l + 1 < (uint32_t)kWave ? s_pre[l + 1] : total) - s_pre[l];
+      const bool split = P.m > 1 && __ballot(size > (uint32_t)kWave) != 0;
+      uint32_t chunks = 1;
+      __builtin_amdgcn_wave_barrier();
+      if (split) {
+          const uint32_t nch = size ? (a + size - 1) / kWave - a / kWave + 1 : 0u, inc = wave_inclusive_scan(nch);
+          s_chunk[0][l] = inc - nch;
+          s_chunk[1][l] = a;
+          s_chunk[2][l] = a + size;
+          __builtin_amdgcn_wave_barrier();
+          chunks = lane_value(inc, kWave - 1);
+      }
+      for (uint32_t t0 = 0; t0 < chunks && done != all; t0 += kWave) {
+        if (split) {
+            uint32_t beg = 0, len = 0;
+            if (t0 + l < chunks) {
+                const uint32_t ln = candidate_lane(t0 + l, s_chunk[0]);
+                const uint32_t c = s_chunk[1][ln] / kWave + (t0 + l - s_chunk[0][ln]);
+                beg = max(s_chunk[1][ln], c * kWave);
+                if (chunk_gap2<D>(qb.lo, qb.hi, P.cbox + (uint64_t)c * (2 * D)) <= geo.eps2) len = min(s_chunk[2][ln], c * kWave + kWave) - beg;
+            }
+            const uint32_t inc = wave_inclusive_scan(len);
+            s_beg[l] = beg;
+            s_pre[l] = inc - len;
+            __builtin_amdgcn_wave_barrier();
+            total = lane_value(inc, kWave - 1);
+        }
         // candidate ci + l of the batch; the next batch's point is loaded
         // before this one is tested, so its latency overlaps the tests
         uint32_t nxt = candidate_pos(l, total, s_beg, s_pre);
@@ -968,6 +1071,7 @@ __device__ __forceinline__ uint32_t count_walk(const Plan &P, uint32_t g, uint64
             }
             done = uniform(done);
         }
+      }
     }
     return done;
 }
@@ -1027,7 +1131,7 @@ __global__ __launch_bounds__(kBlock) void k_core(Plan P)
             }
             done = uniform(done);
             const uint32_t all = (1u << kPch) - 1u;
-            if (done != all) done = count_walk<D, WIDE>(P, g, gkey, pp, done, cnt, s_beg[w], s_pre[w], lt, geo, pc);
+            if (done != all) done = count_walk<D, WIDE>(P, g, gkey, pp, done, cnt, s_beg[w], s_pre[w], lt, geo, nullptr, pc);
             // lane k < np writes the result of point pc + k
             uint32_t mine = 0;
 #pragma unroll
@@ -1082,7 +1186,7 @@ template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock, 6) void k_core_chunks(Plan P)
 {
     if (box_missed(P)) return;
-    __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave];
+    __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave], s_chunk[kWavesPerBlock][3][kWave];
     const uint32_t w = wave_in_block(), l = lane_id();
     const uint32_t n = P.n, minpts = (uint32_t)P.min_pts;
     const Geo<D> geo = call_geo<D>(P);
@@ -1116,7 +1220,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_core_chunks(Plan P)
                 const uint32_t run = (uint32_t)__ballot(grp == g) & left;
                 left &= ~run;
                 const uint32_t got = count_walk<D, WIDE, NP>(P, g, P.group_key[g], pp, ~run & all, cnt, s_beg[w],
-                                                         s_pre[w], lt, geo, pc);
+                                                         s_pre[w], lt, geo, s_chunk[w], pc);
                 done |= got & run;
             }
         }
@@ -1547,6 +1651,146 @@ __global__ __launch_bounds__(kBlock) void k_core_list_lanes(Plan P)
     flush_tests(P, kTestsCore, lt);
 }
 
+// Group mode: eight lanes per point of a sparse cube.  They count the point's
+// own cube whole (every pair in a cube is within eps), then walk the rest of
+// its group and the groups of its list that the point itself can reach (not
+// the box of several points): a slot per lane at a time, then two candidates
+// per lane.  What bounds it is the chain of dependent loads, list entry, box,
+// range, row; eight points per wave run eight chains at once, and a point
+// that has its minPts neighbours costs nothing further (5-D, 1.2M points:
+// 108M tests -> 42M, 804 -> 516 us).  A lane per point makes the chains eight
+// times as long (1231 us).  A point still short after P.core_budget
+// candidates goes to a wave of its own, which also skips the chunks of large
+// groups that lie out of reach.
+constexpr int kOct = 8;
+
+template <int D, bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_core_group_lanes(Plan P)
+{
+    if (box_missed(P)) return;
+    __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave];
+    const uint32_t ns = ld_agent32(&P.ctr->n_sparse);
+    const bool lists = P.nbr_cap && P.ctr->nbr_overflow == 0;
+    const uint32_t w = wave_in_block(), l = lane_id(), sub = l % kOct, first = l - sub;
+    const uint32_t minpts = (uint32_t)P.min_pts, budget = P.core_budget;
+    const int64_t eps2 = P.eps2;
+    uint32_t lt = 0;
+    const WaveRange hca_wr_ = wave_range(P.order);
+    HCA_FOR_UNITS(u, (ns + kOct - 1) / kOct) {
+        const uint32_t i = u * kOct + l / kOct;
+        bool defer = false;
+        uint32_t q = kNone;
+        if (i < ns) {
+            q = P.core_list[i];
+            const uint32_t c = P.cell_of[q], g = P.group_of[c];
+            const Pt<D> p = load_pt<D>(P.spts, q);
+            QBox<D> pb;
+#pragma unroll
+            for (int e = 0; e < D; e++) pb.lo[e] = pb.hi[e] = p.x[e];
+            const uint32_t a0 = P.cell_start[c], b0 = P.cell_start[c + 1];
+            const uint32_t g0 = P.group_start[g], g1 = P.group_start[g + 1];
+            uint32_t cnt = b0 - a0;
+            if (P.rec)
+                for (uint32_t t = sub; t < cnt && t < (uint32_t)kRec; t += kOct) P.rec[(uint64_t)q * kRec + t] = a0 + t;
+            defer = !lists;
+            if (lists) {
+                // slot 0: the group's points before the cube, 1: those after
+                const uint32_t fs = P.nbr_start[g], fc = P.nbr_count[g], bs = P.nbr_bstart[g];
+                const uint32_t nslots = 2u + fc + P.nbr_bcount[g];
+                uint32_t tested = 0;
+                for (uint32_t j = 0; j < nslots && cnt < minpts && tested < budget; j += kOct) {
+                    const uint32_t k = j + sub;
+                    uint32_t lo = 0, size = 0;
+                    if (k == 0) {
+                        lo = g0;
+                        size = a0 - g0;
+                    } else if (k == 1) {
+                        lo = b0;
+                        size = g1 - b0;
+                    } else if (k < nslots) {
+                        const uint32_t G = k - 2u < fc ? P.nbr[fs + k - 2u] : P.nbr_back[bs + (k - 2u - fc)];
+                        if (gbox_within<D>(P, G, pb, eps2)) {
+                            lo = P.group_start[G];
+                            size = P.group_start[G + 1] - lo;
+                        }
+                    }
+                    uint32_t inc = size;
+#pragma unroll
+                    for (int o = 1; o < kOct; o <<= 1) {
+                        const uint32_t t = __shfl_up(inc, o, kOct);
+                        if (sub >= (uint32_t)o) inc += t;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    s_beg[w][l] = lo;
+                    s_pre[w][l] = inc - size;
+                    __builtin_amdgcn_wave_barrier();
+                    const uint32_t total = __shfl(inc, kOct - 1, kOct);
+                    for (uint32_t v = 0; v < total && cnt < minpts && tested < budget; v += 2 * kOct) {
+                        uint32_t pos[2];
+                        Pt<D> o[2];
+#pragma unroll
+                        for (int b = 0; b < 2; b++) {
+                            const uint32_t t = min(v + (uint32_t)b * kOct + sub, total - 1u);
+                            uint32_t r = 0;                   // last slot with pre <= t
+#pragma unroll
+                            for (uint32_t h = kOct / 2; h; h >>= 1)
+                                if (s_pre[w][first + r + h] <= t) r += h;
+                            pos[b] = s_beg[w][first + r] + (t - s_pre[w][first + r]);
+                            o[b] = load_pt<D>(P.spts, pos[b]);
+                        }
+#pragma unroll
+                        for (int b = 0; b < 2; b++) {
+                            const bool ok = v + (uint32_t)b * kOct + sub < total;
+                            lt += ok;
+                            const bool hit = ok && within<D, WIDE>(p, o[b], eps2);
+                            const uint32_t hits = (uint32_t)(__ballot(hit) >> first) & ((1u << kOct) - 1u);
+                            const uint32_t r = cnt + (uint32_t)__popc(hits & ((1u << sub) - 1u));
+                            if (P.rec && hit && r < (uint32_t)kRec) P.rec[(uint64_t)q * kRec + r] = pos[b];
+                            cnt += (uint32_t)__popc(hits);
+                        }
+                        tested += 2 * kOct;
+                    }
+                }
+                // budget spent with candidates left: a wave decides this point
+                defer = cnt < minpts && tested >= budget;
+            }
+            if (!defer && sub == 0) core_result(P, q, c, cnt, minpts);
+        }
+        const uint64_t m = __ballot(defer && sub == 0);
+        if (m) {
+            const uint32_t lead = (uint32_t)__ffsll((unsigned long long)m) - 1u;
+            uint32_t at = 0;
+            if (l == lead) at = atomicAdd(&P.ctr->n_defer, (uint32_t)__popcll(m));
+            at = __shfl(at, lead);
+            if (defer && sub == 0) P.core_defer[at + __popcll(m & __lanemask_lt())] = q;
+        }
+    }
+    flush_tests(P, kTestsCore, lt);
+}
+
+// The points that the lanes of group mode left, one wave each.
+template <int D, bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_core_group_deferred(Plan P)
+{
+    if (box_missed(P)) return;
+    __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave], s_chunk[kWavesPerBlock][3][kWave];
+    const uint32_t w = wave_in_block();
+    const uint32_t nd = ld_agent32(&P.ctr->n_defer);
+    const Geo<D> geo = call_geo<D>(P);
+    uint32_t lt = 0;
+    const WaveRange hca_wr_ = wave_range(P.order);
+    HCA_FOR_UNITS(i, nd) {
+        const uint32_t q = P.core_defer[i];
+        const uint32_t c = P.cell_of[q], g = P.group_of[c];
+        Pt<D> pp[1];
+        uint32_t qpos[1] = {q}, cnt[1] = {0};
+        pp[0] = load_pt<D>(P.spts, q);
+        count_walk<D, WIDE, 1>(P, g, P.group_key[g], pp, 0u, cnt, s_beg[w], s_pre[w], lt, geo, s_chunk[w], kNone, qpos);
+        if (lane_id() == 0) core_result(P, q, c, cnt[0], geo.min_pts);
+    }
+    flush_tests(P, kTestsCore, lt);
+}
+
 // The deferred points of the list lane walk, one wave each: the count walk
 // of a one-point chunk over the cube's list (or the stencil), from zero.
 template <int D, bool WIDE>
@@ -1573,7 +1817,7 @@ __global__ __launch_bounds__(kBlock) void k_core_list_deferred(Plan P)
             qpos[k] = q;
             cnt[k] = 0;
         }
-        count_walk<D, WIDE>(P, c, gkey, pp, all & ~1u, cnt, s_beg[w], s_pre[w], lt, geo, kNone, qpos);
+        count_walk<D, WIDE>(P, c, gkey, pp, all & ~1u, cnt, s_beg[w], s_pre[w], lt, geo, nullptr, kNone, qpos);
         if (lane_id() == 0) core_result(P, q, c, cnt[0], geo.min_pts);
     }
     flush_tests(P, kTestsCore, lt);
@@ -2184,33 +2428,7 @@ template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_core_box(Plan P)
 {
     if (box_missed(P)) return;
-    const uint32_t l = lane_id(), chunks = (P.n + kWave - 1) / kWave;
-    for (uint32_t c = blockIdx.x * kWavesPerBlock + wave_in_block(); c < chunks; c += gridDim.x * kWavesPerBlock) {
-        const uint32_t q = c * kWave + l;
-        const bool core = q < P.n && P.core[q];
-        const Pt<D> p = load_pt<D>(P.spts, min(q, P.n - 1));
-        int32_t mine = 0;
-#pragma unroll
-        for (int e = 0; e < D; e++) {
-            const int32_t lo = wave_min(core ? p.x[e] : INT32_MAX), hi = wave_max(core ? p.x[e] : INT32_MIN);
-            if (l == (uint32_t)e) mine = lo;
-            if (l == (uint32_t)(D + e)) mine = hi;
-        }
-        if (l < 2u * D) P.cbox[(uint64_t)c * (2 * D) + l] = mine;
-    }
-}
-
-// Squared gap between the box (lo, hi) and the chunk box b = [lo: D][hi: D].
-template <int D>
-__device__ __forceinline__ int64_t chunk_gap2(const int32_t *lo, const int32_t *hi, const int32_t *b)
-{
-    int64_t acc = 0;
-#pragma unroll
-    for (int e = 0; e < D; e++) {
-        const int64_t gap = max((int64_t)b[e] - hi[e], (int64_t)lo[e] - b[D + e]);
-        if (gap > 0) acc += gap * gap;
-    }
-    return acc;
+    store_chunk_boxes<D, true>(P);
 }
 
 // Core pairs of the rows [ra0, ra1) of group GA (at most 64 sorted positions)
@@ -2520,18 +2738,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
         // bounding box of GA's core points
         const uint32_t a0 = P.group_start[GA], a1 = P.group_start[GA + 1];
         const uint32_t ca = a0 / kWave, nta = (a1 - 1) / kWave - ca + 1;        // its chunks
-        QBox<D> qb;
-#pragma unroll
-        for (int e = 0; e < D; e++) { qb.lo[e] = INT32_MAX; qb.hi[e] = INT32_MIN; }
-        for (uint32_t q = a0 + l; q < a1 + l; q += kWave) {
-            if (q < a1 && P.core[q]) {
-                const Pt<D> p = load_pt<D>(P.spts, q);
-#pragma unroll
-                for (int e = 0; e < D; e++) { qb.lo[e] = min(qb.lo[e], p.x[e]); qb.hi[e] = max(qb.hi[e], p.x[e]); }
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < D; e++) { qb.lo[e] = wave_min(qb.lo[e]); qb.hi[e] = wave_max(qb.hi[e]); }
+        const QBox<D> qb = group_chunks_box<D, true>(P, a0, a1);
         const NbrSrc src = nbr_source(P, GA);
         // groups GB > GA: the forward list, or the whole stencil
         const uint32_t slots = src.lists ? 1 + src.fcount : src.slots;
@@ -3134,13 +3341,14 @@ void launch_table(const Plan &P, int blocks, hipStream_t s)
 
 void launch_lists(const Plan &P, int blocks, hipStream_t s)
 {
-    if (!P.nbr_cap) return;
     switch (P.d) {
 #define HCA_LISTS_D(DD)                                                                        \
     case DD:                                                                                   \
-        hipLaunchKernelGGL(k_group_box<DD>, dim3(blocks), dim3(kBlock), 0, s, P);             \
-        if (P.pstart) hipLaunchKernelGGL(k_prefix_ranges, dim3(1024), dim3(kBlock), 0, s, P); \
-        hipLaunchKernelGGL(k_nbr_lists<DD>, dim3(blocks), dim3(kBlock), 0, s, P);             \
+        if (P.m > 1 || P.pstart)                                                               \
+            hipLaunchKernelGGL(k_group_prep<DD>, dim3(1024), dim3(kBlock), 0, s, P);           \
+        if (!P.nbr_cap) return;                                                                \
+        hipLaunchKernelGGL(k_group_box<DD>, dim3(blocks), dim3(kBlock), 0, s, P);              \
+        hipLaunchKernelGGL(k_nbr_lists<DD>, dim3(blocks), dim3(kBlock), 0, s, P);              \
         break;
         HCA_LISTS_D(1) HCA_LISTS_D(2) HCA_LISTS_D(3) HCA_LISTS_D(4)
         HCA_LISTS_D(5) HCA_LISTS_D(6) HCA_LISTS_D(7) HCA_LISTS_D(8)
@@ -3189,6 +3397,13 @@ void launch_core(const Plan &P, int blocks, hipStream_t s)
 #undef HCA_CORE_LANES
         }
         hipLaunchKernelGGL(k_core_cubes, dim3(fb), dim3(kFlatBlock), 0, s, P);
+        return;
+    }
+    if (P.m > 1 && P.core_list) {
+        const int fb = (int)std::max<uint64_t>(1, (P.n + kFlatBlock - 1) / kFlatBlock);
+        hipLaunchKernelGGL(k_core_flat<1>, dim3(fb), dim3(kFlatBlock), 0, s, P);
+        HCA_DISPATCH_DW(k_core_group_lanes, P, blocks, s);
+        HCA_DISPATCH_DW(k_core_group_deferred, P, blocks, s);
         return;
     }
     if (P.m > 1) HCA_DISPATCH_DW(k_core_chunks, P, blocks, s);

@@ -41,3 +41,16 @@ def test_prefix_packs(ctx, d, monkeypatch):  # noqa: F811
                 test_gpu.check(ctx, lattice(rng, d, axes, per_axis, int(step)), eps, 3, f"{mode} lattice {axes}")
         pts = quantise(make_blobs(np.random.default_rng(d), 4000, d, 5, 0.03, 0.2), 12)
         test_gpu.check(ctx, pts, 0.025 * math.sqrt(2 * d) * 2 ** 12, 5, f"{mode} blobs")
+
+
+@pytest.mark.parametrize("budget", ["16", "256"])
+def test_group_lanes(ctx, budget, monkeypatch):  # noqa: F811
+    """Core marking by eight lanes per point: minPts below and above the lanes
+    and the records of a point, budgets that leave most points to a wave, and
+    groups of more than a chunk of points."""
+    monkeypatch.setenv("HCA_SMALL", "0")
+    monkeypatch.setenv("HCA_CORE_BUDGET", budget)
+    for d in (6, 8):
+        for std, mp in ((0.03, 3), (0.03, 14), (0.008, 40)):
+            pts = quantise(make_blobs(np.random.default_rng(mp + d), 5003, d, 4, std, 0.15), 12)
+            test_gpu.check(ctx, pts, 0.018 * math.sqrt(2 * d) * 2 ** 12, mp, f"lanes {budget}")
