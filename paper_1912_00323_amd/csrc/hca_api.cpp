@@ -249,6 +249,14 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
                                                                        : 256u;
 }
 
+// Exact merging of cubes over neighbour lists goes by the neighbours that core
+// marking records, without representatives.
+void plan_linked(Plan &P)
+{
+    P.linked = P.m == 1 && P.list_w && P.d >= 3 && P.d <= 4 && !P.rep_only && env_record();
+    if (P.linked) P.n_dir = 0;
+}
+
 // Radix passes for a key of key_bits bits, digits no wider than the key
 // type's (9 bits for 32-bit keys, 8 for 64-bit ones) or the tuned cap.
 uint32_t key_passes(uint32_t key_bits, bool wide, const Tune *t = nullptr)
@@ -1344,6 +1352,7 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
     }
     P.list_w = P.m == 1 ? cube_list_width(d, G.radius, n_off) : 0;
     plan_core_lanes(P, G.radius);
+    plan_linked(P);
     Sizes Z;
     plan_sizes(P, gbits, stats != nullptr && ctx->prof != -1, stats != nullptr, &Z);
     plan_prefix(P, gbits, far_axes >= 2, &Z);
@@ -1697,6 +1706,7 @@ void batch_plan(BatchGroup &g, char *db, const Tune *t)
     for (int32_t v : g.radius) rmax = std::max(rmax, v);
     P.list_w = cube_list_width(d, rmax, P.n_off, t);
     plan_core_lanes(P, rmax, t);
+    plan_linked(P);
     plan_sizes(P, P.key_bits, false, false, &g.Z, t);
     plan_prefix(P, P.key_bits, g.far, &g.Z, t);
 }

@@ -1106,7 +1106,10 @@ __global__ __launch_bounds__(kBlock) void k_core(Plan P)
             const bool dense = b - a >= minpts;
             any_sparse |= !dense;
             if (dense)
-                for (uint32_t q = a + l; q < b; q += kWave) P.core[q] = 1;
+                for (uint32_t q = a + l; q < b; q += kWave) {
+                    P.core[q] = 1;
+                    if (P.rec) P.nrec[q] = 0;
+                }
         }
         if (!any_sparse) {
             for (uint32_t c = c0 + l; c < c1; c += kWave) {
@@ -2185,6 +2188,101 @@ __device__ __forceinline__ void queue_exact(const Plan &P, bool exact, uint32_t 
     }
 }
 
+// Cubes over neighbour lists (three and four axes), exact merging: no
+// representatives.  A point of a sparse cube has its first neighbours
+// recorded by core marking, and linking those (k_link_recorded) joins nearly
+// everything that touches a sparse cube; k_merge_near joins most cubes of
+// core points only through a few sampled pairs.  After a flattening nearly
+// all listed pairs share a root, which costs one load per pair; what is left
+// is tested exactly.  Such cubes hold two or three points on average, and
+// writing, folding and reading 26 or 80 representatives for each was most of
+// the call: 4-D, 1M points, reps and merge 1199 us before.
+constexpr int kMergeLanes = 16;          // lanes per cube
+constexpr uint32_t kNearSlots = 8;       // listed cubes sampled per cube
+constexpr uint32_t kLanePairs = 16;      // point pairs that a lane tests by itself
+
+// Cubes of core points only against the first cubes of their lists: 16
+// sampled pairs each, a lane per pair.
+template <int D, bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_merge_near(Plan P)
+{
+    if (box_missed(P) || !P.nbr_cap || P.ctr->nbr_overflow) return;
+    const uint32_t l = lane_id(), sub = l % kMergeLanes, first = l - sub;
+    const uint32_t nc = ld_agent32(&P.ctr->n_cells);
+    uint32_t lt = 0;
+    const WaveRange hca_wr_ = wave_range(P.order);
+    HCA_FOR_UNITS(u, (nc + kWave / kMergeLanes - 1) / (kWave / kMergeLanes)) {
+        const uint32_t A = u * (kWave / kMergeLanes) + l / kMergeLanes;
+        if (A >= nc) continue;
+        const uint32_t a0 = P.cell_start[A], na = P.cell_start[A + 1] - a0;
+        const Geo<D> geo = cube_geo<D>(P, P.group_key[A]);
+        if (na < geo.min_pts) continue;
+        const Pt<D> pa = load_pt<D>(P.spts, a0 + (uint32_t)(((uint64_t)(sub & 3u) * na) >> 2));
+        const uint32_t fs = P.nbr_start[A], slots = min(P.nbr_count[A], kNearSlots);
+        for (uint32_t j = 0; j < slots; j++) {
+            const uint32_t B = P.nbr[fs + j];
+            if (P.ncore[B] == 0) continue;
+            const uint32_t b0 = P.cell_start[B], nb = P.cell_start[B + 1] - b0;
+            const uint32_t q = b0 + (uint32_t)(((uint64_t)(sub >> 2) * nb) >> 2);
+            lt++;
+            const bool hit = P.core[q] && within<D, WIDE>(pa, load_pt<D>(P.spts, q), geo.eps2);
+            if ((uint32_t)(__ballot(hit) >> first) & ((1u << kMergeLanes) - 1u))
+                if (sub == 0) uf_union<true>(P.parent, A, B);
+        }
+    }
+    flush_tests(P, kTestsMerge, lt);
+}
+
+// Every listed pair of core cubes that does not share a root yet: a few
+// point pairs are tested by the lane, more go to the worklist.
+template <int D, bool WIDE>
+__device__ __forceinline__ void merge_lists(const Plan &P, uint32_t &lt)
+{
+    const uint32_t l = lane_id(), sub = l % kMergeLanes;
+    const uint32_t nc = ld_agent32(&P.ctr->n_cells);
+    const WaveRange hca_wr_ = wave_range(P.order);
+    HCA_FOR_UNITS(u, (nc + kWave / kMergeLanes - 1) / (kWave / kMergeLanes)) {
+        const uint32_t A = u * (kWave / kMergeLanes) + l / kMergeLanes;
+        uint32_t fs = 0, slots = 0, a0 = 0, na = 0, rA = kNone;
+        int64_t eps2 = 0;
+        if (A < nc && P.ncore[A] != 0) {
+            a0 = P.cell_start[A];
+            na = P.cell_start[A + 1] - a0;
+            eps2 = cube_geo<D>(P, P.group_key[A]).eps2;
+            fs = P.nbr_start[A];
+            slots = P.nbr_count[A];
+            rA = uf_find<true>(P.parent, A);
+        }
+        const uint32_t most = wave_max(slots);
+        for (uint32_t j0 = 0; j0 < most; j0 += kMergeLanes) {
+            uint32_t B = kNone;
+            bool exact = false;
+            if (j0 + sub < slots) {
+                B = P.nbr[fs + j0 + sub];
+                if (ld_parent_cached(P.parent + B) != rA && P.ncore[B] != 0)
+                    exact = uf_find<true>(P.parent, A) != uf_find<true>(P.parent, B);
+            }
+            if (exact) {
+                const uint32_t b0 = P.cell_start[B], nb = P.cell_start[B + 1] - b0;
+                if ((uint64_t)na * nb <= kLanePairs) {
+                    exact = false;
+                    bool hit = false;
+                    for (uint32_t ia = a0; ia < a0 + na && !hit; ia++) {
+                        if (!P.core[ia]) continue;
+                        const Pt<D> pa = load_pt<D>(P.spts, ia);
+                        for (uint32_t ib = b0; ib < b0 + nb; ib++) {
+                            lt++;
+                            hit |= P.core[ib] && within<D, WIDE>(pa, load_pt<D>(P.spts, ib), eps2);
+                        }
+                    }
+                    if (hit) uf_union<true>(P.parent, A, B);
+                }
+            }
+            queue_exact<D, WIDE>(P, exact, A, B, lt);
+        }
+    }
+}
+
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_merge_rep(Plan P)
 {
@@ -2194,6 +2292,13 @@ __global__ __launch_bounds__(kBlock) void k_merge_rep(Plan P)
     const uint32_t nc = ld_agent32(&P.ctr->n_cells);
     const WaveRange hca_wr_ = wave_range(P.order);
     const bool lists = P.nbr_cap && P.ctr->nbr_overflow == 0;
+    if constexpr (D == 3 || D == 4) {
+        if (P.linked && lists) {
+            merge_lists<D, WIDE>(P, lt);
+            flush_tests(P, kTestsMerge, lt);
+            return;
+        }
+    }
     const uint64_t flat_units = ((uint64_t)nc * P.n_off + kWave - 1) / kWave;
     if (!lists && flat_units <= 0xffffffffull) {
         // stencil: one (cube, offset) pair per lane, so the few forward
@@ -3451,10 +3556,20 @@ void launch_merge(const Plan &P, int blocks, hipStream_t s)
         // flattening of the forest, then the others, whose finds then start
         // from flat trees (hooking in key order alone builds long chains
         // through large clusters)
-        const int launches = P.merge_split ? 2 : 1;
+        const int launches = P.merge_split && !P.linked ? 2 : 1;
+        if (P.linked) {
+            launch_link_recorded(P, s);
+            switch (P.d * 2 + (P.wide ? 1 : 0)) {
+            case 6: hipLaunchKernelGGL((k_merge_near<3, false>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            case 7: hipLaunchKernelGGL((k_merge_near<3, true>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            case 8: hipLaunchKernelGGL((k_merge_near<4, false>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            case 9: hipLaunchKernelGGL((k_merge_near<4, true>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            }
+            hipLaunchKernelGGL(k_flatten, dim3(1024), dim3(kBlock), 0, s, P);
+        }
         for (int r = 0; r < launches; r++) {
             Plan Q = P;
-            Q.merge_phase = P.merge_split ? (uint32_t)r + 1u : 0u;
+            Q.merge_phase = launches == 2 ? (uint32_t)r + 1u : 0u;
             if (r) hipLaunchKernelGGL(k_flatten, dim3(1024), dim3(kBlock), 0, s, Q);
             if (P.core_list && P.core_lanes == 1) {
                 switch (P.d * 2 + (P.wide ? 1 : 0)) {

@@ -199,6 +199,7 @@ struct Plan {
     // representative points (m == 1 only): directions per cube, and for each
     // offset the direction index of sign(offset) and of -sign(offset)
     uint32_t n_dir;
+    uint32_t linked;            // cubes over lists merge from the recorded neighbours (no representatives)
     const uint16_t *dir_fwd;    // [n_off]
     const uint16_t *dir_bwd;    // [n_off]
     // group lookup: direct table over the packed group key, or hash

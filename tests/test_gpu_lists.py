@@ -54,3 +54,27 @@ def test_group_lanes(ctx, budget, monkeypatch):  # noqa: F811
         for std, mp in ((0.03, 3), (0.03, 14), (0.008, 40)):
             pts = quantise(make_blobs(np.random.default_rng(mp + d), 5003, d, 4, std, 0.15), 12)
             test_gpu.check(ctx, pts, 0.018 * math.sqrt(2 * d) * 2 ** 12, mp, f"lanes {budget}")
+
+
+@pytest.mark.parametrize("d", [3, 4])
+def test_cubes_joined_by_few_pairs(ctx, d, monkeypatch):  # noqa: F811
+    """Cubes of core points only, no recorded neighbours, whose nearest point
+    pairs lie just within or just past eps: the sampled pairs miss them, and
+    small and large products of points take the lane and the worklist."""
+    monkeypatch.setenv("HCA_SMALL", "0")
+    monkeypatch.setenv("HCA_SEARCH", "cube")
+    eps, rng = 100.0, np.random.default_rng(d)
+    for lanes in ("1", "0"):
+        monkeypatch.setenv("HCA_CORE_LANES", lanes)
+        for size in (3, 4, 5, 40, 300):
+            sets = []
+            for pair in range(40):
+                base = np.zeros(d, np.int64)
+                base[d - 1] = 400 * pair
+                for side in (0, 1):
+                    clump = rng.integers(0, 30, size=(size, d))
+                    clump[:, 0] += side * int(rng.integers(70, 131))
+                    sets.append(clump + base)
+            pts = np.concatenate(sets)
+            pts = pts[rng.permutation(len(pts))].astype(np.int32)
+            test_gpu.check(ctx, pts, eps, 3, f"few pairs {size}")
