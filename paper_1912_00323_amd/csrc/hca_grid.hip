@@ -2218,17 +2218,31 @@ __global__ __launch_bounds__(kBlock) void k_merge_near(Plan P)
         const Geo<D> geo = cube_geo<D>(P, P.group_key[A]);
         if (na < geo.min_pts) continue;
         const Pt<D> pa = load_pt<D>(P.spts, a0 + (uint32_t)(((uint64_t)(sub & 3u) * na) >> 2));
-        const uint32_t fs = P.nbr_start[A], slots = min(P.nbr_count[A], kNearSlots);
-        for (uint32_t j = 0; j < slots; j++) {
-            const uint32_t B = P.nbr[fs + j];
-            if (P.ncore[B] == 0) continue;
-            const uint32_t b0 = P.cell_start[B], nb = P.cell_start[B + 1] - b0;
-            const uint32_t q = b0 + (uint32_t)(((uint64_t)(sub >> 2) * nb) >> 2);
-            lt++;
-            const bool hit = P.core[q] && within<D, WIDE>(pa, load_pt<D>(P.spts, q), geo.eps2);
-            if ((uint32_t)(__ballot(hit) >> first) & ((1u << kMergeLanes) - 1u))
-                if (sub == 0) uf_union<true>(P.parent, A, B);
+        // a slot per lane: its cube and point range
+        uint32_t B = kNone, b0 = 0, nb = 0;
+        if (sub < min(P.nbr_count[A], kNearSlots)) {
+            B = P.nbr[P.nbr_start[A] + sub];
+            b0 = P.cell_start[B];
+            nb = P.ncore[B] ? P.cell_start[B + 1] - b0 : 0u;
         }
+        uint32_t q[kNearSlots];
+        Pt<D> pb[kNearSlots];
+        bool core[kNearSlots];
+#pragma unroll
+        for (int j = 0; j < (int)kNearSlots; j++) {
+            const uint32_t nj = __shfl(nb, first + j);
+            q[j] = nj ? __shfl(b0, first + j) + (uint32_t)(((uint64_t)(sub >> 2) * nj) >> 2) : a0;
+            pb[j] = load_pt<D>(P.spts, q[j]);
+            core[j] = nj && P.core[q[j]];
+        }
+        uint32_t hits = 0;               // lane j: slot j has a pair within eps
+#pragma unroll
+        for (int j = 0; j < (int)kNearSlots; j++) {
+            lt++;
+            const uint64_t m = __ballot(core[j] && within<D, WIDE>(pa, pb[j], geo.eps2));
+            if (sub == (uint32_t)j) hits = (uint32_t)(m >> first) & ((1u << kMergeLanes) - 1u);
+        }
+        if (hits) uf_union<true>(P.parent, A, B);
     }
     flush_tests(P, kTestsMerge, lt);
 }
