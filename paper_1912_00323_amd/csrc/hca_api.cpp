@@ -326,14 +326,13 @@ bool env_reps()
 
 constexpr uint64_t kFineStencilMax = 1024;     // default: search cube by cube up to this many offsets
 
-bool plan_geometry(double eps, int d, Geometry *g, bool with_offsets)
+bool plan_geometry(double eps, int d, Geometry *g, bool with_offsets, int mode = env_mode())
 {
     if (!exact_eps2(eps, &g->eps2)) return false;
     const uint64_t e2 = (uint64_t)g->eps2;
     g->side = std::max<int64_t>(1, (int64_t)isqrt_u64(e2 / (uint64_t)d));
     g->radius = offset_radius(g->side, g->eps2);
     enumerate_offsets(d, g->radius, g->side, g->eps2, 1ull << 24, nullptr, &g->stencil);
-    const int mode = env_mode();
     const int64_t E = (int64_t)isqrt_u64(e2);
     const uint32_t m_group = (uint32_t)std::max<int64_t>(1, (E + g->side - 1) / g->side);
     bool cube = g->stencil >= 0 && (uint64_t)g->stencil <= kFineStencilMax;
@@ -438,6 +437,12 @@ struct hca_ctx {
     int geo_d = 0;
     int geo_mode = -1;
     bool geo_reps = true;
+    // the search-group geometry of a large sparse call of four axes
+    bool ggeo_valid = false;
+    int64_t ggeo_eps2 = 0;
+    Geometry ggeo;
+    void *ggeo_dev = nullptr;
+    size_t ggeo_dev_size = 0;
     Geometry geo;
     std::string err;
     bool exact = true;                // false: merge on representatives alone
@@ -1161,6 +1166,53 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
     return HCA_OK;
 }
 
+// Three axes, cubes: data whose box holds few cubes per point find their
+// neighbours in the direct table sooner than in lists, whose five launches a
+// small call does not win back: at most 16 cubes per point under 100k points
+// (calls 1.2 to 1.4 times as fast), at most 4 under 2^18 (1.14); larger calls
+// are slower without lists (0.8).
+bool few_cubes(const Plan &P, uint32_t n, int d)
+{
+    if (d != 3 || n >= (1u << 18)) return false;
+    double cubes = 1;
+    for (int k = 0; k < d; k++) cubes *= (double)P.gmax[k] + 1.0;
+    return cubes <= (n < 100000 ? 16.0 : 4.0) * n;
+}
+
+// A geometry's offset and direction tables to the device.
+hca_status upload_geometry(hca_ctx *ctx, const Geometry &g, int d, void **dev, size_t *dev_size)
+{
+    const size_t n_off = g.off.size() / d;
+    const size_t bytes = align256(g.off.size()) + 2 * align256(n_off * sizeof(uint16_t));
+    hca_status st = ensure(ctx, dev, dev_size, bytes, "offset table");
+    if (st) return st;
+    char *gd = (char *)*dev;
+    HCA_HIP(hipMemcpy(gd, g.off.data(), g.off.size(), hipMemcpyHostToDevice), "offsets");
+    HCA_HIP(hipMemcpy(gd + align256(g.off.size()), g.dir_fwd.data(), n_off * 2, hipMemcpyHostToDevice), "directions");
+    HCA_HIP(hipMemcpy(gd + align256(g.off.size()) + align256(n_off * 2), g.dir_bwd.data(), n_off * 2,
+                      hipMemcpyHostToDevice), "directions");
+    return HCA_OK;
+}
+
+// Four axes, from 2^18 points on: groups of several cubes in place of cubes
+// where the box holds at least 256 cubes per point, i.e. where cubes hold few
+// points and their lists are long (calls on such data are 1.4 to 1.5 times
+// as fast, 5 % at 64 to 256 cubes per point, below that slower, and so are
+// smaller calls).  Calls that ask for counters, representatives or a search
+// mode, and data past 46340 units along two axes (see plan_prefix), keep the
+// cubes; so do keys that would not fit.
+bool group_search(const hca_ctx *ctx, const Geometry &g, uint32_t n, int d, const int64_t *mn, const int64_t *mx)
+{
+    if (d != 4 || g.m != 1 || n < (1u << 18) || !ctx->exact || ctx->fixed || ctx->geo_mode != 0) return false;
+    double cubes = 1;
+    int far = 0;
+    for (int k = 0; k < d; k++) {
+        cubes *= (double)((mx[k] - mn[k]) / g.side + 1);
+        far += mx[k] - mn[k] > 46340;
+    }
+    return cubes >= 256.0 * n && cubes < 0x1p48 && far < 2;
+}
+
 hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, double eps,
                int32_t min_pts, int32_t *labels, uint8_t *core_out, hca_stats *stats)
 {
@@ -1228,26 +1280,18 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
         ctx->geo_reps = reps;
     }
     if (!ctx->fixed && !ctx->geo_uploaded) {
-        const Geometry &g = ctx->geo;
-        const size_t n_off = g.off.size() / d;
-        const size_t bytes = align256(g.off.size()) + 2 * align256(n_off * sizeof(uint16_t));
-        hca_status st = ensure(ctx, &ctx->geo_dev, &ctx->geo_dev_size, bytes, "offset table");
+        hca_status st = upload_geometry(ctx, ctx->geo, d, &ctx->geo_dev, &ctx->geo_dev_size);
         if (st) return st;
-        char *gd = (char *)ctx->geo_dev;
-        HCA_HIP(hipMemcpy(gd, g.off.data(), g.off.size(), hipMemcpyHostToDevice), "offsets");
-        HCA_HIP(hipMemcpy(gd + align256(g.off.size()), g.dir_fwd.data(), n_off * 2,
-                          hipMemcpyHostToDevice), "directions");
-        HCA_HIP(hipMemcpy(gd + align256(g.off.size()) + align256(n_off * 2), g.dir_bwd.data(),
-                          n_off * 2, hipMemcpyHostToDevice), "directions");
         ctx->geo_uploaded = true;
     }
-    const Geometry &G = ctx->geo;
-    const uint32_t n_off = (uint32_t)(G.off.size() / d);
+    const Geometry *geo = &ctx->geo;
     char *geo_dev = (char *)ctx->geo_dev;
     if (ctx->fixed) {
         // the tables go to the front of the fixed area on every call (other
         // calls on this device may have overwritten it), staged through the
         // context's pinned buffer after the bounding-box region
+        const Geometry &G = *geo;
+        const size_t n_off = G.off.size() / d;
         const size_t dir_at = align256(G.off.size()), bytes = dir_at + 2 * align256((size_t)n_off * 2);
         if (bytes > kFixedGeoBytes || ctx->pinned_size < kPinnedBytes + bytes)
             return fail(ctx, HCA_E_RANGE, "offset tables too large for the no-allocation area");
@@ -1300,6 +1344,21 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
         }
     }
 
+    if (!stats && group_search(ctx, *geo, n, d, mn, mx)) {
+        if (!ctx->ggeo_valid || ctx->ggeo_eps2 != eps2) {
+            ctx->ggeo_valid = false;
+            plan_geometry(eps, d, &ctx->ggeo, true, 2);
+            st = upload_geometry(ctx, ctx->ggeo, d, &ctx->ggeo_dev, &ctx->ggeo_dev_size);
+            if (st) return st;
+            ctx->ggeo_valid = true;
+            ctx->ggeo_eps2 = eps2;
+        }
+        geo = &ctx->ggeo;
+        geo_dev = (char *)ctx->ggeo_dev;
+    }
+    const Geometry &G = *geo;
+    const uint32_t n_off = (uint32_t)(G.off.size() / d);
+
     // 2. key layout: group coordinates (dimension 0 most significant) above
     //    the in-group cube offsets
     Plan P;
@@ -1350,7 +1409,7 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
                                           "and representatives enabled");
         P.rep_only = 1;
     }
-    P.list_w = P.m == 1 ? cube_list_width(d, G.radius, n_off) : 0;
+    P.list_w = P.m == 1 && !(few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats) ? cube_list_width(d, G.radius, n_off) : 0;
     plan_core_lanes(P, G.radius);
     plan_linked(P);
     Sizes Z;
@@ -2157,6 +2216,7 @@ void hca_destroy(hca_ctx *ctx)
     if (ctx->io) (void)hipFree(ctx->io);
     if (ctx->aligned) (void)hipFree(ctx->aligned);
     if (ctx->geo_dev) (void)hipFree(ctx->geo_dev);
+    if (ctx->ggeo_dev) (void)hipFree(ctx->ggeo_dev);
     if (ctx->bws) (void)hipFree(ctx->bws);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->check_host) (void)hipHostFree(ctx->check_host);

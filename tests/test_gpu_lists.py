@@ -78,3 +78,18 @@ def test_cubes_joined_by_few_pairs(ctx, d, monkeypatch):  # noqa: F811
             pts = np.concatenate(sets)
             pts = pts[rng.permutation(len(pts))].astype(np.int32)
             test_gpu.check(ctx, pts, eps, 3, f"few pairs {size}")
+
+
+@pytest.mark.parametrize("d,n,eps,q", [(4, 1 << 18, 0.010, 14), (4, 1 << 18, 0.010, 16), (4, 300_001, 0.008, 12),
+                                       (3, 20_001, 0.022, 14), (3, 99_999, 0.03, 16), (3, 100_000, 0.03, 12),
+                                       (3, 200_000, 0.03, 14)])
+def test_search_rules_agree(ctx, d, n, eps, q, monkeypatch):  # noqa: F811
+    """Sizes and densities at which a call changes its search: the same labels
+    and core points as cube by cube over lists."""
+    import torch
+    pts = quantise(make_blobs(np.random.default_rng(n), n, d, 9, 0.02, 0.15), q)
+    x = torch.from_numpy(np.ascontiguousarray(pts, np.int32)).cuda()
+    got = [t.cpu().numpy() for t in ctx.cluster(x, eps * 2 ** q, 6, core=True)]
+    monkeypatch.setenv("HCA_SEARCH", "cube")
+    want = [t.cpu().numpy() for t in ctx.cluster(x, eps * 2 ** q, 6, core=True)]
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
