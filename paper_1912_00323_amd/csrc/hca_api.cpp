@@ -249,11 +249,13 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
                                                                        : 256u;
 }
 
-// Exact merging of cubes over neighbour lists goes by the neighbours that core
-// marking records, without representatives.
+// Exact merging of cubes goes by the neighbours that core marking records,
+// without representatives: over neighbour lists (three and four axes), and
+// over small stencils with the lane walk (one and two).
 void plan_linked(Plan &P)
 {
-    P.linked = P.m == 1 && P.list_w && P.d >= 3 && P.d <= 4 && !P.rep_only && env_record();
+    P.linked = P.m == 1 && !P.rep_only && env_record() &&
+               (P.d <= 2 ? P.core_lanes == 1 && P.n_off <= (uint32_t)kWave && P.n >= (3u << 19) : P.d <= 4 && P.list_w);
     if (P.linked) P.n_dir = 0;
 }
 

@@ -2198,16 +2198,52 @@ __device__ __forceinline__ void queue_exact(const Plan &P, bool exact, uint32_t 
 // writing, folding and reading 26 or 80 representatives for each was most of
 // the call: 4-D, 1M points, reps and merge 1199 us before.
 constexpr int kMergeLanes = 16;          // lanes per cube
-constexpr uint32_t kNearSlots = 8;       // listed cubes sampled per cube
 constexpr uint32_t kLanePairs = 16;      // point pairs that a lane tests by itself
 
 // Cubes of core points only against the first cubes of their lists: 16
 // sampled pairs each, a lane per pair.
+// The forward offsets of a small stencil (at most 64 offsets) in a wave's
+// table, nearest first; returns their number.  Cubes are numbered in key
+// order, so B > A exactly when the first non-zero component is positive.
+template <int D>
+__device__ __forceinline__ uint32_t forward_offsets(const Plan &P, uint32_t *s_fwd)
+{
+    const uint32_t l = lane_id();
+    bool fw = false;
+    if (l < P.n_off) {
+        const int8_t *o = P.off + (uint64_t)l * D;
+        int lead = 0;
+#pragma unroll
+        for (int e = 0; e < D; e++)
+            if (lead == 0) lead = o[e];
+        fw = lead > 0;
+    }
+    const uint64_t fm = __ballot(fw);
+    if (fw) s_fwd[__popcll(fm & __lanemask_lt())] = l;
+    __builtin_amdgcn_wave_barrier();
+    return (uint32_t)__popcll(fm);
+}
+
+// Sample s of 4 of a cube of `size` points: two at either end, so that a
+// cube's samples lie in one or two lines.
+__device__ __forceinline__ uint32_t near_sample(uint32_t s, uint32_t size)
+{
+    return min(s < 2 ? s : size - min(size, s - 1u), size - 1u);
+}
+
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_merge_near(Plan P)
 {
-    if (box_missed(P) || !P.nbr_cap || P.ctr->nbr_overflow) return;
+    if (box_missed(P)) return;
+    // the other cubes sampled; of a plane the two that share a side (more
+    // unions at once build long chains through large clusters: 16M points,
+    // four 194 us)
+    constexpr uint32_t kNear = D <= 2 ? 2 : 8;
+    __shared__ uint32_t s_fwd[kWavesPerBlock][kWave];
     const uint32_t l = lane_id(), sub = l % kMergeLanes, first = l - sub;
+    uint32_t nf = 0;
+    if constexpr (D <= 2) nf = forward_offsets<D>(P, s_fwd[wave_in_block()]);
+    else if (!P.nbr_cap || P.ctr->nbr_overflow) return;
     const uint32_t nc = ld_agent32(&P.ctr->n_cells);
     uint32_t lt = 0;
     const WaveRange hca_wr_ = wave_range(P.order);
@@ -2215,29 +2251,37 @@ __global__ __launch_bounds__(kBlock) void k_merge_near(Plan P)
         const uint32_t A = u * (kWave / kMergeLanes) + l / kMergeLanes;
         if (A >= nc) continue;
         const uint32_t a0 = P.cell_start[A], na = P.cell_start[A + 1] - a0;
-        const Geo<D> geo = cube_geo<D>(P, P.group_key[A]);
+        const uint64_t gkey = P.group_key[A];
+        const Geo<D> geo = cube_geo<D>(P, gkey);
         if (na < geo.min_pts) continue;
-        const Pt<D> pa = load_pt<D>(P.spts, a0 + (uint32_t)(((uint64_t)(sub & 3u) * na) >> 2));
+        const Pt<D> pa = load_pt<D>(P.spts, a0 + near_sample(sub & 3u, na));
         // a slot per lane: its cube and point range
         uint32_t B = kNone, b0 = 0, nb = 0;
-        if (sub < min(P.nbr_count[A], kNearSlots)) {
+        if constexpr (D <= 2) {
+            if (sub < min(nf, kNear)) {
+                const uint64_t nk = group_neighbour<D>(P, gkey, P.off + (uint64_t)s_fwd[wave_in_block()][sub] * D);
+                if (nk != ~0ull) B = group_lookup(P, nk);
+            }
+        } else if (sub < min(P.nbr_count[A], kNear)) {
             B = P.nbr[P.nbr_start[A] + sub];
+        }
+        if (B != kNone) {
             b0 = P.cell_start[B];
             nb = P.ncore[B] ? P.cell_start[B + 1] - b0 : 0u;
         }
-        uint32_t q[kNearSlots];
-        Pt<D> pb[kNearSlots];
-        bool core[kNearSlots];
+        uint32_t q[kNear];
+        Pt<D> pb[kNear];
+        bool core[kNear];
 #pragma unroll
-        for (int j = 0; j < (int)kNearSlots; j++) {
+        for (int j = 0; j < (int)kNear; j++) {
             const uint32_t nj = __shfl(nb, first + j);
-            q[j] = nj ? __shfl(b0, first + j) + (uint32_t)(((uint64_t)(sub >> 2) * nj) >> 2) : a0;
+            q[j] = nj ? __shfl(b0, first + j) + near_sample(sub >> 2, nj) : a0;
             pb[j] = load_pt<D>(P.spts, q[j]);
-            core[j] = nj && P.core[q[j]];
+            core[j] = nj && (nj >= geo.min_pts || P.core[q[j]]);
         }
         uint32_t hits = 0;               // lane j: slot j has a pair within eps
 #pragma unroll
-        for (int j = 0; j < (int)kNearSlots; j++) {
+        for (int j = 0; j < (int)kNear; j++) {
             lt++;
             const uint64_t m = __ballot(core[j] && within<D, WIDE>(pa, pb[j], geo.eps2));
             if (sub == (uint32_t)j) hits = (uint32_t)(m >> first) & ((1u << kMergeLanes) - 1u);
@@ -2245,6 +2289,27 @@ __global__ __launch_bounds__(kBlock) void k_merge_near(Plan P)
         if (hits) uf_union<true>(P.parent, A, B);
     }
     flush_tests(P, kTestsMerge, lt);
+}
+
+// Cubes A (points [a0, a0 + na)) and B by one lane, when they hold few pairs
+// of points: false, nothing done, when they hold more.
+template <int D, bool WIDE>
+__device__ __forceinline__ bool lane_pair(const Plan &P, uint32_t A, uint32_t B, uint32_t a0, uint32_t na, int64_t eps2,
+                                          uint32_t &lt)
+{
+    const uint32_t b0 = P.cell_start[B], nb = P.cell_start[B + 1] - b0;
+    if ((uint64_t)na * nb > kLanePairs) return false;
+    bool hit = false;
+    for (uint32_t ia = a0; ia < a0 + na && !hit; ia++) {
+        if (!P.core[ia]) continue;
+        const Pt<D> pa = load_pt<D>(P.spts, ia);
+        for (uint32_t ib = b0; ib < b0 + nb; ib++) {
+            lt++;
+            hit |= P.core[ib] && within<D, WIDE>(pa, load_pt<D>(P.spts, ib), eps2);
+        }
+    }
+    if (hit) uf_union<true>(P.parent, A, B);
+    return true;
 }
 
 // Every listed pair of core cubes that does not share a root yet: a few
@@ -2276,22 +2341,7 @@ __device__ __forceinline__ void merge_lists(const Plan &P, uint32_t &lt)
                 if (ld_parent_cached(P.parent + B) != rA && P.ncore[B] != 0)
                     exact = uf_find<true>(P.parent, A) != uf_find<true>(P.parent, B);
             }
-            if (exact) {
-                const uint32_t b0 = P.cell_start[B], nb = P.cell_start[B + 1] - b0;
-                if ((uint64_t)na * nb <= kLanePairs) {
-                    exact = false;
-                    bool hit = false;
-                    for (uint32_t ia = a0; ia < a0 + na && !hit; ia++) {
-                        if (!P.core[ia]) continue;
-                        const Pt<D> pa = load_pt<D>(P.spts, ia);
-                        for (uint32_t ib = b0; ib < b0 + nb; ib++) {
-                            lt++;
-                            hit |= P.core[ib] && within<D, WIDE>(pa, load_pt<D>(P.spts, ib), eps2);
-                        }
-                    }
-                    if (hit) uf_union<true>(P.parent, A, B);
-                }
-            }
+            if (exact) exact = !lane_pair<D, WIDE>(P, A, B, a0, na, eps2, lt);
             queue_exact<D, WIDE>(P, exact, A, B, lt);
         }
     }
@@ -2389,23 +2439,10 @@ __global__ __launch_bounds__(kBlock) void k_merge_cubes(Plan P)
     if (box_missed(P)) return;
     __shared__ uint32_t s_fwd[kWavesPerBlock][kWave];
     const uint32_t w = wave_in_block(), l = lane_id();
-    // forward offsets: cubes are numbered in key order, so B > A exactly when
-    // the first non-zero component of the offset is positive
-    bool fw = false;
-    if (l < P.n_off) {
-        const int8_t *o = P.off + (uint64_t)l * D;
-        int lead = 0;
-#pragma unroll
-        for (int e = 0; e < D; e++)
-            if (lead == 0) lead = o[e];
-        fw = lead > 0;
-    }
-    const uint64_t fm = __ballot(fw);
-    if (fw) s_fwd[w][__popcll(fm & __lanemask_lt())] = l;
-    __builtin_amdgcn_wave_barrier();
+    const uint32_t nfw = forward_offsets<D>(P, s_fwd[w]);
     // the forward offsets of this launch (nearest first): all, the first
     // merge_split, or the others
-    const uint32_t nfw = (uint32_t)__popcll(fm), cut = min(P.merge_split, nfw);
+    const uint32_t cut = min(P.merge_split, nfw);
     const uint32_t fa = P.merge_phase == 2 ? cut : 0u;
     const uint32_t nf = (P.merge_phase == 1 ? cut : nfw) - fa;
     if (nf == 0) return;
@@ -2447,6 +2484,42 @@ __global__ __launch_bounds__(kBlock) void k_merge_cubes(Plan P)
         }
         if (todo && !joined && !P.rep_only) todo = uf_find<true>(P.parent, A) != uf_find<true>(P.parent, B);
         queue_exact<D, WIDE>(P, todo && !joined && !P.rep_only, A, B, lt);
+    }
+    flush_tests(P, kTestsMerge, lt);
+}
+
+// One or two axes, exact merging without representatives: every (cube,
+// forward offset) whose two core cubes do not share a root after
+// k_link_listed and k_merge_near.
+template <int D, bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_merge_open(Plan P)
+{
+    if (box_missed(P)) return;
+    __shared__ uint32_t s_fwd[kWavesPerBlock][kWave];
+    const uint32_t w = wave_in_block(), l = lane_id(), nf = forward_offsets<D>(P, s_fwd[w]);
+    if (nf == 0) return;
+    const uint64_t pairs = (uint64_t)ld_agent32(&P.ctr->n_cells) * nf;
+    uint32_t lt = 0;
+    const WaveRange hca_wr_ = wave_range(P.order);
+    HCA_FOR_UNITS(wu, (uint32_t)((pairs + kWave - 1) / kWave)) {
+        const uint64_t u = (uint64_t)wu * kWave + l;
+        uint32_t A = kNone, B = kNone;
+        bool exact = false;
+        if (u < pairs) {
+            A = (uint32_t)(u / nf);
+            const uint32_t f = (uint32_t)(u - (uint64_t)A * nf);
+            if (P.ncore[A] != 0) {
+                const uint64_t gkey = P.group_key[A];
+                const uint64_t nk = group_neighbour<D>(P, gkey, P.off + (uint64_t)s_fwd[w][f] * D);
+                if (nk != ~0ull) B = group_lookup(P, nk);
+                if (B != kNone && ld_parent_cached(P.parent + A) != ld_parent_cached(P.parent + B) && P.ncore[B] != 0 &&
+                    uf_find<true>(P.parent, A) != uf_find<true>(P.parent, B)) {
+                    const uint32_t a0 = P.cell_start[A];
+                    exact = !lane_pair<D, WIDE>(P, A, B, a0, P.cell_start[A + 1] - a0, cube_geo<D>(P, gkey).eps2, lt);
+                }
+            }
+        }
+        queue_exact<D, WIDE>(P, exact, A, B, lt);
     }
     flush_tests(P, kTestsMerge, lt);
 }
@@ -3515,7 +3588,7 @@ void launch_core(const Plan &P, int blocks, hipStream_t s)
         case 5: HCA_CORE_LANES(2, true) break;
 #undef HCA_CORE_LANES
         }
-        hipLaunchKernelGGL(k_core_cubes, dim3(fb), dim3(kFlatBlock), 0, s, P);
+        if (!P.linked) hipLaunchKernelGGL(k_core_cubes, dim3(fb), dim3(kFlatBlock), 0, s, P);
         return;
     }
     if (P.m > 1 && P.core_list) {
@@ -3574,6 +3647,10 @@ void launch_merge(const Plan &P, int blocks, hipStream_t s)
         if (P.linked) {
             launch_link_recorded(P, s);
             switch (P.d * 2 + (P.wide ? 1 : 0)) {
+            case 2: hipLaunchKernelGGL((k_merge_near<1, false>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            case 3: hipLaunchKernelGGL((k_merge_near<1, true>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            case 4: hipLaunchKernelGGL((k_merge_near<2, false>), dim3(blocks), dim3(kBlock), 0, s, P); break;
+            case 5: hipLaunchKernelGGL((k_merge_near<2, true>), dim3(blocks), dim3(kBlock), 0, s, P); break;
             case 6: hipLaunchKernelGGL((k_merge_near<3, false>), dim3(blocks), dim3(kBlock), 0, s, P); break;
             case 7: hipLaunchKernelGGL((k_merge_near<3, true>), dim3(blocks), dim3(kBlock), 0, s, P); break;
             case 8: hipLaunchKernelGGL((k_merge_near<4, false>), dim3(blocks), dim3(kBlock), 0, s, P); break;
@@ -3585,7 +3662,14 @@ void launch_merge(const Plan &P, int blocks, hipStream_t s)
             Plan Q = P;
             Q.merge_phase = launches == 2 ? (uint32_t)r + 1u : 0u;
             if (r) hipLaunchKernelGGL(k_flatten, dim3(1024), dim3(kBlock), 0, s, Q);
-            if (P.core_list && P.core_lanes == 1) {
+            if (P.linked && P.d <= 2) {
+                switch (P.d * 2 + (P.wide ? 1 : 0)) {
+                case 2: hipLaunchKernelGGL((k_merge_open<1, false>), dim3(blocks), dim3(kBlock), 0, s, Q); break;
+                case 3: hipLaunchKernelGGL((k_merge_open<1, true>), dim3(blocks), dim3(kBlock), 0, s, Q); break;
+                case 4: hipLaunchKernelGGL((k_merge_open<2, false>), dim3(blocks), dim3(kBlock), 0, s, Q); break;
+                case 5: hipLaunchKernelGGL((k_merge_open<2, true>), dim3(blocks), dim3(kBlock), 0, s, Q); break;
+                }
+            } else if (P.core_list && P.core_lanes == 1) {
                 switch (P.d * 2 + (P.wide ? 1 : 0)) {
                 case 2: hipLaunchKernelGGL((k_merge_cubes<1, false>), dim3(blocks), dim3(kBlock), 0, s, Q); break;
                 case 3: hipLaunchKernelGGL((k_merge_cubes<1, true>), dim3(blocks), dim3(kBlock), 0, s, Q); break;

@@ -1332,54 +1332,65 @@ __global__ __launch_bounds__(kBlock) void k_hd_merge(Plan P)
     flush_tests(P, kTestsMerge, lt);
 }
 
-// The pairs recorded by core marking (more than 8 axes, or search groups of
-// more than one cube): each core point joins its cube with those of its
+// The pairs recorded by core marking: each core point joins its cube with those of its
 // recorded core neighbours (all within eps), no test needed.  The records,
 // then the flags and cubes of all of them, are loaded before the first
 // union, so their latencies overlap; the point's own root is carried from
 // one union to the next.
+__device__ __forceinline__ void link_point(const Plan &P, uint32_t q)
+{
+    if (!P.core[q]) return;
+    const uint32_t c = P.cell_of[q], nr = min((uint32_t)P.nrec[q], (uint32_t)kRec);
+    if (!nr) return;
+    uint32_t q2[kRec];
+    const uint4 *rp = reinterpret_cast<const uint4 *>(P.rec + (uint64_t)q * kRec);
+#pragma unroll
+    for (int i = 0; i < kRec / 4; i++) {
+        const uint4 v = rp[i];
+        q2[4 * i] = v.x;
+        q2[4 * i + 1] = v.y;
+        q2[4 * i + 2] = v.z;
+        q2[4 * i + 3] = v.w;
+    }
+    // cube of each recorded core neighbour (kNone: not core, or past nr,
+    // where the record holds no position)
+    uint32_t c2[kRec];
+#pragma unroll
+    for (int r = 0; r < kRec; r++) {
+        c2[r] = kNone;
+        if ((uint32_t)r < nr) {
+            const bool cp = P.core[q2[r]];
+            const uint32_t cc = P.cell_of[q2[r]];
+            c2[r] = cp ? cc : kNone;
+        }
+    }
+    uint32_t rc = kNone;
+#pragma unroll
+    for (int r = 0; r < kRec; r++) {
+        if (c2[r] == kNone || c2[r] == c) continue;
+        if (rc == kNone) rc = uf_find(P.parent, c);
+        // rc was c's root when found and stays an ancestor of c, so a
+        // neighbour under rc is already in c's cluster
+        const uint32_t r2 = uf_find(P.parent, c2[r]);
+        if (r2 == rc) continue;
+        uf_union(P.parent, rc, r2);
+        rc = uf_find(P.parent, rc);
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_link_recorded(Plan P)
 {
     if (box_missed(P)) return;
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < P.n; q += gridDim.x * kBlock) {
-        if (!P.core[q]) continue;
-        const uint32_t c = P.cell_of[q], nr = min((uint32_t)P.nrec[q], (uint32_t)kRec);
-        if (!nr) continue;
-        uint32_t q2[kRec];
-        const uint4 *rp = reinterpret_cast<const uint4 *>(P.rec + (uint64_t)q * kRec);
-#pragma unroll
-        for (int i = 0; i < kRec / 4; i++) {
-            const uint4 v = rp[i];
-            q2[4 * i] = v.x;
-            q2[4 * i + 1] = v.y;
-            q2[4 * i + 2] = v.z;
-            q2[4 * i + 3] = v.w;
-        }
-        // cube of each recorded core neighbour (kNone: not core, or past nr,
-        // where the record holds no position)
-        uint32_t c2[kRec];
-#pragma unroll
-        for (int r = 0; r < kRec; r++) {
-            c2[r] = kNone;
-            if ((uint32_t)r < nr) {
-                const bool cp = P.core[q2[r]];
-                const uint32_t cc = P.cell_of[q2[r]];
-                c2[r] = cp ? cc : kNone;
-            }
-        }
-        uint32_t rc = kNone;
-#pragma unroll
-        for (int r = 0; r < kRec; r++) {
-            if (c2[r] == kNone || c2[r] == c) continue;
-            if (rc == kNone) rc = uf_find(P.parent, c);
-            // rc was c's root when found and stays an ancestor of c, so a
-            // neighbour under rc is already in c's cluster
-            const uint32_t r2 = uf_find(P.parent, c2[r]);
-            if (r2 == rc) continue;
-            uf_union(P.parent, rc, r2);
-            rc = uf_find(P.parent, rc);
-        }
-    }
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < P.n; q += gridDim.x * kBlock) link_point(P, q);
+}
+
+// The same over the points of sparse cubes, where core marking has listed
+// them (the others have nothing recorded).
+__global__ __launch_bounds__(kBlock) void k_link_listed(Plan P)
+{
+    if (box_missed(P)) return;
+    const uint32_t ns = ld_agent32(&P.ctr->n_sparse);
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < ns; i += gridDim.x * kBlock) link_point(P, P.core_list[i]);
 }
 
 // Before the walk: whether all core cubes of each group share one root (a
@@ -1566,7 +1577,8 @@ __global__ __launch_bounds__(kBlock) void k_hd_border(Plan P)
 void launch_link_recorded(const Plan &P, hipStream_t s)
 {
     const int cb = (int)std::min<uint64_t>((P.n + kBlock - 1) / kBlock, 2048);
-    hipLaunchKernelGGL(k_link_recorded, dim3(cb), dim3(kBlock), 0, s, P);
+    if (P.core_list) hipLaunchKernelGGL(k_link_listed, dim3(cb), dim3(kBlock), 0, s, P);
+    else hipLaunchKernelGGL(k_link_recorded, dim3(cb), dim3(kBlock), 0, s, P);
 }
 
 void launch_hd_lists(const Plan &P, int blocks, hipStream_t s)

@@ -93,3 +93,18 @@ def test_search_rules_agree(ctx, d, n, eps, q, monkeypatch):  # noqa: F811
     monkeypatch.setenv("HCA_SEARCH", "cube")
     want = [t.cpu().numpy() for t in ctx.cluster(x, eps * 2 ** q, 6, core=True)]
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("d,n", [(1, 1_600_000), (2, 1_572_864), (2, 1_700_003)])
+def test_large_planes_without_representatives(ctx, d, n, monkeypatch):  # noqa: F811
+    """Large sets of one and two axes merge from recorded neighbours and
+    sampled pairs: the same labels as with representatives (no records)."""
+    import torch
+    pts = quantise(make_blobs(np.random.default_rng(n), n, d, 40, 0.01, 0.1), 16)
+    x = torch.from_numpy(np.ascontiguousarray(pts, np.int32)).cuda()
+    for eps, mp in ((0.002, 8), (0.0005, 40)):
+        got = ctx.cluster(x, eps * 2 ** 16, mp)
+        monkeypatch.setenv("HCA_RECORD", "0")
+        want = ctx.cluster(x, eps * 2 ** 16, mp)
+        monkeypatch.delenv("HCA_RECORD")
+        assert torch.equal(got, want), (d, n, eps)
