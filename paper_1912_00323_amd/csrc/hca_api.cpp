@@ -824,7 +824,7 @@ void launch_sequence(hca_ctx *ctx, Plan &P, const Sizes &Z, char *base = nullptr
     launch_border(P, wb, s);
     mark(ctx, HCA_PHASE_BORDER, true);
     mark(ctx, HCA_PHASE_LABELS, false);
-    launch_labels(P, P.scan_status + Z.scan_tiles + 32, P.ctr->scan_tickets + 1, s);
+    launch_labels(P, P.scan_status + Z.scan_tiles + 32, P.ctr->scan_tickets + 1, B.keys_a, B.keys_b, s);
     mark(ctx, HCA_PHASE_LABELS, true);
 }
 
@@ -913,7 +913,7 @@ void launch_hd_rest(hca_ctx *ctx, Plan &P, const Sizes &Z)
     launch_hd_border(P, Z.wb, s);
     mark(ctx, HCA_PHASE_BORDER, true);
     mark(ctx, HCA_PHASE_LABELS, false);
-    launch_labels(P, P.scan_status + Z.scan_tiles + 32, P.ctr->scan_tickets + 1, s);
+    launch_labels(P, P.scan_status + Z.scan_tiles + 32, P.ctr->scan_tickets + 1, nullptr, nullptr, s);
     mark(ctx, HCA_PHASE_LABELS, true);
 }
 

@@ -3455,38 +3455,123 @@ __global__ __launch_bounds__(kBlock) void k_label_cubes(Plan P)
     }
 }
 
-// Every point takes its cube's label (core) or its owner root's label (border).
+// Label and core flag of the point at sorted position a.
+__device__ __forceinline__ int32_t point_label(const Plan &P, uint32_t a, bool core)
+{
+    const uint32_t cube = core ? P.cell_of[a] : P.owner[a];
+    return cube == kNone ? -1 : P.label_of[cube];
+}
+
+// Core and noise points of a block: one atomic per counter, on one of
+// kWorkRegions lines.
+__device__ __forceinline__ void block_tally(const Plan &P, uint32_t n_core, uint32_t n_noise, uint32_t (*s_cnt)[16])
+{
+    const uint32_t waves = blockDim.x / kWave;
+    n_core = wave_sum(n_core);
+    n_noise = wave_sum(n_noise);
+    if (lane_id() == 0) {
+        s_cnt[0][threadIdx.x / kWave] = n_core;
+        s_cnt[1][threadIdx.x / kWave] = n_noise;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t c = 0, z = 0;
+        for (uint32_t i = 0; i < waves; i++) { c += s_cnt[0][i]; z += s_cnt[1][i]; }
+        const uint32_t r = (blockIdx.x % kWorkRegions) * kCounterStride;
+        if (c) atomicAdd(&P.ctr->tally[0][r], c);
+        if (z) atomicAdd(&P.ctr->tally[1][r], z);
+    }
+}
+
+// Millions of labels written to their input positions straight from sorted
+// order are as many stores of four bytes to lines of their own (16M points:
+// 368 us for 64 MB).  From kLabelSplit points on they go in two steps, so that
+// all stores to memory are runs: each block sorts a tile of labels in LDS by
+// the range of 2^15 input positions and appends the runs to the ranges'
+// lists; then a block per range puts its list in order in LDS and writes it.
+// (With 64 ranges filled by scattered stores inside an XCD's L2 the second
+// step alone took 267 us.)
+constexpr int kLabelBlock = 1024, kLabelItems = 16, kLabelTile = kLabelBlock * kLabelItems;
+
+__global__ __launch_bounds__(kLabelBlock) void k_label_bin(Plan P, uint16_t *__restrict__ idx, int32_t *__restrict__ val)
+{
+    if (box_missed(P)) return;
+    __shared__ uint32_t s_n[kLabelRanges], s_pre[kLabelRanges], s_to[kLabelRanges], s_red[kLabelBlock / kWave];
+    __shared__ uint32_t s_idx[kLabelTile];
+    __shared__ int32_t s_val[kLabelTile];
+    __shared__ uint32_t s_cnt[2][16];
+    const uint32_t t = threadIdx.x, a0 = blockIdx.x * kLabelTile, m = min((uint32_t)kLabelTile, P.n - a0);
+    s_n[t] = 0;
+    __syncthreads();
+    uint32_t at[kLabelItems], to[kLabelItems], n_core = 0, n_noise = 0;
+    int32_t lab[kLabelItems];                   // twice the label, plus one for a core point
+#pragma unroll
+    for (int j = 0; j < kLabelItems; j++) {
+        const uint32_t a = a0 + min((uint32_t)j * kLabelBlock + t, m - 1u);
+        const bool core = P.core[a];
+        to[j] = P.sidx[a];
+        const int32_t label = point_label(P, a, core);
+        lab[j] = 2 * label + (core ? 1 : 0);
+        if ((uint32_t)j * kLabelBlock + t < m) {
+            n_core += core;
+            n_noise += label < 0;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kLabelItems; j++)
+        if ((uint32_t)j * kLabelBlock + t < m) at[j] = atomicAdd(&s_n[to[j] >> kLabelShift], 1u);
+    __syncthreads();
+    const uint32_t c = s_n[t];
+    uint32_t all;
+    const uint32_t before = block_exclusive_scan<uint32_t, kLabelBlock / kWave>(c, s_red, &all);
+    s_pre[t] = before;
+    // (list position of the tile's first entry of range t, less its place in the tile)
+    s_to[t] = (t << kLabelShift) + (c ? atomicAdd(&P.ctr->label_at[t], c) : 0u) - before;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kLabelItems; j++) {
+        if ((uint32_t)j * kLabelBlock + t >= m) continue;
+        const uint32_t k = s_pre[to[j] >> kLabelShift] + at[j];
+        s_idx[k] = to[j];
+        s_val[k] = lab[j];
+    }
+    __syncthreads();
+    for (uint32_t k = t; k < m; k += kLabelBlock) {
+        const uint32_t i = s_idx[k], pos = s_to[i >> kLabelShift] + k;
+        idx[pos] = (uint16_t)(i & ((1u << kLabelShift) - 1u));
+        val[pos] = s_val[k];
+    }
+    if (P.want_stats) block_tally(P, n_core, n_noise, s_cnt);
+}
+
+__global__ __launch_bounds__(kLabelBlock) void k_label_fill(Plan P, const uint16_t *__restrict__ idx,
+                                                            const int32_t *__restrict__ val)
+{
+    if (box_missed(P)) return;
+    __shared__ int32_t s_val[1 << kLabelShift];
+    const uint32_t r0 = blockIdx.x << kLabelShift, m = min(1u << kLabelShift, P.n - r0);
+    for (uint32_t k = threadIdx.x; k < m; k += kLabelBlock) s_val[idx[r0 + k]] = val[r0 + k];
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < m; k += kLabelBlock) P.labels[r0 + k] = s_val[k] >> 1;
+    if (P.core_out)
+        for (uint32_t k = threadIdx.x; k < m; k += kLabelBlock) P.core_out[r0 + k] = (uint8_t)(s_val[k] & 1);
+}
+
 __global__ __launch_bounds__(kBlock) void k_label_write(Plan P)
 {
     if (box_missed(P)) return;
-    __shared__ uint32_t s_cnt[2][kWavesPerBlock];
+    __shared__ uint32_t s_cnt[2][16];
     uint32_t n_core = 0, n_noise = 0;
     for (uint32_t a = blockIdx.x * kBlock + threadIdx.x; a < P.n; a += gridDim.x * kBlock) {
         const bool core = P.core[a];
-        const uint32_t cube = core ? P.cell_of[a] : P.owner[a];
         const uint32_t i = P.sidx[a];
-        const int32_t label = cube == kNone ? -1 : P.label_of[cube];
+        const int32_t label = point_label(P, a, core);
         P.labels[i] = label;
         if (P.core_out) P.core_out[i] = core;
         n_core += core;
         n_noise += label < 0;
     }
-    if (!P.want_stats) return;
-    // one atomic per block and counter, on one of kWorkRegions lines
-    n_core = wave_sum(n_core);
-    n_noise = wave_sum(n_noise);
-    if (lane_id() == 0) {
-        s_cnt[0][wave_in_block()] = n_core;
-        s_cnt[1][wave_in_block()] = n_noise;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t c = 0, z = 0;
-        for (int i = 0; i < kWavesPerBlock; i++) { c += s_cnt[0][i]; z += s_cnt[1][i]; }
-        const uint32_t r = (blockIdx.x % kWorkRegions) * kCounterStride;
-        if (c) atomicAdd(&P.ctr->tally[0][r], c);
-        if (z) atomicAdd(&P.ctr->tally[1][r], z);
-    }
+    if (P.want_stats) block_tally(P, n_core, n_noise, s_cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -3713,16 +3798,23 @@ void launch_border(const Plan &P, int blocks, hipStream_t s)
     else HCA_DISPATCH_DW(k_border, P, blocks, s);
 }
 
-void launch_labels(const Plan &P, uint64_t *status, uint32_t *ticket, hipStream_t s)
+void launch_labels(const Plan &P, uint64_t *status, uint32_t *ticket, void *tmp_a, void *tmp_b, hipStream_t s)
 {
     const int cb = (int)std::min<uint64_t>((P.n + kBlock - 1) / kBlock, 1024);
     hipLaunchKernelGGL(k_label_marks, dim3(cb), dim3(kBlock), 0, s, P);
     const uint32_t nw = (P.n + 31u) >> 5;
-    const uint32_t tiles = (nw + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_label_scan, dim3(tiles), dim3(kBlock), 0, s, P, status, ticket);
+    const uint32_t scan_tiles = (nw + kScanTile - 1) / kScanTile;
+    hipLaunchKernelGGL(k_label_scan, dim3(scan_tiles), dim3(kBlock), 0, s, P, status, ticket);
     if (P.nseg)
         hipLaunchKernelGGL(k_seg_label_base, dim3((P.nseg + kBlock - 1) / kBlock), dim3(kBlock), 0, s, P);
     hipLaunchKernelGGL(k_label_cubes, dim3(cb), dim3(kBlock), 0, s, P);
+    if (tmp_a && P.n >= kLabelSplit && P.n <= kLabelRanges << kLabelShift) {
+        const uint32_t tiles = (P.n + kLabelTile - 1) / kLabelTile, ranges = (P.n - 1) / (1u << kLabelShift) + 1;
+        hipLaunchKernelGGL(k_label_bin, dim3(tiles), dim3(kLabelBlock), 0, s, P, (uint16_t *)tmp_a, (int32_t *)tmp_b);
+        hipLaunchKernelGGL(k_label_fill, dim3(ranges), dim3(kLabelBlock), 0, s, P, (const uint16_t *)tmp_a,
+                           (const int32_t *)tmp_b);
+        return;
+    }
     const int blocks = (int)std::min<uint64_t>((P.n + kBlock - 1) / kBlock, 4096);
     hipLaunchKernelGGL(k_label_write, dim3(blocks), dim3(kBlock), 0, s, P);
 }

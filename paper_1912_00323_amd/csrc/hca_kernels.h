@@ -38,7 +38,8 @@ void launch_merge_intra(const Plan &P, int blocks, hipStream_t s);
 void launch_merge(const Plan &P, int blocks, hipStream_t s);
 void launch_compress(const Plan &P, int blocks, hipStream_t s);
 void launch_border(const Plan &P, int blocks, hipStream_t s);
-void launch_labels(const Plan &P, uint64_t *status, uint32_t *ticket, hipStream_t s);
+// (tmp_a, tmp_b: n words each, free by then, or null)
+void launch_labels(const Plan &P, uint64_t *status, uint32_t *ticket, void *tmp_a, void *tmp_b, hipStream_t s);
 
 // more than kMaxDim axes (P.hd): bounding box partials [blocks][2][d], sort of
 // the keys with the rows gathered afterwards, neighbour lists, core points,

@@ -9,6 +9,10 @@ namespace hca {
 
 constexpr int kMaxDim = 8;                     // axes of the packed cube key
 constexpr int kMaxDimHigh = 64;                // axes of a point (more than 8: hashed cubes)
+constexpr uint32_t kLabelShift = 15;          // labels are binned by ranges of 2^15 input positions,
+constexpr uint32_t kLabelRanges = 1024;       // at most so many,
+constexpr uint32_t kLabelSplit = 3u << 20;    // from so many points on (labels phase, us, written at once and binned:
+                                              // 2M points 45 and 61, 4M 74 and 64, 8M 191 and 103, 16M 389 and 190)
 constexpr int kRec = 16;                       // neighbours recorded per point by core marking
 // More than kMaxDim axes: candidates a point of the first core pass looks at
 // before it is left to the next pass; the host may lower it per call.
@@ -100,6 +104,7 @@ struct Counters {
     // kWorkRegions lines so that thousands of blocks do not all add to one
     // address
     uint32_t tally[2][kWorkRegions * kCounterStride];
+    uint32_t label_at[kLabelRanges];    // labels in the list of each range of input positions
 };
 
 enum { kTestsCore = 0, kTestsMerge = 1, kTestsBorder = 2, kTestsIntra = 3 };

@@ -108,3 +108,32 @@ def test_large_planes_without_representatives(ctx, d, n, monkeypatch):  # noqa: 
         want = ctx.cluster(x, eps * 2 ** 16, mp)
         monkeypatch.delenv("HCA_RECORD")
         assert torch.equal(got, want), (d, n, eps)
+
+
+@pytest.mark.parametrize("n", [(3 << 20) - 1, 3 << 20, (3 << 20) + 1, 3_300_000])
+def test_labels_of_large_sets(ctx, n):  # noqa: F811
+    """Labels and core flags binned by input position: they follow the points
+    into another order, clusters numbered by their first points."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.rand(n, 2, device="cuda", generator=gen)
+    x[: n // 2] = (x[: n // 2] * 40).floor() / 40 + 0.004 * torch.randn(n // 2, 2, device="cuda", generator=gen)
+    x = (x * 2 ** 15).to(torch.int32).contiguous()
+    order = torch.randperm(n, device="cuda", generator=gen)
+    eps, mp = 20.0, 12
+    lab, core = ctx.cluster(x, eps, mp, core=True)
+    lab2, core2 = ctx.cluster(x[order].contiguous(), eps, mp, core=True)
+    assert torch.equal(core[order], core2)
+    # one label per label where core points are concerned (a border point may
+    # have cores of two clusters in reach, and goes to the first)
+    c = core2.bool()
+    a, b = lab[order][c].long(), lab2[c].long()
+    assert int(a.min()) == 0 and int(b.min()) == 0 and int(a.max()) == int(b.max())
+    pairs = torch.unique(torch.stack([a, b], 1), dim=0)
+    assert len(pairs) == int(a.max()) + 1 == len(torch.unique(pairs[:, 1]))
+    assert torch.equal(lab[order] < 0, lab2 < 0)
+    # numbered by first member
+    members = lab >= 0
+    first = torch.full((int(lab.max()) + 1,), n, device="cuda").scatter_reduce(
+        0, lab[members].long(), torch.arange(n, device="cuda")[members], "amin")
+    assert bool((first[1:] > first[:-1]).all())
