@@ -34,21 +34,22 @@ ALU_PHASES = {"core": "tests_core", "intra": "tests_intra", "merge": "tests_merg
               "border": "tests_border"}
 PHASE_KERNELS = {
     "bbox": ["k_bbox", "k_bbox_check"], "sort": ["k_keys_hist", "k_onesweep"], "cells": ["k_cells", "k_table_clear", "k_table"],
-    "lists": ["k_group_box", "k_prefix_ranges", "k_nbr_lists", "k_nbr_bscan", "k_nbr_back"],
-    "core": ["k_core", "k_core_chunks", "k_core_flat", "k_core_lanes", "k_core_deferred", "k_core_cubes"],
+    "lists": ["k_group_prep", "k_group_box", "k_nbr_lists", "k_nbr_bscan", "k_nbr_back"],
+    "core": ["k_core", "k_core_chunks", "k_core_flat", "k_core_lanes", "k_core_deferred", "k_core_list_lanes",
+             "k_core_list_deferred", "k_core_group_lanes", "k_core_group_deferred", "k_core_cubes"],
     "reps": ["k_reps_init", "k_reps", "k_reps_small", "k_reps_big"],
-    "intra": ["k_link_recorded", "k_core_box", "k_merge_tiles", "k_merge_big", "k_merge_unify"],
-    "merge": ["k_merge_rep", "k_merge_cubes", "k_merge_exact", "k_merge_inter", "k_merge_pairs", "k_flatten",
-              "k_compress"],
+    "intra": ["k_link_recorded", "k_link_listed", "k_core_box", "k_merge_tiles", "k_merge_big", "k_merge_unify"],
+    "merge": ["k_merge_near", "k_merge_open", "k_merge_rep", "k_merge_cubes", "k_merge_exact", "k_merge_inter",
+              "k_merge_pairs", "k_flatten", "k_compress"],
     "border": ["k_border", "k_border_chunks", "k_border_rec", "k_border_list", "k_border_walk_list"],
-    "labels": ["k_label_marks", "k_label_scan", "k_label_cubes", "k_label_write"],
+    "labels": ["k_label_marks", "k_label_scan", "k_label_cubes", "k_label_write", "k_label_bin", "k_label_fill"],
 }
 # more than 8 axes: the kernels of each phase
 PHASE_KERNELS_HIGH = {
     "bbox": ["k_hd_bbox"], "sort": ["k_hd_keys_hist", "k_onesweep", "k_hd_gather"],
-    "cells": ["k_cells", "k_table"], "lists": ["k_hd_group_box", "k_hd_lists", "k_nbr_bscan", "k_nbr_back"],
-    "core": ["k_hd_core", "k_hd_core_rest", "k_hd_gcore"],
-    "merge": ["k_link_recorded", "k_hd_unify", "k_hd_merge", "k_compress"],
+    "cells": ["k_cells", "k_table"], "lists": ["k_hd_group_init", "k_hd_group_box", "k_hd_lists", "k_nbr_bscan", "k_nbr_back"],
+    "core": ["k_hd_planes", "k_hd_runs", "k_hd_core_tiles", "k_hd_left", "k_hd_core", "k_hd_core_rest", "k_hd_gcore"],
+    "merge": ["k_link_recorded", "k_flatten", "k_hd_unify", "k_hd_need", "k_hd_merge", "k_compress"],
     "border": ["k_hd_noncore_list", "k_hd_border"],
     "labels": PHASE_KERNELS["labels"],
 }

@@ -87,8 +87,8 @@ typedef struct {
     int64_t n_core_points;
     int64_t n_clusters;
     int64_t n_noise;
-    int64_t exact_pairs;      /* cube pairs (one cube per group) or pairs of not yet unified
-                               * groups (m > 1) queued for the exact all-pairs test */
+    int64_t exact_pairs;      /* cube pairs (one cube per group), or chunks of 64 points of a
+                               * group against another (m > 1), queued for the exact test */
     int32_t key_bits;         /* bits of the packed cube key */
     int32_t sort_passes;      /* radix passes of the cube-key sort */
     int32_t group;            /* cubes per group side used */

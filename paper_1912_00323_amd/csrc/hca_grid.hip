@@ -580,8 +580,8 @@ __device__ __forceinline__ uint32_t forward_offset(uint32_t f, uint32_t pa, uint
     return o;
 }
 
-// Can the group box at b (lo, hi) hold a point farther than eps from the box
-// q?  32-bit when the host has shown that every tested pair's squared
+// Is every point of the group box ob farther than eps from the box qb?  32-bit
+// when the host has shown that every tested pair's squared
 // distance fits: that bound covers pairs within the stencil's reach, but a
 // prefix range also meets groups far beyond it, so each gap is clamped to
 // 46341 (whose square already exceeds any int32 eps^2) and the sum saturates
@@ -783,7 +783,8 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
         if (threadIdx.x < nf) {
             for (uint32_t f = 0; f < nf; f++) rank += s_norm[f] < norm || (s_norm[f] == norm && f < threadIdx.x);
             int64_t kd = 0;
-            for (uint32_t e = 0; e < P.paxes; e++) kd += (int64_t)(int8_t)(off >> (8 * e)) * (int64_t)(1ull << P.goff[e]);
+            for (uint32_t e = 0; e < P.paxes; e++)
+                kd += (int64_t)(int8_t)(off >> (8 * e)) * (int64_t)(1ull << P.goff[e]);
             s_off[rank] = off;
             s_kd[rank] = kd;
         }
@@ -791,118 +792,118 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
     }
     const DynRange dr_ = dyn_range(P.ctr->dyn[kDynLists], P.order);
     HCA_FOR_UNITS_DYN(u, (ng + pack - 1) / pack, dr_) {
-      uint32_t left = 1;
-      if (P.pstart)
-          left = list_by_prefix<D>(P, u * pack, ng, nf, pack, scan_max, s_off, s_kd, s_pre[w], s_rs[w], s_sub[w],
-                                   s_box[w], s_eps2[w], at, end, overflow);
-      while (left) {
-        const uint32_t g = u * pack + (__ffs(left) - 1);
-        left &= left - 1;
-        const uint64_t gkey = P.group_key[g];
-        const Geo<D> geo = cube_geo<D>(P, gkey);
-        const QBox<D> qb = load_gbox<D>(P, g);
-        // both halves' gap sums, sorted ascending, with their signs
-        for (int i = l; i < NA; i += kWave) s_in[w][i] = half_gap2<D, DA>(P, gkey, 0, i, qb, geo);
-        __builtin_amdgcn_wave_barrier();
-        bitonic_sort(s_in[w], NA, s_sa[w], s_ia[w]);
-        __builtin_amdgcn_wave_barrier();
-        for (int j = l; j < NB; j += kWave) s_in[w][j] = half_gap2<D, DB>(P, gkey, DA, j, qb, geo);
-        __builtin_amdgcn_wave_barrier();
-        bitonic_sort(s_in[w], NB, s_sb[w], s_ib[w]);
-        __builtin_amdgcn_wave_barrier();
-        for (int i = l; i < NA; i += kWave) s_ga[w][i] = half_sign<DA>(P, s_ia[w][i]);
-        for (int j = l; j < NB; j += kWave) s_gb[w][j] = half_sign<DB>(P, s_ib[w][j]);
-        // valid j per i (a prefix of the sorted second half; none when the
-        // first half points backwards), then their prefix
-        uint32_t tot = 0;
-        for (int i0 = 0; i0 < NA; i0 += kWave) {
-            const int i = i0 + (int)l;
-            uint32_t c = 0;
-            if (i < NA && s_sa[w][i] != INT64_MAX && s_ga[w][i] >= 0) {
-                const int64_t lim = geo.eps2 - s_sa[w][i];
-                int lo = 0, hi = NB;                      // first j with s_sb > lim
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_sb[w][mid] <= lim) lo = mid + 1; else hi = mid;
-                }
-                c = (uint32_t)lo;
-            }
-            const uint32_t inc = wave_inclusive_scan(c);
-            if (i < NA) s_pre[w][i] = tot + inc - c;
-            tot += lane_value(inc, kWave - 1);
-        }
-        if (l == 0) s_pre[w][NA] = tot;
-        // key offsets of both halves in sorted order
-        for (int i = l; i < NA; i += kWave) s_ka[w][i] = half_key_delta<DA>(P, 0, s_ia[w][i]);
-        for (int j = l; j < NB; j += kWave) s_kb[w][j] = half_key_delta<DB>(P, DA, s_ib[w][j]);
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t start = at;
-        bool fits = true;
-        for (uint32_t t0 = 0; t0 < tot; t0 += kWave * kListBatch) {
-            uint64_t nk[kListBatch];
-            uint32_t G[kListBatch];
-#pragma unroll
-            for (int b = 0; b < kListBatch; b++) {
-                const uint32_t t = t0 + b * kWave + l;
-                nk[b] = ~0ull;
-                if (t < tot) {
-                    int lo = 0, hi = NA;                  // last i with s_pre[i] <= t
-                    while (hi - lo > 1) {
+        uint32_t left = 1;
+        if (P.pstart)
+            left = list_by_prefix<D>(P, u * pack, ng, nf, pack, scan_max, s_off, s_kd, s_pre[w], s_rs[w], s_sub[w],
+                                     s_box[w], s_eps2[w], at, end, overflow);
+        while (left) {
+            const uint32_t g = u * pack + (__ffs(left) - 1);
+            left &= left - 1;
+            const uint64_t gkey = P.group_key[g];
+            const Geo<D> geo = cube_geo<D>(P, gkey);
+            const QBox<D> qb = load_gbox<D>(P, g);
+            // both halves' gap sums, sorted ascending, with their signs
+            for (int i = l; i < NA; i += kWave) s_in[w][i] = half_gap2<D, DA>(P, gkey, 0, i, qb, geo);
+            __builtin_amdgcn_wave_barrier();
+            bitonic_sort(s_in[w], NA, s_sa[w], s_ia[w]);
+            __builtin_amdgcn_wave_barrier();
+            for (int j = l; j < NB; j += kWave) s_in[w][j] = half_gap2<D, DB>(P, gkey, DA, j, qb, geo);
+            __builtin_amdgcn_wave_barrier();
+            bitonic_sort(s_in[w], NB, s_sb[w], s_ib[w]);
+            __builtin_amdgcn_wave_barrier();
+            for (int i = l; i < NA; i += kWave) s_ga[w][i] = half_sign<DA>(P, s_ia[w][i]);
+            for (int j = l; j < NB; j += kWave) s_gb[w][j] = half_sign<DB>(P, s_ib[w][j]);
+            // valid j per i (a prefix of the sorted second half; none when the
+            // first half points backwards), then their prefix
+            uint32_t tot = 0;
+            for (int i0 = 0; i0 < NA; i0 += kWave) {
+                const int i = i0 + (int)l;
+                uint32_t c = 0;
+                if (i < NA && s_sa[w][i] != INT64_MAX && s_ga[w][i] >= 0) {
+                    const int64_t lim = geo.eps2 - s_sa[w][i];
+                    int lo = 0, hi = NB;                      // first j with s_sb > lim
+                    while (lo < hi) {
                         const int mid = (lo + hi) >> 1;
-                        if (s_pre[w][mid] <= t) lo = mid; else hi = mid;
+                        if (s_sb[w][mid] <= lim) lo = mid + 1; else hi = mid;
                     }
-                    const uint32_t j = t - s_pre[w][lo];
-                    // first half zero: the second half must point forwards
-                    if (s_ga[w][lo] > 0 || s_gb[w][j] > 0) nk[b] = gkey + (uint64_t)(s_ka[w][lo] + s_kb[w][j]);
+                    c = (uint32_t)lo;
+                }
+                const uint32_t inc = wave_inclusive_scan(c);
+                if (i < NA) s_pre[w][i] = tot + inc - c;
+                tot += lane_value(inc, kWave - 1);
+            }
+            if (l == 0) s_pre[w][NA] = tot;
+            // key offsets of both halves in sorted order
+            for (int i = l; i < NA; i += kWave) s_ka[w][i] = half_key_delta<DA>(P, 0, s_ia[w][i]);
+            for (int j = l; j < NB; j += kWave) s_kb[w][j] = half_key_delta<DB>(P, DA, s_ib[w][j]);
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t start = at;
+            bool fits = true;
+            for (uint32_t t0 = 0; t0 < tot; t0 += kWave * kListBatch) {
+                uint64_t nk[kListBatch];
+                uint32_t G[kListBatch];
+#pragma unroll
+                for (int b = 0; b < kListBatch; b++) {
+                    const uint32_t t = t0 + b * kWave + l;
+                    nk[b] = ~0ull;
+                    if (t < tot) {
+                        int lo = 0, hi = NA;                  // last i with s_pre[i] <= t
+                        while (hi - lo > 1) {
+                            const int mid = (lo + hi) >> 1;
+                            if (s_pre[w][mid] <= t) lo = mid; else hi = mid;
+                        }
+                        const uint32_t j = t - s_pre[w][lo];
+                        // first half zero: the second half must point forwards
+                        if (s_ga[w][lo] > 0 || s_gb[w][j] > 0) nk[b] = gkey + (uint64_t)(s_ka[w][lo] + s_kb[w][j]);
+                    }
+                }
+                group_lookup_n<kListBatch>(P, nk, G);
+#pragma unroll
+                for (int b = 0; b < kListBatch; b++) {
+                    // both groups' point boxes within eps (32-bit when the host has
+                    // shown that every tested pair's squared distance fits)
+                    if (G[b] != kNone) {
+                        const QBox<D> ob = load_gbox<D>(P, G[b]);
+                        bool far;
+                        if (P.wide) {
+                            int64_t acc = 0;
+#pragma unroll
+                            for (int e = 0; e < D; e++) {
+                                const int64_t gap = max((int64_t)ob.lo[e] - qb.hi[e], (int64_t)qb.lo[e] - ob.hi[e]);
+                                acc += gap > 0 ? gap * gap : 0;
+                            }
+                            far = acc > geo.eps2;
+                        } else {
+                            int32_t acc = 0;
+#pragma unroll
+                            for (int e = 0; e < D; e++) {
+                                const int32_t gap = max(max(ob.lo[e] - qb.hi[e], qb.lo[e] - ob.hi[e]), 0);
+                                acc += __mul24(gap, gap);
+                            }
+                            far = acc > (int32_t)min(geo.eps2, (int64_t)INT32_MAX);
+                        }
+                        if (far) G[b] = kNone;
+                    }
+                    const uint64_t m = __ballot(G[b] != kNone);
+                    const uint32_t k = (uint32_t)__popcll(m);
+                    if (at + k > end) fits = false;
+                    if (fits && G[b] != kNone) {
+                        P.nbr[at + __popcll(m & __lanemask_lt())] = G[b];
+                        atomicAdd(P.nbr_bcount + G[b], 1u);
+                    }
+                    if (fits) at += k;
                 }
             }
-            group_lookup_n<kListBatch>(P, nk, G);
-#pragma unroll
-            for (int b = 0; b < kListBatch; b++) {
-                // both groups' point boxes within eps (32-bit when the host has
-                // shown that every tested pair's squared distance fits)
-                if (G[b] != kNone) {
-                    const QBox<D> ob = load_gbox<D>(P, G[b]);
-                    bool far;
-                    if (P.wide) {
-                        int64_t acc = 0;
-#pragma unroll
-                        for (int e = 0; e < D; e++) {
-                            const int64_t gap = max((int64_t)ob.lo[e] - qb.hi[e], (int64_t)qb.lo[e] - ob.hi[e]);
-                            acc += gap > 0 ? gap * gap : 0;
-                        }
-                        far = acc > geo.eps2;
-                    } else {
-                        int32_t acc = 0;
-#pragma unroll
-                        for (int e = 0; e < D; e++) {
-                            const int32_t gap = max(max(ob.lo[e] - qb.hi[e], qb.lo[e] - ob.hi[e]), 0);
-                            acc += __mul24(gap, gap);
-                        }
-                        far = acc > (int32_t)min(geo.eps2, (int64_t)INT32_MAX);
-                    }
-                    if (far) G[b] = kNone;
-                }
-                const uint64_t m = __ballot(G[b] != kNone);
-                const uint32_t k = (uint32_t)__popcll(m);
-                if (at + k > end) fits = false;
-                if (fits && G[b] != kNone) {
-                    P.nbr[at + __popcll(m & __lanemask_lt())] = G[b];
-                    atomicAdd(P.nbr_bcount + G[b], 1u);
-                }
-                if (fits) at += k;
+            __builtin_amdgcn_wave_barrier();
+            if (l == 0) {
+                P.nbr_start[g] = start;
+                P.nbr_count[g] = fits ? at - start : kNone;
+            }
+            if (!fits) {
+                at = start;
+                overflow++;
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        if (l == 0) {
-            P.nbr_start[g] = start;
-            P.nbr_count[g] = fits ? at - start : kNone;
-        }
-        if (!fits) {
-            at = start;
-            overflow++;
-        }
-      }
     }
     if (l == 0 && overflow) atomicAdd(&P.ctr->nbr_overflow, overflow);
 }
@@ -1012,66 +1013,67 @@ __device__ __forceinline__ uint32_t count_walk(const Plan &P, uint32_t g, uint64
     const QBox<D> qb = chunk_box<D, NP>(pp, ~done);
     const NbrSrc src = nbr_source(P, g);
     for (uint32_t oc = 0; oc < src.slots && done != all; oc += kWave) {
-      uint32_t total = load_neighbours<D>(P, g, gkey, src, oc, 0, false, qb, s_beg, s_pre, geo);
-      // Search groups of more than a chunk of points: their chunks in place of
-      // the groups, those within eps of the box only (a dense group holds
-      // thousands of points, most of them far from any one of its
-      // neighbours' points)
-      const uint32_t a = s_beg[l], size = (l + 1 < (uint32_t)kWave ? s_pre[l + 1] : total) - s_pre[l];
-      const bool split = P.m > 1 && __ballot(size > (uint32_t)kWave) != 0;
-      uint32_t chunks = 1;
-      __builtin_amdgcn_wave_barrier();
-      if (split) {
-          const uint32_t nch = size ? (a + size - 1) / kWave - a / kWave + 1 : 0u, inc = wave_inclusive_scan(nch);
-          s_chunk[0][l] = inc - nch;
-          s_chunk[1][l] = a;
-          s_chunk[2][l] = a + size;
-          __builtin_amdgcn_wave_barrier();
-          chunks = lane_value(inc, kWave - 1);
-      }
-      for (uint32_t t0 = 0; t0 < chunks && done != all; t0 += kWave) {
+        uint32_t total = load_neighbours<D>(P, g, gkey, src, oc, 0, false, qb, s_beg, s_pre, geo);
+        // Search groups of more than a chunk of points: their chunks in place of
+        // the groups, those within eps of the box only (a dense group holds
+        // thousands of points, most of them far from any one of its
+        // neighbours' points)
+        const uint32_t a = s_beg[l], size = (l + 1 < (uint32_t)kWave ? s_pre[l + 1] : total) - s_pre[l];
+        const bool split = P.m > 1 && __ballot(size > (uint32_t)kWave) != 0;
+        uint32_t chunks = 1;
+        __builtin_amdgcn_wave_barrier();
         if (split) {
-            uint32_t beg = 0, len = 0;
-            if (t0 + l < chunks) {
-                const uint32_t ln = candidate_lane(t0 + l, s_chunk[0]);
-                const uint32_t c = s_chunk[1][ln] / kWave + (t0 + l - s_chunk[0][ln]);
-                beg = max(s_chunk[1][ln], c * kWave);
-                if (chunk_gap2<D>(qb.lo, qb.hi, P.cbox + (uint64_t)c * (2 * D)) <= geo.eps2) len = min(s_chunk[2][ln], c * kWave + kWave) - beg;
-            }
-            const uint32_t inc = wave_inclusive_scan(len);
-            s_beg[l] = beg;
-            s_pre[l] = inc - len;
+            const uint32_t nch = size ? (a + size - 1) / kWave - a / kWave + 1 : 0u, inc = wave_inclusive_scan(nch);
+            s_chunk[0][l] = inc - nch;
+            s_chunk[1][l] = a;
+            s_chunk[2][l] = a + size;
             __builtin_amdgcn_wave_barrier();
-            total = lane_value(inc, kWave - 1);
+            chunks = lane_value(inc, kWave - 1);
         }
-        // candidate ci + l of the batch; the next batch's point is loaded
-        // before this one is tested, so its latency overlaps the tests
-        uint32_t nxt = candidate_pos(l, total, s_beg, s_pre);
-        Pt<D> qn = load_pt<D>(P.spts, nxt);
-        for (uint32_t ci = 0; ci < total && done != all; ci += kWave) {
-            const bool ok = ci + l < total;
-            const uint32_t pos = nxt;
-            const Pt<D> q = qn;
-            if (ci + kWave < total) {
-                nxt = candidate_pos(ci + kWave + l, total, s_beg, s_pre);
-                qn = load_pt<D>(P.spts, nxt);
-            }
-#pragma unroll
-            for (int k = 0; k < NP; k++) {
-                if (done & (1u << k)) continue;
-                lt += ok;
-                const bool hit = within<D, WIDE>(pp[k], q, geo.eps2) & ok;
-                const uint64_t hm = __ballot(hit);
-                if (record && hm && cnt[k] < (uint32_t)kRec) {
-                    const uint32_t r = cnt[k] + __popcll(hm & __lanemask_lt());
-                    if (hit && r < (uint32_t)kRec) P.rec[(uint64_t)(qpos ? qpos[k] : pc + k) * kRec + r] = pos;
+        for (uint32_t t0 = 0; t0 < chunks && done != all; t0 += kWave) {
+            if (split) {
+                uint32_t beg = 0, len = 0;
+                if (t0 + l < chunks) {
+                    const uint32_t ln = candidate_lane(t0 + l, s_chunk[0]);
+                    const uint32_t c = s_chunk[1][ln] / kWave + (t0 + l - s_chunk[0][ln]);
+                    beg = max(s_chunk[1][ln], c * kWave);
+                    if (chunk_gap2<D>(qb.lo, qb.hi, P.cbox + (uint64_t)c * (2 * D)) <= geo.eps2)
+                        len = min(s_chunk[2][ln], c * kWave + kWave) - beg;
                 }
-                cnt[k] += __popcll(hm);
-                if (cnt[k] >= minpts) done |= 1u << k;
+                const uint32_t inc = wave_inclusive_scan(len);
+                s_beg[l] = beg;
+                s_pre[l] = inc - len;
+                __builtin_amdgcn_wave_barrier();
+                total = lane_value(inc, kWave - 1);
             }
-            done = uniform(done);
+            // candidate ci + l of the batch; the next batch's point is loaded
+            // before this one is tested, so its latency overlaps the tests
+            uint32_t nxt = candidate_pos(l, total, s_beg, s_pre);
+            Pt<D> qn = load_pt<D>(P.spts, nxt);
+            for (uint32_t ci = 0; ci < total && done != all; ci += kWave) {
+                const bool ok = ci + l < total;
+                const uint32_t pos = nxt;
+                const Pt<D> q = qn;
+                if (ci + kWave < total) {
+                    nxt = candidate_pos(ci + kWave + l, total, s_beg, s_pre);
+                    qn = load_pt<D>(P.spts, nxt);
+                }
+#pragma unroll
+                for (int k = 0; k < NP; k++) {
+                    if (done & (1u << k)) continue;
+                    lt += ok;
+                    const bool hit = within<D, WIDE>(pp[k], q, geo.eps2) & ok;
+                    const uint64_t hm = __ballot(hit);
+                    if (record && hm && cnt[k] < (uint32_t)kRec) {
+                        const uint32_t r = cnt[k] + __popcll(hm & __lanemask_lt());
+                        if (hit && r < (uint32_t)kRec) P.rec[(uint64_t)(qpos ? qpos[k] : pc + k) * kRec + r] = pos;
+                    }
+                    cnt[k] += __popcll(hm);
+                    if (cnt[k] >= minpts) done |= 1u << k;
+                }
+                done = uniform(done);
+            }
         }
-      }
     }
     return done;
 }
@@ -3301,7 +3303,7 @@ __global__ __launch_bounds__(kBlock) void k_border(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave];
-    const uint32_t w = wave_in_block(), l = lane_id();
+    const uint32_t w = wave_in_block();
     uint32_t lt = 0;
     const uint32_t ng = ld_agent32(&P.ctr->n_groups);
     const DynRange dr_ = dyn_range(P.ctr->dyn[kDynBorder], P.order);
@@ -3493,7 +3495,8 @@ __device__ __forceinline__ void block_tally(const Plan &P, uint32_t n_core, uint
 // step alone took 267 us.)
 constexpr int kLabelBlock = 1024, kLabelItems = 16, kLabelTile = kLabelBlock * kLabelItems;
 
-__global__ __launch_bounds__(kLabelBlock) void k_label_bin(Plan P, uint16_t *__restrict__ idx, int32_t *__restrict__ val)
+__global__ __launch_bounds__(kLabelBlock) void k_label_bin(Plan P, uint16_t *__restrict__ idx,
+                                                           int32_t *__restrict__ val)
 {
     if (box_missed(P)) return;
     __shared__ uint32_t s_n[kLabelRanges], s_pre[kLabelRanges], s_to[kLabelRanges], s_red[kLabelBlock / kWave];

@@ -191,7 +191,8 @@ struct Plan {
     // it leaves the point to a wave-wide walk, and the two point lists
     // (carved from the worklist, which is free until merging)
     uint32_t radius;
-    uint32_t core_lanes;        // lane walk for core marking: 0 off, 1 column ranges (d <= 2), 2 neighbour lists (d 3..4)
+    uint32_t core_lanes;        // lane walk for core marking: 0 off, 1 column ranges (d <= 2), 2 neighbour lists (cubes,
+                                // d 3..4), 3 eight lanes per point (groups of several cubes)
     uint32_t core_budget;
     uint32_t *core_list;        // [n] sorted positions of points of sparse cubes
     uint32_t *core_defer;       // [n] the points left to the wave-wide walk
@@ -237,8 +238,8 @@ struct Plan {
     uint32_t *gcube;            // [n] group -> first cube with a core point, kNone if none
     uint8_t *unified;           // [n] group -> its core cubes share one union-find root
     uint32_t *groot;            // [n] group -> that root when unified (snapshot after intra linking), else kNone (m > 1)
-    int32_t *cbox;              // [ceil(n / 64)][2][d] box of the core points of every 64 sorted positions (m > 1;
-                                // in owner, free until borders)
+    int32_t *cbox;              // [ceil(n / 64)][2][d] point box of every 64 sorted positions, from linking on of
+                                // the core points among them (m > 1; in owner, free until borders)
     // group mode: the non-empty neighbour groups of each group (self
     // excluded) that can hold a point within eps of one of its points.  Each
     // wave fills its own slab of nbr_cap / waves entries; a group whose list
@@ -249,10 +250,10 @@ struct Plan {
     uint32_t rep_only;          // merge on representatives alone (approximate)
     uint32_t nbr_cap;
     uint32_t list_w;            // offsets per axis walked by the list build: 2R + 1
-    // group mode: the groups sharing a prefix of the first d/2 axes (the key
-    // above bit pshift) are consecutive; pstart / pend give the range of
+    // the groups sharing a prefix of the first paxes axes (the key above bit
+    // pshift) are consecutive; pstart / pend give the range of
     // each prefix (valid when group_key[pstart[p]] >> pshift == p), or null
-    uint32_t pshift, paxes;     // (the prefix spans the first paxes axes)
+    uint32_t pshift, paxes;
     uint32_t pnarrow;           // long ranges are narrowed along the next axis
     uint32_t *pstart;           // [2^pbits]
     uint32_t *pend;             // [2^pbits]
