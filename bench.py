@@ -26,6 +26,8 @@ METRIC = "points clustered/s (2-D 1M, 8-D 500k) vs HBM roofline; served p50/p99 
 HBM_PEAK_GBS = 8000.0
 # int32 VALU lane-ops: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3e12 /s
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
+# int8 matrix ops (a multiply-add counts as two): 256 CUs x 8192 x 2.4 GHz
+MFMA_PEAK_TOPS = 256 * 8192 * 2.4e9 / 1e12
 WORKLOADS = {"2d": 2, "8d": 3, "small": 1, "batch": 4, "served": 5, "54d": 54}
 # 54d: the shape of the paper's largest data set (PAMAP2, Table 1), 54 axes
 HIGH_N = 3_850_505
@@ -311,6 +313,16 @@ def measure(w, steps: int, warmup: int, merge: str, with_cpu: bool) -> dict:
 
     def alu_roofline(phase, ms):
         n_tests = statistics.mean(tests[ALU_PHASES[phase]])
+        if phase == "core" and stats["packed_rows"]:
+            # byte planes on the matrix units: four products over the axes
+            # padded to a multiple of 32
+            per_test = 4 * 2 * (-(-w.d // 32) * 32)
+            achieved = per_test * n_tests / (ms * 1e-3) / 1e12
+            return {"bound": "mfma", "phase": phase, "kernels": kernels[phase],
+                    "achieved": round(achieved, 1), "peak": round(MFMA_PEAK_TOPS, 1),
+                    "unit": "Tops/s (int8 matrix ops)", "frac": round(achieved / MFMA_PEAK_TOPS, 5),
+                    "traffic": traffic(phase)[0], "traffic_source": traffic(phase)[1], "pair_tests": n_tests,
+                    "ops_per_test": per_test, "phase_ms": round(ms, 4)}
         ops = 3.0 * w.d * n_tests                        # d sub + d mul + (d-1) add + compare
         achieved = ops / (ms * 1e-3) / 1e12
         t, src = traffic(phase)
