@@ -11,7 +11,7 @@ HERE = Path(__file__).resolve().parent
 ROOT = HERE.parent
 CSRC = HERE / "csrc"
 OUT = HERE / "libhca.so"
-SOURCES = ["hca_sort.hip", "hca_grid.hip", "hca_highd.hip", "hca_small.hip", "hca_batch.hip", "hca_static.hip", "hca_api.cpp",
+SOURCES = ["hca_sort.hip", "hca_grid.hip", "hca_highd.hip", "hca_batch.hip", "hca_static.hip", "hca_api.cpp",
            "hca_server.cpp", "hca_tune.cpp"]
 ARCH = os.environ.get("HCA_OFFLOAD_ARCH", "gfx950")
 

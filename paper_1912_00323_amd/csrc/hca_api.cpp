@@ -1067,7 +1067,7 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
 }
 
 // ---- small calls -----------------------------------------------------------------
-// Points up to which a call is clustered by all pairs (hca_small.hip), by
+// Points up to which a call is clustered by all pairs (hca_small.h), by
 // where the two paths meet on blobs (us, grid against all pairs: 1-D 8k 126,
 // 103, 12k 127, 137; 2-D 12k 177, 144, 16k 178, 193; 3-D 16k 343, 226; 4-D 16k
 // 476, 265; 8-D 16k 417, 292, wide distances 439, 474; 16-D 16k 656, 227).  Any

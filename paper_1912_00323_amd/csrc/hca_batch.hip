@@ -195,3 +195,5 @@ void launch_seg_scatter(const SegParam *seg, const uint32_t *seg_of, const int32
 }
 
 }  // namespace hca
+
+#include "hca_small.h"

@@ -56,7 +56,7 @@ void launch_link_recorded(const Plan &P, hipStream_t s);
 // the non-core points whose neighbours were not all recorded into P.blist
 void launch_border_list(const Plan &P, hipStream_t s);
 
-// small calls by all pairs (hca_small.hip)
+// small calls by all pairs (hca_small.h)
 constexpr uint32_t kSmallMax = 16384;          // points, at most
 constexpr uint32_t kSmallBoxes = 32;           // blocks of the box pass
 struct SmallArgs {

@@ -1,4 +1,5 @@
-// Small calls: all pairs instead of a grid.
+// Small calls: all pairs instead of a grid.  (Kernels and their launch, compiled
+// with hca_batch.hip.)
 //
 // A call of a few thousand points through the grid is some twenty to thirty
 // launches of a few microseconds each, with one or two host round trips
