@@ -1172,7 +1172,8 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
 // neighbours in the direct table sooner than in lists, whose five launches a
 // small call does not win back: at most 16 cubes per point under 100k points
 // (calls 1.2 to 1.4 times as fast), at most 4 under 2^18 (1.14); larger calls
-// are slower without lists (0.8).
+// are slower without lists (0.8).  (Data past 46340 units along two axes keep
+// the lists, see plan_prefix.)
 bool few_cubes(const Plan &P, uint32_t n, int d)
 {
     if (d != 3 || n >= (1u << 18)) return false;
@@ -1411,7 +1412,8 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
                                           "and representatives enabled");
         P.rep_only = 1;
     }
-    P.list_w = P.m == 1 && !(few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats) ? cube_list_width(d, G.radius, n_off) : 0;
+    const bool no_lists = few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats && far_axes < 2;
+    P.list_w = P.m == 1 && !no_lists ? cube_list_width(d, G.radius, n_off) : 0;
     plan_core_lanes(P, G.radius);
     plan_linked(P);
     Sizes Z;

@@ -772,7 +772,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
         for (uint32_t e = 0; e < P.paxes; e++) all *= P.list_w;
         for (uint32_t e = P.paxes; e < (uint32_t)D; e++) others *= P.list_w;
         nf = (all + 1) / 2;
-        pack = min((uint32_t)kListPack, kWave / nf);
+        pack = P.pnarrow ? min((uint32_t)kListPack, kWave / nf) : 1u;
         scan_max = max(64u, 2u * others);
         uint32_t off = 0, norm = 0, rank = 0;
         if (threadIdx.x < nf) {
