@@ -581,11 +581,14 @@ __device__ __forceinline__ uint32_t forward_offset(uint32_t f, uint32_t pa, uint
 }
 
 // Is every point of the group box ob farther than eps from the box qb?  32-bit
-// when the host has shown that every tested pair's squared
-// distance fits: that bound covers pairs within the stencil's reach, but a
-// prefix range also meets groups far beyond it, so each gap is clamped to
-// 46341 (whose square already exceeds any int32 eps^2) and the sum saturates
-// at 2^31.
+// when the host has shown that every tested pair's squared distance fits.
+// That bound covers pairs within the stencil's reach, but a prefix range also
+// meets groups far beyond it, so each gap is clamped to 46340 and the sum
+// saturates at 2^31: 2^31 + 46340^2 still fits 32 bits.  (From 46341 on it
+// does not: two such gaps came out as a sum of a few thousand.)  A clamped gap
+// always counts as far: data with a gap past 46340 units are narrow only by
+// the stencil's reach, with d reach^2 below 2^31, and eps^2 is then well
+// below 46340^2.
 template <int D>
 __device__ __forceinline__ bool list_far(const Plan &P, const QBox<D> &ob, const QBox<D> &qb, int64_t eps2)
 {
@@ -602,7 +605,7 @@ __device__ __forceinline__ bool list_far(const Plan &P, const QBox<D> &ob, const
 #pragma unroll
     for (int e = 0; e < D; e++) {
         const int32_t gap = max(max(ob.lo[e] - qb.hi[e], qb.lo[e] - ob.hi[e]), 0);
-        const uint32_t gc = min((uint32_t)gap, 46341u);
+        const uint32_t gc = min((uint32_t)gap, 46340u);
         acc = min(acc + __umul24(gc, gc), 0x80000000u);
     }
     return acc > (uint32_t)min(eps2, (int64_t)INT32_MAX);
