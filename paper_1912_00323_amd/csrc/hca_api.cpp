@@ -567,7 +567,7 @@ uint32_t cube_list_width(int d, int32_t radius, uint32_t n_off, const Tune *t = 
 // Sizes of one launch sequence, fixed before the workspace is carved.
 struct Sizes {
     bool wide_keys = false;
-    uint32_t pbits = 0;              // bits of the group-key prefix of the first d/2 axes (0: no prefix ranges)
+    uint32_t pbits = 0;              // bits of the group-key prefix of the first Plan::paxes axes (0: no prefix ranges)
     uint32_t gbits = 0;              // bits of the group key (direct table: 2^gbits slots)
     uint64_t hcap = 0;               // hash slots allocated
     uint32_t sort_tiles = 0, scan_tiles = 0;
@@ -624,11 +624,9 @@ void plan_sizes(Plan &P, uint32_t gbits, bool count_work, bool want_stats, Sizes
 // fit a wave (27 offsets of three axes in the groups' three cells per axis,
 // 25 of two in the cubes' five): the more axes, the shorter the ranges (5-D,
 // 1.2M points, lists with a prefix of 2, 3 and 4 axes: 390, 244 and 371 us;
-// 3-D, 1M points, half the axes and 2: 487 and 169).  Data that reach past
-// 46340 units along two axes or more keep half the axes and whole ranges
-// (far: list_far's 32-bit sum can wrap there and keep far groups), and so do
-// calls without the memory for the larger table (half).
-void plan_prefix(Plan &P, uint32_t gbits, bool far, Sizes *Z, const Tune *t = nullptr, bool half = false)
+// 3-D, 1M points, half the axes and 2: 487 and 169).  Calls without the memory
+// for the larger table keep half the axes (half).
+void plan_prefix(Plan &P, uint32_t gbits, Sizes *Z, const Tune *t = nullptr, bool half = false)
 {
     Z->pbits = 0;
     const bool want = t && t->prefix >= 0 ? t->prefix != 0 : env_prefix();
@@ -641,8 +639,7 @@ void plan_prefix(Plan &P, uint32_t gbits, bool far, Sizes *Z, const Tune *t = nu
     };
     int axes = P.d / 2;
     if (!fits(axes, 2 * kWave - 1)) return;
-    P.pnarrow = !(far && !P.wide);
-    if (P.pnarrow && !half)
+    if (!half)
         while (axes + 1 < P.d && fits(axes + 1, kWave / 2)) axes++;
     P.paxes = (uint32_t)axes;
     P.pshift = P.goff[axes - 1];
@@ -1172,8 +1169,7 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
 // neighbours in the direct table sooner than in lists, whose five launches a
 // small call does not win back: at most 16 cubes per point under 100k points
 // (calls 1.2 to 1.4 times as fast), at most 4 under 2^18 (1.14); larger calls
-// are slower without lists (0.8).  (Data past 46340 units along two axes keep
-// the lists, see plan_prefix.)
+// are slower without lists (0.8).
 bool few_cubes(const Plan &P, uint32_t n, int d)
 {
     if (d != 3 || n >= (1u << 18)) return false;
@@ -1202,18 +1198,13 @@ hca_status upload_geometry(hca_ctx *ctx, const Geometry &g, int d, void **dev, s
 // points and their lists are long (calls on such data are 1.4 to 1.5 times
 // as fast, 5 % at 64 to 256 cubes per point, below that slower, and so are
 // smaller calls).  Calls that ask for counters, representatives or a search
-// mode, and data past 46340 units along two axes (see plan_prefix), keep the
-// cubes; so do keys that would not fit.
+// mode keep the cubes; so do keys that would not fit.
 bool group_search(const hca_ctx *ctx, const Geometry &g, uint32_t n, int d, const int64_t *mn, const int64_t *mx)
 {
     if (d != 4 || g.m != 1 || n < (1u << 18) || !ctx->exact || ctx->fixed || ctx->geo_mode != 0) return false;
     double cubes = 1;
-    int far = 0;
-    for (int k = 0; k < d; k++) {
-        cubes *= (double)((mx[k] - mn[k]) / g.side + 1);
-        far += mx[k] - mn[k] > 46340;
-    }
-    return cubes >= 256.0 * n && cubes < 0x1p48 && far < 2;
+    for (int k = 0; k < d; k++) cubes *= (double)((mx[k] - mn[k]) / g.side + 1);
+    return cubes >= 256.0 * n && cubes < 0x1p48;
 }
 
 hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, double eps,
@@ -1378,11 +1369,9 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
     P.sd = (uint32_t)d;
     uint32_t gbits = 0;
     int64_t span_max = 0;
-    int far_axes = 0;
     for (int k = d - 1; k >= 0; k--) {
         P.origin[k] = (int32_t)mn[k];
         const uint64_t span = (uint64_t)(mx[k] - mn[k]);
-        far_axes += span > 46340;
         span_max = std::max<int64_t>(span_max, (int64_t)span);
         const uint64_t cmax = span / (uint64_t)G.side;
         P.gmax[k] = (uint32_t)(cmax / G.m);
@@ -1412,19 +1401,19 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
                                           "and representatives enabled");
         P.rep_only = 1;
     }
-    const bool no_lists = few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats && far_axes < 2;
+    const bool no_lists = few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats;
     P.list_w = P.m == 1 && !no_lists ? cube_list_width(d, G.radius, n_off) : 0;
     plan_core_lanes(P, G.radius);
     plan_linked(P);
     Sizes Z;
     plan_sizes(P, gbits, stats != nullptr && ctx->prof != -1, stats != nullptr, &Z);
-    plan_prefix(P, gbits, far_axes >= 2, &Z);
+    plan_prefix(P, gbits, &Z);
     P.pts = points;
     P.labels = labels;
     P.core_out = core_out;
     st = workspace(ctx, ws_bytes(P, Z));
     if (st && P.paxes > (uint32_t)d / 2) {
-        plan_prefix(P, gbits, far_axes >= 2, &Z, nullptr, true);
+        plan_prefix(P, gbits, &Z, nullptr, true);
         ctx->err.clear();
         st = workspace(ctx, ws_bytes(P, Z));
     }
@@ -1506,7 +1495,6 @@ struct BatchGroup {
     // layout of the packed key shared by the data sets (from their boxes)
     uint32_t gw[kMaxDim] = {};
     bool wide = false;
-    bool far = false;                   // some data set reaches past 46340 units along two axes
     uint32_t cubes_axis = 1;            // largest cube count along an axis of any data set
     Tune tune;                          // knobs of its launch sequence
     std::string tune_key;               // what the autotuner's cache knows it by
@@ -1698,18 +1686,14 @@ hca_status batch_layout(hca_ctx *ctx, BatchGroup &g, const char *hb, const Batch
     const int d = g.d;
     const uint32_t *box = (const uint32_t *)(hb + g.h_box);
     uint64_t cmax[kMaxDim] = {};
-    g.far = false;
     for (size_t i = 0; i < g.par.size(); i++) {
         SegParam &sp = g.par[i];
         if (sets[g.segs[i]].n == 0) continue;
-        int far_axes = 0;
         for (int k = 0; k < d; k++) {
             const int32_t lo = (int32_t)(~box[i * 2 * d + k] ^ 0x80000000u);
             const int32_t hi = (int32_t)(box[i * 2 * d + d + k] ^ 0x80000000u);
             const int64_t span = (int64_t)hi - lo;
             if (span >= (1ll << 30)) return fail(ctx, HCA_E_RANGE, "coordinate span >= 2^30 along an axis");
-            far_axes += span > 46340;
-            g.far |= far_axes >= 2;
             sp.origin[k] = lo;
             cmax[k] = std::max<uint64_t>(cmax[k], (uint64_t)span / (uint64_t)sp.side);
         }
@@ -1771,7 +1755,7 @@ void batch_plan(BatchGroup &g, char *db, const Tune *t)
     plan_core_lanes(P, rmax, t);
     plan_linked(P);
     plan_sizes(P, P.key_bits, false, false, &g.Z, t);
-    plan_prefix(P, P.key_bits, g.far, &g.Z, t);
+    plan_prefix(P, P.key_bits, &g.Z, t);
 }
 
 hca_status run_sets(hca_ctx *ctx, const BatchSet *sets, int32_t nseg)

@@ -652,7 +652,6 @@ __device__ __forceinline__ uint32_t list_by_prefix(const Plan &P, uint32_t g0, u
             if (f == 0) {
                 rs = g + 1;
                 size = P.pend[pr] - rs;
-                if (!P.pnarrow) length = P.pend[pr] - P.pstart[pr];
             } else {
                 const uint32_t a = P.pstart[pr];
                 if (a < ng && (P.group_key[a] >> P.pshift) == pr) {
@@ -660,7 +659,7 @@ __device__ __forceinline__ uint32_t list_by_prefix(const Plan &P, uint32_t g0, u
                     size = P.pend[pr] - a;
                 }
             }
-            if (size > kRangeCut && P.pnarrow) {
+            if (size > kRangeCut) {
                 // first groups with a key of at least ka and kb
                 const uint32_t x = P.paxes, sh = P.goff[x];
                 const int64_t c = (int64_t)((gkey >> sh) & ((1ull << P.gw[x]) - 1ull)), R = (int64_t)(P.list_w >> 1);
@@ -775,7 +774,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
         for (uint32_t e = 0; e < P.paxes; e++) all *= P.list_w;
         for (uint32_t e = P.paxes; e < (uint32_t)D; e++) others *= P.list_w;
         nf = (all + 1) / 2;
-        pack = P.pnarrow ? min((uint32_t)kListPack, kWave / nf) : 1u;
+        pack = min((uint32_t)kListPack, kWave / nf);
         scan_max = max(64u, 2u * others);
         uint32_t off = 0, norm = 0, rank = 0;
         if (threadIdx.x < nf) {

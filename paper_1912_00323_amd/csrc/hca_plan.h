@@ -254,7 +254,6 @@ struct Plan {
     // pshift) are consecutive; pstart / pend give the range of
     // each prefix (valid when group_key[pstart[p]] >> pshift == p), or null
     uint32_t pshift, paxes;
-    uint32_t pnarrow;           // long ranges are narrowed along the next axis
     uint32_t *pstart;           // [2^pbits]
     uint32_t *pend;             // [2^pbits]
     uint32_t *nbr_count;        // [n] forward entries

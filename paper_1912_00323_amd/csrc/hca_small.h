@@ -101,24 +101,18 @@ __device__ __forceinline__ bool small_narrow(const SmallArgs &A, const int32_t *
 // packed cube key that surely fits 63 bits (a coordinate takes at most one
 // bit more than its cube number, with search groups of at most eight cubes);
 // past eight: data that byte planes hold.  Anything else is left to the
-// general path, which refuses what it refuses.  So are, from three to eight
-// axes, data that reach past 46340 units along two axes or more: the gap
-// sums of the general path's neighbour lists can wrap there, so that far
-// pairs come out as neighbours, and a call gets the same labels whichever
-// way it goes.
+// general path, which refuses what it refuses.
 __device__ __forceinline__ bool small_takes(const SmallArgs &A, const int32_t *s_box)
 {
     uint64_t sum = 0, bits = 0;
-    int far = 0;
     for (int k = 0; k < A.d; k++) {
         const uint64_t span = (uint64_t)((int64_t)s_box[A.d + k] - s_box[k]);
-        far += span > 46340;
         if (span >= (A.d > kMaxDim ? 1ull << 15 : 1ull << 30)) return false;
         sum += span * span;
         if (A.d <= kMaxDim) bits += 1 + max(3, 64 - __clzll((long long)(span / A.side)));
     }
     if (A.d > kMaxDim) return sum < (1ull << 31);
-    return bits <= 63 && (A.d < 3 || far < 2);
+    return bits <= 63;
 }
 
 // ---------------------------------------------------------------------------
