@@ -1352,6 +1352,13 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
     }
     const Geometry &G = *geo;
     const uint32_t n_off = (uint32_t)(G.off.size() / d);
+    // a call that the box of the previous calls does not allow (their radius
+    // may have been another) is planned from its own
+    auto from_own_box = [&] {
+        ctx->box_armed = false;
+        ctx->err.clear();
+        return run(ctx, points_in, n64, d, eps, min_pts, labels, core_out, stats);
+    };
 
     // 2. key layout: group coordinates (dimension 0 most significant) above
     //    the in-group cube offsets
@@ -1380,7 +1387,10 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
         gbits += P.gw[k];
     }
     P.key_bits = gbits + P.fine_bits;
-    if (P.key_bits > 63) return fail(ctx, HCA_E_RANGE, "packed cube key needs more than 63 bits");
+    if (P.key_bits > 63) {
+        if (ahead) return from_own_box();
+        return fail(ctx, HCA_E_RANGE, "packed cube key needs more than 63 bits");
+    }
     P.passes = sort_passes(P.key_bits, P.key_bits > 32);
     P.digit_bits = std::max<uint32_t>(1, (P.key_bits + P.passes - 1) / P.passes);
     // largest coordinate difference of any pair the kernels test
@@ -1417,6 +1427,7 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
         ctx->err.clear();
         st = workspace(ctx, ws_bytes(P, Z));
     }
+    if (st && ahead) return from_own_box();
     if (st) return st;
     if (ahead) {
         // this call's box, into the workspace as sized for the whole call,
