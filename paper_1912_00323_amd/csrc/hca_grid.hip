@@ -2747,10 +2747,12 @@ __global__ __launch_bounds__(kBlock) void k_merge_tiles(Plan P)
         const uint32_t q = c * kWave + l;
         const bool in = q < P.n;
         const uint32_t cube = P.cell_of[min(q, P.n - 1)], grp = P.group_of[cube];
-        const bool big = group_chunks(P, grp) > kTileMaxChunks;
+        // (a group of one cube has nothing to link, however many points it holds)
+        const uint32_t nch = group_chunks(P, grp);
+        const bool big = nch > kTileMaxChunks, linked = nch != 0 && !big;
         const uint64_t starts = __ballot(in && big && P.group_start[grp] == q);
         if (starts && l == 0) atomicAdd(&P.ctr->n_big_groups, (uint32_t)__popcll(starts));
-        const bool core = in && !big && P.core[q];
+        const bool core = in && linked && P.core[q];
         const uint64_t live = __ballot(core);
         if (!live) continue;
         uint32_t root = core ? uf_find(P.parent, cube) : kNone;
@@ -2791,7 +2793,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_tiles(Plan P)
         const uint32_t c1 = (c + 1) * kWave;
         if (c1 >= P.n) continue;
         const uint32_t g = lane_value(grp, kWave - 1), g0 = uniform(P.group_start[g]), g1 = uniform(P.group_start[g + 1]);
-        if (g1 > c1 && !lane_value((uint32_t)big, kWave - 1))
+        if (g1 > c1 && lane_value((uint32_t)linked, kWave - 1))
             link_rows<D, WIDE, true>(P, g, g, false, false, max(g0, c * kWave), c1, c1, g1, s_pt[w], lt);
     }
     flush_tests(P, kTestsIntra, lt);

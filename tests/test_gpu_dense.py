@@ -1,0 +1,36 @@
+"""Data of few cubes with very many points each, and other sets that are
+cheap for the method: labels against the construction, and phases that must
+not grow with the square of the points (their times stay far below what the
+quadratic walk takes)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from test_gpu import ctx  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,cubes", [(4, 8), (5, 2), (6, 2), (8, 1)])
+def test_groups_of_one_huge_cube(ctx, d, cubes):  # noqa: F811
+    """A million points in a few groups of a single cube: nothing to link inside
+    a group (47 ms when its points were walked all the same)."""
+    import torch
+    n = 1_000_000
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    which = torch.randint(0, cubes, (n,), device="cuda", generator=gen)
+    pts = torch.randint(0, 3, (n, d), device="cuda", generator=gen)
+    pts[:, 0] += 4000 * which
+    pts = pts.to(torch.int32).contiguous()
+    first = torch.full((cubes,), n, device="cuda").scatter_reduce(0, which, torch.arange(n, device="cuda"), "amin")
+    want = torch.argsort(torch.argsort(first))[which].to(torch.int32)
+    ctx.set_profiling("all")
+    try:
+        for _ in range(2):
+            assert torch.equal(ctx.cluster(pts, 60.0, 8), want)
+        times = ctx.phase_times()
+    finally:
+        ctx.set_profiling(None)
+    print(times, flush=True)
+    assert times["intra"] < 5.0, times
