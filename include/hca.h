@@ -95,7 +95,7 @@ typedef struct {
     int32_t wide;             /* 1 if squared distances were computed in 64 bits */
     int32_t dense_table;      /* 1 if the group lookup was a direct-indexed table */
     int32_t list_overflow;    /* groups searched over the whole stencil because their
-                               * neighbour list did not fit its slab (m > 1) */
+                               * neighbour list did not fit the list array (m > 1) */
     /* point-pair distance tests executed by core marking, merging and border
      * assignment; counted only while phase profiling is on (hca_set_profiling),
      * else 0 */

@@ -82,6 +82,7 @@ struct Counters {
     uint32_t pad_tally[2];      // (core and noise counts: see tally)
     uint32_t n_clusters;
     uint32_t nbr_overflow;      // groups whose neighbour list did not fit
+    uint32_t nbr_used;          // entries of the list array handed out to waves
     uint32_t hmask;             // hash slots in use - 1 (a power of two - 1)
     uint32_t nbr_ticket;        // tiles of the backward-list scan
     uint32_t hd_left[kHdPasses];    // more than kMaxDim axes: points left undecided by each core pass
@@ -241,9 +242,10 @@ struct Plan {
     int32_t *cbox;              // [ceil(n / 64)][2][d] point box of every 64 sorted positions, from linking on of
                                 // the core points among them (m > 1; in owner, free until borders)
     // group mode: the non-empty neighbour groups of each group (self
-    // excluded) that can hold a point within eps of one of its points.  Each
-    // wave fills its own slab of nbr_cap / waves entries; a group whose list
-    // does not fit gets nbr_count = kNone and is searched over the stencil.
+    // excluded) that can hold a point within eps of one of its points.  Waves
+    // fill blocks of the nbr_cap entries (more than kMaxDim axes: their own
+    // slabs of nbr_cap / waves); when a group's list does not fit, it gets
+    // nbr_count = kNone and every group is searched over the stencil.
     // The lookups find each pair once, from the smaller key ("forward"); the
     // pair is kept when the two groups' point boxes come within eps, and the
     // reverse entries ("backward") are filled in afterwards.
@@ -258,7 +260,7 @@ struct Plan {
     uint32_t *pend;             // [2^pbits]
     uint32_t *nbr_count;        // [n] forward entries
     uint32_t *nbr_start;        // [n]
-    uint32_t *nbr;              // [nbr_cap] forward entries in per-wave slabs
+    uint32_t *nbr;              // [nbr_cap] forward entries
     uint32_t *nbr_bcount;       // [n] backward entries
     uint32_t *nbr_bstart;       // [n]
     uint32_t *nbr_bcursor;      // [n]

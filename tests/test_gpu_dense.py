@@ -34,3 +34,23 @@ def test_groups_of_one_huge_cube(ctx, d, cubes):  # noqa: F811
         ctx.set_profiling(None)
     print(times, flush=True)
     assert times["intra"] < 5.0, times
+
+
+@pytest.mark.parametrize("d", [5, 6])
+def test_long_lists_in_a_small_array(ctx, d, monkeypatch):  # noqa: F811
+    """Lists longer than a wave's even share of the list array, with room for
+    all of them together: they fit, and the labels are the oracle's."""
+    import oracle
+    from test_gpu import gpu_labels
+    monkeypatch.setenv("HCA_LIST_SLAB", "64")
+    rng = np.random.default_rng(d)
+    eps = 100.0
+    block = rng.integers(0, 300, size=(3000, d))
+    block[:, 5:] //= 30
+    lone = np.zeros((4000, d), np.int64)
+    lone[:, 0], lone[:, 1] = 3000 + 400 * (np.arange(4000) % 64), 400 * (np.arange(4000) // 64)
+    pts = np.concatenate([block, lone])[rng.permutation(7000)].astype(np.int32)
+    want = oracle.dbscan(pts, eps, 5)
+    got, st = gpu_labels(ctx, pts, eps, 5, stats=True)
+    assert np.array_equal(got, want)
+    assert st["list_overflow"] == 0, st
