@@ -611,23 +611,30 @@ __device__ __forceinline__ bool list_far(const Plan &P, const QBox<D> &ob, const
     return acc > (uint32_t)min(eps2, (int64_t)INT32_MAX);
 }
 
-// Room for k more entries of the group (or pack of groups) whose entries lie at
-// [start, at) in the wave's block [at.., end): when they do not fit, the wave
-// takes another block of the array and moves them there.  False when the
-// array is full.  (With a fixed share of the array per wave a call whose lists
+// A quarter of the list array is shared out evenly, the rest taken in blocks by
+// waves whose share is used up.  (With fixed shares alone a call whose lists
 // fit in all could still overflow in one wave, and every group was then
-// searched over the stencil: 7-D, 383k points, core marking 0.5 -> 15.5 ms.)
+// searched over the stencil: 7-D, 383k points, core marking 0.5 -> 15.5 ms.
+// Without shares every wave's first block queued up at one counter: 5-D, 149k
+// points, lists 45 -> 213 us.)
+constexpr uint32_t kListBlock = 1024;
 struct ListRoom {
-    uint32_t at, end, block;
+    uint32_t at, end;           // of the wave's share or block
+    uint32_t pool;              // first entry past the shares
 };
+
+// Room for k more entries of the group (or pack of groups) whose entries so far
+// lie at [start, at): when they do not fit, the wave takes a block and moves
+// them there.  False when the array is full.
 
 __device__ __forceinline__ bool list_room(const Plan &P, ListRoom &room, uint32_t &start, uint32_t k)
 {
     if (room.at + k <= room.end) return true;
     const uint32_t have = room.at - start, need = have + k;
-    uint32_t base = kNone, size = max(room.block, need);
-    if (lane_id() == 0 && (uint64_t)ld_agent32(&P.ctr->nbr_used) + need <= P.nbr_cap)
-        base = atomicAdd(&P.ctr->nbr_used, size);
+    const uint32_t size = max(min(kListBlock, (P.nbr_cap - room.pool) / 4096u), need + kWave);
+    uint32_t base = kNone;
+    if (lane_id() == 0 && (uint64_t)room.pool + ld_agent32(&P.ctr->nbr_used) + need <= P.nbr_cap)
+        base = room.pool + atomicAdd(&P.ctr->nbr_used, size);
     base = lane_value(base, 0);
     if (base == kNone || (uint64_t)base + need > P.nbr_cap) return false;
     __threadfence_block();
@@ -791,7 +798,8 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
     const uint32_t w = wave_in_block(), l = lane_id();
     const uint32_t ng = ld_agent32(&P.ctr->n_groups);
     const uint32_t waves = gridDim.x * kWavesPerBlock;
-    ListRoom room = {0, 0, max(1u, min(1024u, P.nbr_cap / waves / 4))};
+    const uint32_t share = P.nbr_cap / waves / 4, mine = (blockIdx.x * kWavesPerBlock + w) * share;
+    ListRoom room = {mine, mine + share, waves * share};
     uint32_t overflow = 0;
     // forward offsets of the prefix's axes, nearest first
     uint32_t nf = 0, pack = 1, scan_max = 0;

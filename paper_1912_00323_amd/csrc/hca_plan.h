@@ -82,7 +82,7 @@ struct Counters {
     uint32_t pad_tally[2];      // (core and noise counts: see tally)
     uint32_t n_clusters;
     uint32_t nbr_overflow;      // groups whose neighbour list did not fit
-    uint32_t nbr_used;          // entries of the list array handed out to waves
+    uint32_t nbr_used;          // entries of the list array handed out in blocks
     uint32_t hmask;             // hash slots in use - 1 (a power of two - 1)
     uint32_t nbr_ticket;        // tiles of the backward-list scan
     uint32_t hd_left[kHdPasses];    // more than kMaxDim axes: points left undecided by each core pass
