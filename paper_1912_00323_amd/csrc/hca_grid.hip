@@ -2948,6 +2948,46 @@ __device__ __forceinline__ void link_chunk(const Plan &P, uint32_t GA, uint32_t 
 // linked on the spot).
 constexpr uint32_t kInlineTiles = 4;
 
+// The rows [ra0, ra1) and columns [rb0, rb1) of two unified groups, small ones:
+// the first pair within eps joins them.
+template <int D, bool WIDE>
+__device__ __forceinline__ void link_small(const Plan &P, uint32_t ga, uint32_t gb, uint32_t ra0, uint32_t ra1, uint32_t rb0,
+                                           uint32_t rb1, int32_t (*s_pt)[D], uint32_t &lt)
+{
+    const uint32_t l = lane_id();
+    if (uf_find(P.parent, ga) == uf_find(P.parent, gb)) return;
+    for (uint32_t ia = ra0; ia < ra1; ia += kWave) {
+        const uint32_t qi = ia + l;
+        const bool core_i = qi < ra1 && P.core[qi];
+        const uint64_t mi = __ballot(core_i);
+        if (!mi) continue;
+        const Pt<D> pi = load_pt<D>(P.spts, core_i ? qi : ra0);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int e = 0; e < D; e++) s_pt[l][e] = pi.x[e];
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t jb = rb0; jb < rb1; jb += kWave) {
+            const uint32_t qj = jb + l;
+            const bool core_j = qj < rb1 && P.core[qj];
+            if (!__ballot(core_j)) continue;
+            const Pt<D> pj = load_pt<D>(P.spts, core_j ? qj : rb0);
+            uint64_t rows = mi;
+            while (rows) {
+                const uint32_t r = __ffsll((unsigned long long)rows) - 1;
+                rows &= rows - 1;
+                Pt<D> pr;
+#pragma unroll
+                for (int e = 0; e < D; e++) pr.x[e] = s_pt[r][e];
+                lt += core_j;
+                if (__ballot(core_j && within<D, WIDE>(pr, pj, P.eps2))) {
+                    if (l == 0) uf_union(P.parent, ga, gb);
+                    return;
+                }
+            }
+        }
+    }
+}
+
 // Held to 128 registers (four waves per SIMD): a few spill, and the walk
 // still gains from the extra wave.
 template <int D, bool WIDE>
@@ -3020,9 +3060,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_merge_inter(Plan P)
                 if (next == kNone) break;
                 const uint32_t src_lane = next & 63u;
                 const uint32_t gb = __shfl(GB, src_lane);
-                for (uint32_t ra = a0; ra < a1; ra += kWave)
-                    link_rows<D, WIDE, false>(P, GA, gb, true, true, ra, min(a1, ra + kWave), P.group_start[gb],
-                                       P.group_start[gb + 1], s_pt[w], lt);
+                link_small<D, WIDE>(P, ga, P.gcube[gb], a0, a1, P.group_start[gb], P.group_start[gb + 1], s_pt[w], lt);
                 if (l == src_lane) rank = kNone;
             }
             if (both && tiles <= kInlineTiles) GB = kNone;
