@@ -1701,28 +1701,33 @@ __global__ __launch_bounds__(kBlock) void k_core_list_lanes(Plan P)
 // that has its minPts neighbours costs nothing further (5-D, 1.2M points:
 // 108M tests -> 42M, 804 -> 516 us).  A lane per point makes the chains eight
 // times as long (1231 us).  A point still short after P.core_budget
-// candidates goes to a wave of its own, which also skips the chunks of large
-// groups that lie out of reach.
+// candidates is left to k_core_group_rest, which also skips the chunks of large
+// groups that lie out of reach.  A wave that had to leave more than half of
+// its points hands on the others untested: where points need more candidates
+// than that, the lanes only add to the chunks' work (uniform 6-D, 314k points,
+// minPts 10: chunks alone 870 us, lanes and a wave per point left 3357).
 constexpr int kOct = 8;
+
+// Eight lanes per point, or (no lists, or lists that overflowed) a wave per
+// chunk of points?
+__device__ __forceinline__ bool by_octets(const Plan &P) { return P.nbr_cap && P.ctr->nbr_overflow == 0; }
 
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_core_group_lanes(Plan P)
 {
-    if (box_missed(P)) return;
+    if (box_missed(P) || !by_octets(P)) return;
     __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave];
     const uint32_t ns = ld_agent32(&P.ctr->n_sparse);
-    const bool lists = P.nbr_cap && P.ctr->nbr_overflow == 0;
     const uint32_t w = wave_in_block(), l = lane_id(), sub = l % kOct, first = l - sub;
     const uint32_t minpts = (uint32_t)P.min_pts, budget = P.core_budget;
     const int64_t eps2 = P.eps2;
-    uint32_t lt = 0;
+    uint32_t lt = 0, taken = 0, passed = 0;
     const WaveRange hca_wr_ = wave_range(P.order);
     HCA_FOR_UNITS(u, (ns + kOct - 1) / kOct) {
         const uint32_t i = u * kOct + l / kOct;
-        bool defer = false;
-        uint32_t q = kNone;
-        if (i < ns) {
-            q = P.core_list[i];
+        bool defer = i < ns;
+        const uint32_t q = defer ? P.core_list[i] : kNone;
+        if (defer && 2 * passed <= taken) {
             const uint32_t c = P.cell_of[q], g = P.group_of[c];
             const Pt<D> p = load_pt<D>(P.spts, q);
             QBox<D> pb;
@@ -1733,71 +1738,70 @@ __global__ __launch_bounds__(kBlock) void k_core_group_lanes(Plan P)
             uint32_t cnt = b0 - a0;
             if (P.rec)
                 for (uint32_t t = sub; t < cnt && t < (uint32_t)kRec; t += kOct) P.rec[(uint64_t)q * kRec + t] = a0 + t;
-            defer = !lists;
-            if (lists) {
-                // slot 0: the group's points before the cube, 1: those after
-                const uint32_t fs = P.nbr_start[g], fc = P.nbr_count[g], bs = P.nbr_bstart[g];
-                const uint32_t nslots = 2u + fc + P.nbr_bcount[g];
-                uint32_t tested = 0;
-                for (uint32_t j = 0; j < nslots && cnt < minpts && tested < budget; j += kOct) {
-                    const uint32_t k = j + sub;
-                    uint32_t lo = 0, size = 0;
-                    if (k == 0) {
-                        lo = g0;
-                        size = a0 - g0;
-                    } else if (k == 1) {
-                        lo = b0;
-                        size = g1 - b0;
-                    } else if (k < nslots) {
-                        const uint32_t G = k - 2u < fc ? P.nbr[fs + k - 2u] : P.nbr_back[bs + (k - 2u - fc)];
-                        if (gbox_within<D>(P, G, pb, eps2)) {
-                            lo = P.group_start[G];
-                            size = P.group_start[G + 1] - lo;
-                        }
-                    }
-                    uint32_t inc = size;
-#pragma unroll
-                    for (int o = 1; o < kOct; o <<= 1) {
-                        const uint32_t t = __shfl_up(inc, o, kOct);
-                        if (sub >= (uint32_t)o) inc += t;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    s_beg[w][l] = lo;
-                    s_pre[w][l] = inc - size;
-                    __builtin_amdgcn_wave_barrier();
-                    const uint32_t total = __shfl(inc, kOct - 1, kOct);
-                    for (uint32_t v = 0; v < total && cnt < minpts && tested < budget; v += 2 * kOct) {
-                        uint32_t pos[2];
-                        Pt<D> o[2];
-#pragma unroll
-                        for (int b = 0; b < 2; b++) {
-                            const uint32_t t = min(v + (uint32_t)b * kOct + sub, total - 1u);
-                            uint32_t r = 0;                   // last slot with pre <= t
-#pragma unroll
-                            for (uint32_t h = kOct / 2; h; h >>= 1)
-                                if (s_pre[w][first + r + h] <= t) r += h;
-                            pos[b] = s_beg[w][first + r] + (t - s_pre[w][first + r]);
-                            o[b] = load_pt<D>(P.spts, pos[b]);
-                        }
-#pragma unroll
-                        for (int b = 0; b < 2; b++) {
-                            const bool ok = v + (uint32_t)b * kOct + sub < total;
-                            lt += ok;
-                            const bool hit = ok && within<D, WIDE>(p, o[b], eps2);
-                            const uint32_t hits = (uint32_t)(__ballot(hit) >> first) & ((1u << kOct) - 1u);
-                            const uint32_t r = cnt + (uint32_t)__popc(hits & ((1u << sub) - 1u));
-                            if (P.rec && hit && r < (uint32_t)kRec) P.rec[(uint64_t)q * kRec + r] = pos[b];
-                            cnt += (uint32_t)__popc(hits);
-                        }
-                        tested += 2 * kOct;
+            // slot 0: the group's points before the cube, 1: those after
+            const uint32_t fs = P.nbr_start[g], fc = P.nbr_count[g], bs = P.nbr_bstart[g];
+            const uint32_t nslots = 2u + fc + P.nbr_bcount[g];
+            uint32_t tested = 0;
+            for (uint32_t j = 0; j < nslots && cnt < minpts && tested < budget; j += kOct) {
+                const uint32_t k = j + sub;
+                uint32_t lo = 0, size = 0;
+                if (k == 0) {
+                    lo = g0;
+                    size = a0 - g0;
+                } else if (k == 1) {
+                    lo = b0;
+                    size = g1 - b0;
+                } else if (k < nslots) {
+                    const uint32_t G = k - 2u < fc ? P.nbr[fs + k - 2u] : P.nbr_back[bs + (k - 2u - fc)];
+                    if (gbox_within<D>(P, G, pb, eps2)) {
+                        lo = P.group_start[G];
+                        size = P.group_start[G + 1] - lo;
                     }
                 }
-                // budget spent with candidates left: a wave decides this point
-                defer = cnt < minpts && tested >= budget;
+                uint32_t inc = size;
+#pragma unroll
+                for (int o = 1; o < kOct; o <<= 1) {
+                    const uint32_t t = __shfl_up(inc, o, kOct);
+                    if (sub >= (uint32_t)o) inc += t;
+                }
+                __builtin_amdgcn_wave_barrier();
+                s_beg[w][l] = lo;
+                s_pre[w][l] = inc - size;
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t total = __shfl(inc, kOct - 1, kOct);
+                for (uint32_t v = 0; v < total && cnt < minpts && tested < budget; v += 2 * kOct) {
+                    uint32_t pos[2];
+                    Pt<D> o[2];
+#pragma unroll
+                    for (int b = 0; b < 2; b++) {
+                        const uint32_t t = min(v + (uint32_t)b * kOct + sub, total - 1u);
+                        uint32_t r = 0;                   // last slot with pre <= t
+#pragma unroll
+                        for (uint32_t h = kOct / 2; h; h >>= 1)
+                            if (s_pre[w][first + r + h] <= t) r += h;
+                        pos[b] = s_beg[w][first + r] + (t - s_pre[w][first + r]);
+                        o[b] = load_pt<D>(P.spts, pos[b]);
+                    }
+#pragma unroll
+                    for (int b = 0; b < 2; b++) {
+                        const bool ok = v + (uint32_t)b * kOct + sub < total;
+                        lt += ok;
+                        const bool hit = ok && within<D, WIDE>(p, o[b], eps2);
+                        const uint32_t hits = (uint32_t)(__ballot(hit) >> first) & ((1u << kOct) - 1u);
+                        const uint32_t r = cnt + (uint32_t)__popc(hits & ((1u << sub) - 1u));
+                        if (P.rec && hit && r < (uint32_t)kRec) P.rec[(uint64_t)q * kRec + r] = pos[b];
+                        cnt += (uint32_t)__popc(hits);
+                    }
+                    tested += 2 * kOct;
+                }
             }
+            // budget spent with candidates left: a wave decides this point
+            defer = cnt < minpts && tested >= budget;
             if (!defer && sub == 0) core_result(P, q, c, cnt, minpts);
         }
         const uint64_t m = __ballot(defer && sub == 0);
+        taken += kOct;
+        passed += (uint32_t)__popcll(m);
         if (m) {
             const uint32_t lead = (uint32_t)__ffsll((unsigned long long)m) - 1u;
             uint32_t at = 0;
@@ -1809,26 +1813,61 @@ __global__ __launch_bounds__(kBlock) void k_core_group_lanes(Plan P)
     flush_tests(P, kTestsCore, lt);
 }
 
-// The points that the lanes of group mode left, one wave each.
+// The points that the lanes of group mode left, or without the lanes all
+// points of sparse cubes: a wave takes NP of them, which lie near each other in
+// the list, or a single one when there are few for each wave (5-D, 1M points:
+// 142 us against 260 in fours; uniform 6-D, where nearly all are left: the
+// call 5.3 ms one by one, 3.1 in fours).
+constexpr uint32_t kRestSingle = 16;
+template <int D, bool WIDE, int NP>
+__device__ __forceinline__ void core_group_points(const Plan &P, const uint32_t *list, uint32_t count, uint32_t (*s_beg)[kWave],
+                                                  uint32_t (*s_pre)[kWave], uint32_t (*s_chunk)[3][kWave], uint32_t &lt)
+{
+    const uint32_t w = wave_in_block(), l = lane_id();
+    const Geo<D> geo = call_geo<D>(P);
+    const DynRange dr_ = dyn_range(P.ctr->dyn[kDynCore], P.order);
+    HCA_FOR_UNITS_DYN(u, (count + NP - 1) / NP, dr_) {
+        const uint32_t i0 = u * NP, np = min((uint32_t)NP, count - i0);
+        const uint32_t q = list[i0 + min(l, np - 1)], c = P.cell_of[q], grp = P.group_of[c];
+        Pt<D> pp[NP];
+        uint32_t qpos[NP], cnt[NP];
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            qpos[k] = lane_value(q, k);
+            cnt[k] = 0;
+            pp[k] = load_pt<D>(P.spts, qpos[k]);
+#pragma unroll
+            for (int e = 0; e < D; e++) pp[k].x[e] = uniform_i(pp[k].x[e]);
+        }
+        uint32_t left = (1u << np) - 1u;
+        while (left) {
+            const uint32_t g = lane_value(grp, __ffs(left) - 1);
+            const uint32_t run = (uint32_t)__ballot(grp == g) & left;
+            left &= ~run;
+            count_walk<D, WIDE, NP>(P, g, P.group_key[g], pp, ~run & ((1u << NP) - 1u), cnt, s_beg[w], s_pre[w], lt, geo,
+                                    s_chunk[w], kNone, qpos);
+        }
+        uint32_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < NP; k++)
+            if ((uint32_t)k == l) mine = cnt[k];
+        if (l < np) core_result(P, q, c, mine, geo.min_pts);
+    }
+}
+
 template <int D, bool WIDE>
-__global__ __launch_bounds__(kBlock) void k_core_group_deferred(Plan P)
+__global__ __launch_bounds__(kBlock, 6) void k_core_group_rest(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave], s_chunk[kWavesPerBlock][3][kWave];
-    const uint32_t w = wave_in_block();
-    const uint32_t nd = ld_agent32(&P.ctr->n_defer);
-    const Geo<D> geo = call_geo<D>(P);
+    const bool lanes = by_octets(P);
+    const uint32_t count = ld_agent32(lanes ? &P.ctr->n_defer : &P.ctr->n_sparse);
+    const uint32_t *list = lanes ? P.core_defer : P.core_list;
     uint32_t lt = 0;
-    const WaveRange hca_wr_ = wave_range(P.order);
-    HCA_FOR_UNITS(i, nd) {
-        const uint32_t q = P.core_defer[i];
-        const uint32_t c = P.cell_of[q], g = P.group_of[c];
-        Pt<D> pp[1];
-        uint32_t qpos[1] = {q}, cnt[1] = {0};
-        pp[0] = load_pt<D>(P.spts, q);
-        count_walk<D, WIDE, 1>(P, g, P.group_key[g], pp, 0u, cnt, s_beg[w], s_pre[w], lt, geo, s_chunk[w], kNone, qpos);
-        if (lane_id() == 0) core_result(P, q, c, cnt[0], geo.min_pts);
-    }
+    if (count <= kRestSingle * gridDim.x * kWavesPerBlock)
+        core_group_points<D, WIDE, 1>(P, list, count, s_beg, s_pre, s_chunk, lt);
+    else
+        core_group_points<D, WIDE, (D > 4 ? 4 : kPch)>(P, list, count, s_beg, s_pre, s_chunk, lt);
     flush_tests(P, kTestsCore, lt);
 }
 
@@ -3759,7 +3798,7 @@ void launch_core(const Plan &P, int blocks, hipStream_t s)
         const int fb = (int)std::max<uint64_t>(1, (P.n + kFlatBlock - 1) / kFlatBlock);
         hipLaunchKernelGGL(k_core_flat<1>, dim3(fb), dim3(kFlatBlock), 0, s, P);
         HCA_DISPATCH_DW(k_core_group_lanes, P, blocks, s);
-        HCA_DISPATCH_DW(k_core_group_deferred, P, blocks, s);
+        HCA_DISPATCH_DW(k_core_group_rest, P, blocks, s);
         return;
     }
     if (P.m > 1) HCA_DISPATCH_DW(k_core_chunks, P, blocks, s);

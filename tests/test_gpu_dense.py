@@ -54,3 +54,28 @@ def test_long_lists_in_a_small_array(ctx, d, monkeypatch):  # noqa: F811
     got, st = gpu_labels(ctx, pts, eps, 5, stats=True)
     assert np.array_equal(got, want)
     assert st["list_overflow"] == 0, st
+
+
+@pytest.mark.parametrize("slab", ["0", "16", None])
+@pytest.mark.parametrize("budget", ["16", "256"])
+def test_points_left_by_the_lanes(ctx, slab, budget, monkeypatch):  # noqa: F811
+    """Core marking by eight lanes per point at small sizes: few and nearly all
+    points left to the chunks, no lists, and lists that overflow."""
+    import oracle
+    from paper_1912_00323_amd.datagen import make_blobs, quantise
+    from test_gpu import gpu_labels
+    monkeypatch.setenv("HCA_SMALL", "0")
+    monkeypatch.setenv("HCA_CORE_LANES", "1")
+    monkeypatch.setenv("HCA_CORE_BUDGET", budget)
+    if slab:
+        monkeypatch.setenv("HCA_LIST_SLAB", slab)
+    if budget == "16":
+        monkeypatch.setenv("HCA_WAVE_BLOCKS", "8")          # many units per wave
+    for d, std, f, mp in ((5, 0.03, 0.5, 4), (6, 0.2, 0.55, 9), (6, 0.01, 0.6, 40), (8, 0.02, 0.75, 10), (7, 0.3, 0.3, 2)):
+        pts = quantise(make_blobs(np.random.default_rng(mp + d), 5003, d, 4, std, 0.15), 12)
+        eps = std * np.sqrt(2 * d) * f * 2 ** 12
+        print(f"[case] d={d} std={std} mp={mp} slab={slab} budget={budget}", flush=True)
+        want, counts, _ = oracle.dbscan(pts, eps, mp, details=True)
+        got, core = gpu_labels(ctx, pts, eps, mp, core=True)
+        assert np.array_equal(core.astype(bool), counts >= mp), (d, mp)
+        assert np.array_equal(got, want), (d, mp)
