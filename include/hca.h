@@ -103,8 +103,8 @@ typedef struct {
     int64_t tests_merge;      /* between neighbouring cubes or groups */
     int64_t tests_border;
     int64_t tests_intra;      /* inside search groups (m > 1) */
-    int32_t packed_rows;      /* d > 8: 1 if rows were packed as byte planes (every span below 2^15 and the
-                               * squared spans below 2^31 in all) */
+    int32_t packed_rows;      /* d > 8: 1 if rows were packed as int16 pairs and byte planes (every span below
+                               * 2^15 and the squared spans below 2^31 in all) */
     int32_t key_axes;         /* d > 8: axes spanned by the search-group key (0 for d <= 8) */
     int64_t core_rest;        /* points left undecided by the first core-marking pass (its
                                * candidate budget spent) and walked by a second: d > 8, and

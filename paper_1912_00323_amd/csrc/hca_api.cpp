@@ -667,6 +667,7 @@ void carve_ws(Carver &cv, Plan &P, SortBuffers &B, const Sizes &Z, uint32_t **ze
         P.rec = cv.take<uint32_t>((size_t)kRec * n);
         P.nrec = cv.take<uint8_t>(n);
         P.blist = P.hd_list + n;
+        P.spts16 = P.hd16 ? cv.take<uint32_t>((size_t)n * (P.sd / 2)) : nullptr;
         if (P.hd_steps) {
             P.planes = cv.take<int32_t>((size_t)n * 16 * P.hd_steps);
             P.nnorm = cv.take<int32_t>(n);
@@ -861,7 +862,7 @@ void fill_stats(hca_ctx *ctx, const Plan &P, hca_stats *stats)
         stats->wide = P.wide;
         stats->dense_table = (int32_t)P.dense;
         stats->list_overflow = (int32_t)hc->nbr_overflow;
-    stats->packed_rows = P.planes != nullptr ? 1 : 0;
+    stats->packed_rows = P.spts16 != nullptr ? 1 : 0;
     stats->key_axes = P.hd ? (int32_t)P.kd : 0;
     stats->core_rest = P.hd ? (int64_t)hc->hd_left[0] : P.core_list && P.m == 1 ? (int64_t)hc->n_defer : 0;
 }
@@ -1026,12 +1027,14 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
     P.passes = sort_passes(P.key_bits, true);
     P.digit_bits = (P.key_bits + P.passes - 1) / P.passes;
     P.wide = reach >= ((unsigned __int128)1 << 31) ? 1 : 0;
-    // byte planes when every span is below 2^15 and sums fit 32 bits
+    // packed int16 rows and byte planes when every span is below 2^15 and sums fit 32 bits
     // (HCA_PACKED=0 turns them off)
     bool narrow16 = !P.wide;
     for (int k = 0; k < d; k++) narrow16 = narrow16 && mx[k] - mn[k] < (1ll << 15);
     if (const char *e = std::getenv("HCA_PACKED")) narrow16 = narrow16 && std::strcmp(e, "0") != 0;
+    P.hd16 = narrow16 ? 1u : 0u;
     P.hd_steps = !narrow16 ? 0u : d <= 32 ? 1u : 2u;
+    P.hd_tiles = P.hd_steps != 0;
     plan_hd_passes(P);
     P.list_w = 3;
     Sizes Z;
@@ -1046,6 +1049,13 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
     // 3. the launch sequence; lists that did not fit: again with 4x the room
     while (true) {
         st = ensure(ctx, &ctx->ws, &ctx->ws_size, ws_bytes(P, Z), "workspace");
+        if (st && P.hd_steps) {
+            // without the memory for the planes: the rows alone
+            P.hd_steps = 0;
+            P.planes = nullptr;
+            ctx->err.clear();
+            st = ensure(ctx, &ctx->ws, &ctx->ws_size, ws_bytes(P, Z), "workspace");
+        }
         if (st) return st;
         launch_hd_first(ctx, P, Z);
         HCA_HIP(hipGetLastError(), "kernel launch");

@@ -20,10 +20,20 @@
 
 namespace hca {
 
-// A staged point in LDS: its int32 coordinates, then (plane form) its row of
-// byte planes and its negated squared norm.
-constexpr int kOwnPlanes = kMaxDimHigh, kOwnNorm = kMaxDimHigh + kMaxDimHigh / 2;
-constexpr int kOwnStride = kOwnNorm + 4;
+// A staged point in LDS: its int32 coordinates, then (packed form) its
+// coordinates less the origin as int16 pairs.
+constexpr int kOwnStride = kMaxDimHigh + kMaxDimHigh / 2;
+
+typedef short short2_t __attribute__((ext_vector_type(2)));
+
+// acc + (a.lo - b.lo)^2 + (a.hi - b.hi)^2 for two packed int16 pairs (their
+// differences fit int16: every span is below 2^15).
+__device__ __forceinline__ int32_t sq_dot16(uint32_t a, uint32_t b, int32_t acc)
+{
+    const short2_t d = __builtin_bit_cast(short2_t, a) - __builtin_bit_cast(short2_t, b);
+    return __builtin_amdgcn_sdot2(d, d, acc, false);
+}
+
 
 // ---------------------------------------------------------------------------
 // Byte planes.  When every span is below 2^15 and the squared spans add up to
@@ -85,25 +95,25 @@ __global__ __launch_bounds__(kBlock) void k_hd_planes(Plan P)
 
 // ---------------------------------------------------------------------------
 // Point box of every group over all axes.  Groups are very uneven (one point
-// to tens of thousands), so the points are cut into chunks of kBoxChunk and a
+// to tens of thousands), so the points are cut into chunks (box_chunk) and a
 // wave takes the boxes of the stretches of groups in its chunk; a group that
 // lies in several chunks is folded together with atomics.  (54 axes, 3.85M
 // points: 5.3 ms with a wave per group, 0.38 ms this way.)
 // ---------------------------------------------------------------------------
-constexpr uint32_t kBoxChunk = kWave;
+__device__ __forceinline__ uint32_t box_chunk(const Plan &) { return (uint32_t)kWave; }
 
 // Before it: backward list counters cleared, "no core cube yet" and "one
 // root" for every group, and an empty box for the groups of several chunks.
 __global__ __launch_bounds__(kBlock) void k_hd_group_init(Plan P)
 {
     if (box_missed(P)) return;
-    const uint32_t sd = P.sd, ng = ld_agent32(&P.ctr->n_groups);
+    const uint32_t sd = P.sd, ng = ld_agent32(&P.ctr->n_groups), per = box_chunk(P);
     for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < ng; g += gridDim.x * kBlock) {
         st_agent32(P.nbr_bcount + g, 0u);
         st_agent32(P.nbr_bcursor + g, 0u);
         st_agent32(P.gcube + g, kNone);
         P.unified[g] = 1;
-        if (P.group_start[g] / kBoxChunk == (P.group_start[g + 1] - 1) / kBoxChunk) continue;
+        if (P.group_start[g] / per == (P.group_start[g + 1] - 1) / per) continue;
         uint32_t *box = (uint32_t *)(P.gbox + (uint64_t)g * 2 * sd);
         for (uint32_t e = 0; e < sd; e++) {
             st_agent32(box + e, (uint32_t)INT32_MAX);
@@ -118,10 +128,10 @@ __global__ __launch_bounds__(kBlock) void k_hd_group_box(Plan P)
     // lane (row, axis): kWave / sd rows at a time
     const uint32_t l = lane_id(), sd = P.sd, rows = kWave / sd, row = l / sd, axis = l - row * sd;
     const bool in = row < rows;
-    const uint32_t chunks = (P.n + kBoxChunk - 1) / kBoxChunk;
+    const uint32_t per = box_chunk(P), chunks = (P.n + per - 1) / per;
     const WaveRange hca_wr_ = wave_range(P.order);
     HCA_FOR_UNITS(u, chunks) {
-        const uint32_t c0 = u * kBoxChunk, c1 = min(P.n, c0 + kBoxChunk);
+        const uint32_t c0 = u * per, c1 = min(P.n, c0 + per);
         const uint32_t pg = P.group_of[P.cell_of[min(c0 + l, c1 - 1)]];
         const uint32_t pg0 = P.group_start[pg], pg1 = P.group_start[pg + 1];
         for (uint32_t s = c0; s < c1;) {
@@ -153,7 +163,7 @@ __global__ __launch_bounds__(kBlock) void k_hd_group_box(Plan P)
             }
             if (l < sd) {
                 int32_t *box = P.gbox + (uint64_t)g * 2 * sd;
-                if (g0 / kBoxChunk == (g1 - 1) / kBoxChunk) {
+                if (g0 / per == (g1 - 1) / per) {
                     box[l] = l0;
                     box[sd + l] = h0;
                 } else {
@@ -387,13 +397,12 @@ __device__ __forceinline__ void hd_stage(const Plan &P, uint32_t pc, uint32_t np
         const uint32_t k = i / sd, e = i - k * sd;
         own[k][e] = P.spts[(uint64_t)(pc + min(k, np - 1)) * sd + e];
     }
-    if (P.planes) {
-        const uint32_t pw = 16u * P.hd_steps;             // words of a row of planes
-        for (uint32_t i = lane_id(); i < kPch * pw; i += kWave) {
-            const uint32_t k = i / pw, e = i - k * pw;
-            own[k][kOwnPlanes + e] = P.planes[(uint64_t)(pc + min(k, np - 1)) * pw + e];
+    if (P.spts16) {
+        const uint32_t hw = sd >> 1;
+        for (uint32_t i = lane_id(); i < kPch * hw; i += kWave) {
+            const uint32_t k = i / hw, e = i - k * hw;
+            own[k][kMaxDimHigh + e] = (int32_t)P.spts16[(uint64_t)(pc + min(k, np - 1)) * hw + e];
         }
-        if (lane_id() < (uint32_t)kPch) own[lane_id()][kOwnNorm] = P.nnorm[pc + min(lane_id(), np - 1)];
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -401,13 +410,12 @@ __device__ __forceinline__ void hd_stage(const Plan &P, uint32_t pc, uint32_t np
 // The 8 rows at sorted positions pos[0..8) (wave-uniform) into LDS.
 __device__ __forceinline__ void hd_stage_at(const Plan &P, const uint32_t *pos, int32_t (*own)[kOwnStride])
 {
-    const uint32_t sd = P.sd, l = lane_id(), pw = 16u * P.hd_steps;
+    const uint32_t sd = P.sd, l = lane_id();
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int k = 0; k < kPch; k++) {
         if (l < sd) own[k][l] = P.spts[(uint64_t)pos[k] * sd + l];
-        if (P.planes && l < pw) own[k][kOwnPlanes + l] = P.planes[(uint64_t)pos[k] * pw + l];
-        if (P.planes && l == 0) own[k][kOwnNorm] = P.nnorm[pos[k]];
+        if (P.spts16 && l < (sd >> 1)) own[k][kMaxDimHigh + l] = (int32_t)P.spts16[(uint64_t)pos[k] * (sd >> 1) + l];
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -483,12 +491,12 @@ __device__ __forceinline__ uint32_t hd_load_neighbours(const Plan &P, uint32_t g
 }
 
 // Row forms, fixed per call by the host, one kernel instance each: 32-bit
-// sums of int32 rows, 64-bit sums, or byte planes of up to 32 or 64 axes.
-constexpr int kRowNarrow = 0, kRowWide = 1, kRowPlanes1 = 2, kRowPlanes2 = 3;
+// sums of int32 rows, 64-bit sums, or packed int16 rows.
+constexpr int kRowNarrow = 0, kRowWide = 1, kRowPacked = 2;
 
 __host__ __device__ inline int row_form(const Plan &P)
 {
-    return P.wide ? kRowWide : !P.planes ? kRowNarrow : P.hd_steps == 1 ? kRowPlanes1 : kRowPlanes2;
+    return P.wide ? kRowWide : P.spts16 ? kRowPacked : kRowNarrow;
 }
 
 // Squared distances from the candidate row at sorted position pos to the 8
@@ -516,38 +524,33 @@ __device__ __forceinline__ void hd_dist(const Plan &P, const int32_t (*own)[kOwn
         }
 #pragma unroll
         for (int k = 0; k < kPch; k++) dd[k] = acc[k];
-    } else if constexpr (ROW == kRowPlanes1 || ROW == kRowPlanes2) {
-        // four axes per byte dot product, four products per word of a plane
-        constexpr int KS = ROW == kRowPlanes1 ? 1 : 2;
-        const uint4 *prow = reinterpret_cast<const uint4 *>(P.planes) + (uint64_t)pos * (4 * KS);
-        uint4 v[4 * KS];
+    } else if constexpr (ROW == kRowPacked) {
+        // packed int16 coordinates: two axes per subtract and dot step
+        const uint4 *prow = reinterpret_cast<const uint4 *>(P.spts16 + (uint64_t)pos * (P.sd >> 1));
+        const uint32_t n8 = P.sd >> 3;
+        uint4 v[kMaxDimHigh / 8];
 #pragma unroll
-        for (int e = 0; e < 4 * KS; e++) v[e] = prow[e];
-        const int32_t nq = P.nnorm[pos];
-#pragma unroll
-        for (int k = 0; k < kPch; k++) {
-            int32_t hh = 0, hl = 0, ll = 0;
-#pragma unroll
-            for (int half = 0; half < 2; half++)
-#pragma unroll
-                for (int st = 0; st < KS; st++) {
-                    const int e = half * 2 * KS + st;
-                    const uint4 oh = reinterpret_cast<const uint4 *>(own[k] + kOwnPlanes)[e];
-                    const uint4 ol = reinterpret_cast<const uint4 *>(own[k] + kOwnPlanes)[e + KS];
-                    const uint32_t ch[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
-                    const uint32_t cl[4] = {v[e + KS].x, v[e + KS].y, v[e + KS].z, v[e + KS].w};
-                    const uint32_t ph[4] = {oh.x, oh.y, oh.z, oh.w}, pl[4] = {ol.x, ol.y, ol.z, ol.w};
-#pragma unroll
-                    for (int w = 0; w < 4; w++) {
-                        hh = __builtin_amdgcn_sdot4((int)ch[w], (int)ph[w], hh, false);
-                        hl = __builtin_amdgcn_sdot4((int)ch[w], (int)pl[w], hl, false);
-                        hl = __builtin_amdgcn_sdot4((int)cl[w], (int)ph[w], hl, false);
-                        ll = __builtin_amdgcn_sdot4((int)cl[w], (int)pl[w], ll, false);
-                    }
-                }
-            const uint32_t dot = ((((uint32_t)hh << 8) + (uint32_t)hl) << 8) + (uint32_t)ll;
-            dd[k] = -(int32_t)((uint32_t)own[k][kOwnNorm] + (uint32_t)nq + 2u * dot);
+        for (int e = 0; e < kMaxDimHigh / 8; e++) {
+            v[e] = make_uint4(0, 0, 0, 0);
+            if ((uint32_t)e < n8) v[e] = prow[e];
         }
+        int32_t acc[kPch];
+#pragma unroll
+        for (int k = 0; k < kPch; k++) acc[k] = 0;
+#pragma unroll
+        for (int e = 0; e < kMaxDimHigh / 8; e++) {
+            if ((uint32_t)e >= n8) continue;
+#pragma unroll
+            for (int k = 0; k < kPch; k++) {
+                const uint4 o = reinterpret_cast<const uint4 *>(own[k] + kMaxDimHigh)[e];
+                acc[k] = sq_dot16(v[e].x, o.x, acc[k]);
+                acc[k] = sq_dot16(v[e].y, o.y, acc[k]);
+                acc[k] = sq_dot16(v[e].z, o.z, acc[k]);
+                acc[k] = sq_dot16(v[e].w, o.w, acc[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kPch; k++) dd[k] = acc[k];
     } else {
         // the whole row in flight at once (one memory latency per candidate)
         int4 v[kMaxDimHigh / 4];
@@ -650,8 +653,10 @@ __device__ __forceinline__ void hd_tally(const Plan &P, bool in, uint32_t cell, 
 // First pass: chunks of 8 consecutive sorted points, each point looking at
 // up to P.hd_budget candidates; points still undecided are appended to
 // the list of the second pass.
+// The packed form is held to 96 registers (five waves per SIMD): some
+// spill, and the walk still gains from the extra wave.
 template <int ROW>
-__global__ __launch_bounds__(kBlock) void k_hd_core(Plan P)
+__global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ __align__(16) int32_t s_own[kWavesPerBlock][kPch][kOwnStride];
@@ -715,7 +720,7 @@ __global__ __launch_bounds__(kBlock) void k_hd_core(Plan P)
 
 // Second pass: chunks of 8 points of the list, walked to the end.
 template <int ROW>
-__global__ __launch_bounds__(kBlock) void k_hd_core_rest(Plan P)
+__global__ __launch_bounds__(kBlock, ROW == kRowPacked ? 5 : 1) void k_hd_core_rest(Plan P)
 {
     if (box_missed(P)) return;
     __shared__ __align__(16) int32_t s_own[kWavesPerBlock][kPch][kOwnStride];
@@ -1614,7 +1619,7 @@ static void launch_hd_core_tiles(const Plan &P, hipStream_t s)
     }
 }
 
-void launch_hd_planes(const Plan &P, hipStream_t s)
+static void launch_hd_planes(const Plan &P, hipStream_t s)
 {
     const uint64_t chunks = (uint64_t)P.n * 2 * P.hd_steps;
     const int pb = (int)std::min<uint64_t>((chunks + kBlock - 1) / kBlock, 4096);
@@ -1624,16 +1629,24 @@ void launch_hd_planes(const Plan &P, hipStream_t s)
 
 void launch_hd_core(const Plan &P, int blocks, hipStream_t s)
 {
-    switch (row_form(P)) {
-    case kRowWide:
-        hipLaunchKernelGGL(k_hd_core<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P);
-        hipLaunchKernelGGL(k_hd_core_rest<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P);
-        break;
-    case kRowPlanes1: launch_hd_core_tiles<1>(P, s); break;
-    case kRowPlanes2: launch_hd_core_tiles<2>(P, s); break;
-    default:
-        hipLaunchKernelGGL(k_hd_core<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
-        hipLaunchKernelGGL(k_hd_core_rest<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
+    if (P.planes && P.hd_tiles) {
+        launch_hd_planes(P, s);
+        if (P.hd_steps == 1) launch_hd_core_tiles<1>(P, s);
+        else launch_hd_core_tiles<2>(P, s);
+    } else {
+        switch (row_form(P)) {
+        case kRowWide:
+            hipLaunchKernelGGL(k_hd_core<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P);
+            hipLaunchKernelGGL(k_hd_core_rest<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P);
+            break;
+        case kRowPacked:
+            hipLaunchKernelGGL(k_hd_core<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P);
+            hipLaunchKernelGGL(k_hd_core_rest<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P);
+            break;
+        default:
+            hipLaunchKernelGGL(k_hd_core<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
+            hipLaunchKernelGGL(k_hd_core_rest<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
+        }
     }
     const int cb = (int)std::min<uint64_t>((P.n + kBlock - 1) / kBlock, 1024);
     hipLaunchKernelGGL(k_hd_gcore, dim3(cb), dim3(kBlock), 0, s, P);
@@ -1647,8 +1660,7 @@ void launch_hd_merge(const Plan &P, int blocks, hipStream_t s)
     hipLaunchKernelGGL(k_hd_need, dim3(blocks), dim3(kBlock), 0, s, P);
     switch (row_form(P)) {
     case kRowWide: hipLaunchKernelGGL(k_hd_merge<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P); break;
-    case kRowPlanes1: hipLaunchKernelGGL(k_hd_merge<kRowPlanes1>, dim3(blocks), dim3(kBlock), 0, s, P); break;
-    case kRowPlanes2: hipLaunchKernelGGL(k_hd_merge<kRowPlanes2>, dim3(blocks), dim3(kBlock), 0, s, P); break;
+    case kRowPacked: hipLaunchKernelGGL(k_hd_merge<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P); break;
     default: hipLaunchKernelGGL(k_hd_merge<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
     }
 }
@@ -1660,8 +1672,7 @@ void launch_hd_border(const Plan &P, int blocks, hipStream_t s)
     launch_border_list(P, s);
     switch (row_form(P)) {
     case kRowWide: hipLaunchKernelGGL(k_hd_border<kRowWide>, dim3(blocks), dim3(kBlock), 0, s, P); break;
-    case kRowPlanes1: hipLaunchKernelGGL(k_hd_border<kRowPlanes1>, dim3(blocks), dim3(kBlock), 0, s, P); break;
-    case kRowPlanes2: hipLaunchKernelGGL(k_hd_border<kRowPlanes2>, dim3(blocks), dim3(kBlock), 0, s, P); break;
+    case kRowPacked: hipLaunchKernelGGL(k_hd_border<kRowPacked>, dim3(blocks), dim3(kBlock), 0, s, P); break;
     default: hipLaunchKernelGGL(k_hd_border<kRowNarrow>, dim3(blocks), dim3(kBlock), 0, s, P);
     }
 }

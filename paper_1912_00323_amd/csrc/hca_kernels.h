@@ -46,7 +46,6 @@ void launch_labels(const Plan &P, uint64_t *status, uint32_t *ticket, void *tmp_
 // merging and border points
 void launch_bbox_hd(int d, const int32_t *pts, uint32_t n, int32_t *partial, int blocks, hipStream_t s);
 void launch_sort_hd(Plan &P, SortBuffers &B, hipStream_t s);
-void launch_hd_planes(const Plan &P, hipStream_t s);   // byte planes and norms of the sorted rows
 void launch_hd_lists(const Plan &P, int blocks, hipStream_t s);
 void launch_hd_core(const Plan &P, int blocks, hipStream_t s);
 void launch_hd_merge(const Plan &P, int blocks, hipStream_t s);

@@ -174,10 +174,14 @@ struct Plan {
     uint8_t *nrec;              // [n] neighbours found when at most kRec (then all are recorded), else
                                 // kRec + 1; 0 for points of cubes with minPts points
     uint32_t *blist;            // [n] non-core points whose neighbours were not all recorded (with rec)
-    // byte planes of the sorted points (hd, every span below 2^15 and 32-bit
-    // sums; else null): rows of 16 hd_steps words, and the negated squared
+    // hd, every span below 2^15 and 32-bit sums (else null): the sorted points
+    // less the origin as packed int16 pairs, for the walks over rows, and as
+    // byte planes, for the tiles: rows of 16 hd_steps words, and the negated squared
     // norms of the points less the centre
+    uint32_t hd16;              // packed rows wanted
+    uint32_t *spts16;           // [n][sd / 2]
     uint32_t hd_steps;          // 1 up to 32 axes, 2 above; 0: no planes
+    uint32_t hd_tiles;          // core marking by tiles on the planes (else walks over rows)
     int32_t *planes;            // [n][16 hd_steps]
     int32_t *nnorm;             // [n]
     uint64_t *hd_mask;          // [ceil(n / 64)] points a pass of core marking left undecided
