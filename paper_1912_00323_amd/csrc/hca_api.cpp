@@ -1034,7 +1034,6 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
     if (const char *e = std::getenv("HCA_PACKED")) narrow16 = narrow16 && std::strcmp(e, "0") != 0;
     P.hd16 = narrow16 ? 1u : 0u;
     P.hd_steps = !narrow16 ? 0u : d <= 32 ? 1u : 2u;
-    P.hd_tiles = P.hd_steps != 0;
     plan_hd_passes(P);
     P.list_w = 3;
     Sizes Z;
@@ -1059,10 +1058,15 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
         if (st) return st;
         launch_hd_first(ctx, P, Z);
         HCA_HIP(hipGetLastError(), "kernel launch");
-        HCA_HIP(hipMemcpyAsync(ctx->pinned, &P.ctr->nbr_overflow, sizeof(uint32_t), hipMemcpyDeviceToHost, s),
-                "list check");
+        HCA_HIP(hipMemcpyAsync(ctx->pinned, P.ctr, offsetof(Counters, hmask), hipMemcpyDeviceToHost, s), "list check");
         HCA_HIP(hipStreamSynchronize(s), "list sync");
-        if (*(const uint32_t *)ctx->pinned == 0) break;
+        const Counters *found = (const Counters *)ctx->pinned;
+        // a point alone in its group (or every point a core point) costs a tile
+        // as much as 64 (us, core, rows and tiles: 9 axes, 272k points in 269k
+        // groups 417 and 1248, 10 axes, 108k in as many 187 and 497; from 1.5
+        // points a group on the tiles win: 86 and 104, 193 and 360)
+        P.hd_tiles = P.hd_steps && min_pts > 1 && 4ull * n >= 5ull * found->n_groups;
+        if (found->nbr_overflow == 0) break;
         if (P.nbr_cap >= kHdListMax)
             return fail(ctx, HCA_E_NOMEM, "neighbour lists need more than 2^30 entries");
         P.nbr_cap = (uint32_t)std::min<uint64_t>(4ull * P.nbr_cap, kHdListMax);

@@ -100,7 +100,11 @@ __global__ __launch_bounds__(kBlock) void k_hd_planes(Plan P)
 // lies in several chunks is folded together with atomics.  (54 axes, 3.85M
 // points: 5.3 ms with a wave per group, 0.38 ms this way.)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t box_chunk(const Plan &) { return (uint32_t)kWave; }
+// Up to 2^15 points the chunks are of 16, so that there are waves enough for
+// groups of one or two points (us, lists, with 64 and 16: 16 axes, 23k points
+// 689 and 664, 27 axes, 9k 253 and 230; few large groups share more atomics: 12
+// axes, 31k points in 6 groups 31 and 49).
+__device__ __forceinline__ uint32_t box_chunk(const Plan &P) { return P.n < (1u << 15) ? 16u : (uint32_t)kWave; }
 
 // Before it: backward list counters cleared, "no core cube yet" and "one
 // root" for every group, and an empty box for the groups of several chunks.
