@@ -259,12 +259,28 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
 
 // Exact merging of cubes goes by the neighbours that core marking records,
 // without representatives: over neighbour lists (three and four axes), and
-// over small stencils with the lane walk (one and two).
-void plan_linked(Plan &P)
+// over small stencils with the lane walk (one and two), there from 1.5M points
+// on where few points lie in sparse cubes, which are the ones that records
+// link.  At most minPts - 1 points of each of the box's `cubes` cubes do, so
+// that is certain from 8 minPts points per cube on (us, kernels of a call,
+// representatives and records: 2-D 16M points in 126k cubes 1448 and 1124, 1.6M
+// in 20k 352 and 280; but 4M in 126k 556 and 598, 2.8M in 670k 1370 and 1917,
+// where linking all the sparse points' records alone takes 990).
+void plan_linked(Plan &P, double cubes, int32_t min_pts)
 {
     P.linked = P.m == 1 && !P.rep_only && env_record() &&
-               (P.d <= 2 ? P.core_lanes == 1 && P.n_off <= (uint32_t)kWave && P.n >= (3u << 19) : P.d <= 4 && P.list_w);
+               (P.d <= 2 ? P.core_lanes == 1 && P.n_off <= (uint32_t)kWave && P.n >= (3u << 19) &&
+                               (double)P.n >= 8.0 * min_pts * cubes
+                         : P.d <= 4 && P.list_w);
     if (P.linked) P.n_dir = 0;
+}
+
+// Cubes of the box, as wide as the key fields allow (one set's).
+double box_cubes(const Plan &P)
+{
+    double cubes = 1;
+    for (int k = 0; k < P.d; k++) cubes *= (double)P.gmax[k] + 1.0;
+    return cubes;
 }
 
 // Radix passes for a key of key_bits bits, digits no wider than the key
@@ -1195,9 +1211,7 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
 bool few_cubes(const Plan &P, uint32_t n, int d)
 {
     if (d != 3 || n >= (1u << 18)) return false;
-    double cubes = 1;
-    for (int k = 0; k < d; k++) cubes *= (double)P.gmax[k] + 1.0;
-    return cubes <= (n < 100000 ? 16.0 : 4.0) * n;
+    return box_cubes(P) <= (n < 100000 ? 16.0 : 4.0) * n;
 }
 
 // A geometry's offset and direction tables to the device.
@@ -1436,7 +1450,7 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
     const bool no_lists = few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats;
     P.list_w = P.m == 1 && !no_lists ? cube_list_width(d, G.radius, n_off) : 0;
     plan_core_lanes(P, G.radius);
-    plan_linked(P);
+    plan_linked(P, box_cubes(P), min_pts);
     Sizes Z;
     plan_sizes(P, gbits, stats != nullptr && ctx->prof != -1, stats != nullptr, &Z);
     plan_prefix(P, gbits, &Z);
@@ -1786,7 +1800,9 @@ void batch_plan(BatchGroup &g, char *db, const Tune *t)
     for (int32_t v : g.radius) rmax = std::max(rmax, v);
     P.list_w = cube_list_width(d, rmax, P.n_off, t);
     plan_core_lanes(P, rmax, t);
-    plan_linked(P);
+    uint32_t most = 1;
+    for (const SegParam &sp : g.par) most = std::max(most, sp.min_pts);
+    plan_linked(P, box_cubes(P) * (double)ns, (int32_t)std::min<uint32_t>(most, INT32_MAX));
     plan_sizes(P, P.key_bits, false, false, &g.Z, t);
     plan_prefix(P, P.key_bits, &g.Z, t);
 }

@@ -79,3 +79,16 @@ def test_points_left_by_the_lanes(ctx, slab, budget, monkeypatch):  # noqa: F811
         got, core = gpu_labels(ctx, pts, eps, mp, core=True)
         assert np.array_equal(core.astype(bool), counts >= mp), (d, mp)
         assert np.array_equal(got, want), (d, mp)
+
+
+@pytest.mark.parametrize("n,eps,mp", [(1_600_000, 0.012, 4), (1_600_000, 0.03, 9), (1_600_000, 0.0012, 8)])
+def test_planes_by_records_and_representatives(ctx, n, eps, mp):  # noqa: F811
+    """Large planar sets on both sides of the rule between merging from records
+    and by representatives, against the grid oracle."""
+    import oracle
+    import torch
+    from paper_1912_00323_amd.datagen import make_blobs, quantise
+    pts = quantise(make_blobs(np.random.default_rng(n + mp), n, 2, 30, 0.02, 0.1), 15)
+    print(f"[case] eps={eps} mp={mp}", flush=True)
+    got = ctx.cluster(torch.from_numpy(np.ascontiguousarray(pts, np.int32)).cuda(), eps * 2 ** 15, mp).cpu().numpy()
+    assert np.array_equal(got, oracle.hca_grid(pts, eps * 2 ** 15, mp, threads=8))
