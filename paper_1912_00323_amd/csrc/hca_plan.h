@@ -11,8 +11,10 @@ constexpr int kMaxDim = 8;                     // axes of the packed cube key
 constexpr int kMaxDimHigh = 64;                // axes of a point (more than 8: hashed cubes)
 constexpr uint32_t kLabelShift = 15;          // labels are binned by ranges of 2^15 input positions,
 constexpr uint32_t kLabelRanges = 1024;       // at most so many,
-constexpr uint32_t kLabelSplit = 3u << 20;    // from so many points on (labels phase, us, written at once and binned:
-                                              // 2M points 45 and 61, 4M 74 and 64, 8M 191 and 103, 16M 389 and 190)
+constexpr uint32_t kLabelSplit = 6u << 20;    // from so many points on (2-D, labels phase, us, written at once and
+                                              // binned: points in random order 4M 70 and 58, 8M 186 and 97, 16M 385
+                                              // and 183; sorted along one axis 4M 38 and 73, 8M 73 and 104, 16M 127
+                                              // and 185, where the rest of the call makes up for it)
 constexpr int kRec = 16;                       // neighbours recorded per point by core marking
 // More than kMaxDim axes: candidates a point of the first core pass looks at
 // before it is left to the next pass; the host may lower it per call.

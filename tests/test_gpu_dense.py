@@ -92,3 +92,23 @@ def test_planes_by_records_and_representatives(ctx, n, eps, mp):  # noqa: F811
     print(f"[case] eps={eps} mp={mp}", flush=True)
     got = ctx.cluster(torch.from_numpy(np.ascontiguousarray(pts, np.int32)).cuda(), eps * 2 ** 15, mp).cpu().numpy()
     assert np.array_equal(got, oracle.hca_grid(pts, eps * 2 ** 15, mp, threads=8))
+
+
+@pytest.mark.parametrize("n", [6 << 20, 6_400_001])
+def test_labels_in_and_out_of_order(ctx, n):  # noqa: F811
+    """Binned labels where some tiles' points lie in order and write their
+    labels at once, and others' do not, with core flags: the grid oracle's."""
+    import oracle
+    import torch
+    rng = np.random.default_rng(n)
+    pts = rng.integers(0, 1 << 15, size=(n, 2))
+    pts[: n // 2] = (pts[: n // 2] // 800) * 800 + rng.integers(0, 60, size=(n // 2, 2))
+    pts = pts[rng.permutation(n)]
+    k = n // 3                                              # a third in the order of its cubes
+    key = (pts[:k, 0] // 20) * 4096 + pts[:k, 1] // 20
+    pts[:k] = pts[:k][np.argsort(key, kind="stable")]
+    pts = np.ascontiguousarray(pts, np.int32)
+    got, core = ctx.cluster(torch.from_numpy(pts).cuda(), 30.0, 12, core=True)
+    want, flags, _ = oracle.hca_grid(pts, 30.0, 12, threads=8, details=True)
+    assert np.array_equal(core.cpu().numpy(), flags.astype(np.uint8))
+    assert np.array_equal(got.cpu().numpy(), want)
