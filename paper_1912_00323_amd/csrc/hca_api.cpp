@@ -265,12 +265,14 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
 // that is certain from 8 minPts points per cube on (us, kernels of a call,
 // representatives and records: 2-D 16M points in 126k cubes 1448 and 1124, 1.6M
 // in 20k 352 and 280; but 4M in 126k 556 and 598, 2.8M in 670k 1370 and 1917,
-// where linking all the sparse points' records alone takes 990).
+// where linking all the sparse points' records alone takes 990).  One axis: up
+// to 1024 cubes, as the finds walk along long rows of them (27.8k cubes, merge
+// 224 and 493; 4.1k 96 and 124).
 void plan_linked(Plan &P, double cubes, int32_t min_pts)
 {
     P.linked = P.m == 1 && !P.rep_only && env_record() &&
                (P.d <= 2 ? P.core_lanes == 1 && P.n_off <= (uint32_t)kWave && P.n >= (3u << 19) &&
-                               (double)P.n >= 8.0 * min_pts * cubes
+                               (double)P.n >= 8.0 * min_pts * cubes && (P.d == 2 || cubes <= 1024.0)
                          : P.d <= 4 && P.list_w);
     if (P.linked) P.n_dir = 0;
 }
