@@ -1205,11 +1205,13 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
     return HCA_OK;
 }
 
-// Three axes, cubes: data whose box holds few cubes per point find their
-// neighbours in the direct table sooner than in lists, whose five launches a
-// small call does not win back: at most 16 cubes per point under 100k points
-// (calls 1.2 to 1.4 times as fast), at most 4 under 2^18 (1.14); larger calls
-// are slower without lists (0.8).
+// Three axes, cubes: small calls whose box holds few cubes per point mark their
+// core points by a wave per cube over the lists instead of a lane per point of
+// a sparse cube: at most 16 cubes per point under 100k points, at most 4 under
+// 2^18 (us a call, lanes and waves: blobs of 29k points 324 and 232, 87k 392
+// and 272, 170k 546 and 349).  Without lists at all such blobs take 213, 256
+// and 483, but uniform points, whose merging over the stencil grows with the
+// cubes, twice as long (154k points 1176, with lists and waves 707).
 bool few_cubes(const Plan &P, uint32_t n, int d)
 {
     if (d != 3 || n >= (1u << 18)) return false;
@@ -1449,9 +1451,9 @@ hca_status run(hca_ctx *ctx, const int32_t *points, int64_t n64, int32_t d, doub
                                           "and representatives enabled");
         P.rep_only = 1;
     }
-    const bool no_lists = few_cubes(P, n, d) && ctx->geo_mode == 0 && !stats;
-    P.list_w = P.m == 1 && !no_lists ? cube_list_width(d, G.radius, n_off) : 0;
+    P.list_w = P.m == 1 ? cube_list_width(d, G.radius, n_off) : 0;
     plan_core_lanes(P, G.radius);
+    if (P.core_lanes == 2 && few_cubes(P, n, d) && ctx->geo_mode == 0 && !std::getenv("HCA_CORE_LANES")) P.core_lanes = 0;
     plan_linked(P, box_cubes(P), min_pts);
     Sizes Z;
     plan_sizes(P, gbits, stats != nullptr && ctx->prof != -1, stats != nullptr, &Z);

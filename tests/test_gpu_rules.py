@@ -1,0 +1,38 @@
+"""GPU parity around the rules that pick how a call of three axes marks its core
+points: sizes and densities that lie on either side (checked here against the
+rules themselves), against the oracle's DBSCAN definition."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1912_00323_amd.datagen import make_blobs, quantise
+from test_gpu import ctx, gpu_labels  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def cubes_of_box(pts, eps):
+    side = oracle.grid_geometry(eps, pts.shape[1])[0]
+    return int(np.prod([int(s) // side + 1 for s in pts.max(0).astype(np.int64) - pts.min(0)]))
+
+
+@pytest.mark.parametrize("n,eps,few", [(16_385, 0.03, True), (16_385, 0.012, False), (20_001, 0.03, True),
+                                       (20_001, 0.022, False), (30_000, 0.025, True)])
+@pytest.mark.parametrize("uniform", [False, True])
+def test_few_cubes(ctx, n, eps, few, uniform):  # noqa: F811
+    rng = np.random.default_rng(n)
+    pts = rng.integers(0, 1 << 14, size=(n, 3)).astype(np.int32) if uniform else \
+        np.clip(quantise(make_blobs(rng, n, 3, 9, 0.02, 0.15), 14), 0, (1 << 14) - 1)
+    pts[:2] = [[0, 0, 0], [(1 << 14) - 1] * 3]
+    eps *= 2 ** 14
+    cubes = cubes_of_box(pts, eps)
+    print(f"[case] n={n} cubes={cubes} ({cubes / n:.1f} per point)", flush=True)
+    assert (cubes <= 16 * n) == few
+    want, counts, _ = oracle.dbscan(pts, eps, 6, details=True)
+    got, core = gpu_labels(ctx, pts, eps, 6, core=True)
+    assert np.array_equal(core.astype(bool), counts >= 6)
+    assert np.array_equal(got, want)
+    got, core, _ = gpu_labels(ctx, pts, eps, 6, core=True, stats=True)
+    assert np.array_equal(core.astype(bool), counts >= 6) and np.array_equal(got, want)
