@@ -1104,12 +1104,14 @@ hca_status run_hd(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d, do
 }
 
 // ---- small calls -----------------------------------------------------------------
-// Points up to which a call is clustered by all pairs (hca_small.h), by
-// where the two paths meet on blobs (us, grid against all pairs: 1-D 8k 126,
-// 103, 12k 127, 137; 2-D 12k 177, 144, 16k 178, 193; 3-D 16k 343, 226; 4-D 16k
-// 476, 265; 8-D 16k 417, 292, wide distances 439, 474; 16-D 16k 656, 227).  Any
-// of the general path's test knobs keeps a call on that path; HCA_SMALL=k: up
-// to k points (0: never).
+// Points up to which a call is clustered by all pairs (hca_small.h), by where
+// the two paths meet on blobs in 32 bits and in 64, whose distances cost more,
+// and on lines of points in order (us, grid against all pairs: 1-D 8k 126, 103,
+// 12k 127, 137; 2-D 12k blobs 157, 152, wide 157, 183, a line 197, 158; 3-D 12k
+// 204, 163, wide 206, 206, 16k 207, 213 and 199, 294; 4-D 12k wide 274, 228, 16k
+// 290, 327; 8-D 12k wide 385, 325, 16k 439, 474; 16-D 16k 656, 227).  Any of
+// the general path's test knobs keeps a call on that path; HCA_SMALL=k: up to
+// k points (0: never).
 uint32_t small_limit(int32_t d)
 {
     for (const char *e : {"HCA_SEARCH", "HCA_RECORD", "HCA_PREFIX", "HCA_HD_BUDGET", "HCA_CORE_LANES", "HCA_CORE_BUDGET",
@@ -1117,7 +1119,7 @@ uint32_t small_limit(int32_t d)
                           "HCA_CUBE_LISTS", "HCA_LIST_SLAB", "HCA_WAVE_BLOCKS", "HCA_HASH_BITS", "HCA_PACKED"})
         if (std::getenv(e)) return 0;
     if (const char *e = std::getenv("HCA_SMALL")) return (uint32_t)std::min<long>(std::max(0l, std::atol(e)), kSmallMax);
-    return d == 1 ? 8192u : d == 2 || (d >= 5 && d <= kMaxDim) ? 12288u : kSmallMax;
+    return d == 1 ? 8192u : d == 2 ? 10240u : d == 4 ? 14336u : d <= kMaxDim ? 12288u : kSmallMax;
 }
 
 // A small call by all pairs.  *taken is false when the data are left to the
