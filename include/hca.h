@@ -353,10 +353,12 @@ hca_status hca_set_exact(hca_ctx *ctx, int32_t exact);
  * compares it with the one planned with.  When they differ, the results of
  * that launch are discarded and the call is planned from its own box and run
  * again, so results never depend on this setting.  Calls without allocation
- * (hca_cluster_noalloc) always wait for their own box.  HCA_E_INVAL for other
- * values or a NULL context.
- * hca_plan_reuse_counts: calls of this context planned ahead so far, and how
- * many of them ran again (HOST pointers owned by the caller). */
+ * (hca_cluster_noalloc) always wait for their own box.  Small calls, which are
+ * clustered by all pairs, lay nothing out by the box and never run again, but
+ * are counted alike.  HCA_E_INVAL for other values or a NULL context.
+ * hca_plan_reuse_counts: calls of this context whose box was expected to repeat
+ * so far, and how many of them had another (HOST pointers owned by the
+ * caller). */
 hca_status hca_set_plan_reuse(hca_ctx *ctx, int32_t on);
 hca_status hca_plan_reuse_counts(const hca_ctx *ctx, int64_t *calls, int64_t *reruns);
 

@@ -1160,27 +1160,22 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
     hca_status st = workspace(ctx, carve(nullptr));
     if (st) return st;
     carve(ws_base(ctx));
-    // up to eight axes the box takes part in plan reuse as that of any call
-    const bool ahead = d <= kMaxDim && ctx->reuse && ctx->box_armed && !ctx->fixed && ctx->box_n == n && ctx->box_d == d;
-    if (ahead) {
-        A.planned = 1;
-        for (int k = 0; k < d; k++) {
-            A.expect.mn[k] = ctx->box_mn[k];
-            A.expect.mx[k] = ctx->box_mx[k];
-        }
-    }
     launch_small(A, s);
     HCA_HIP(hipGetLastError(), "kernel launch");
     HCA_HIP(hipStreamSynchronize(s), "clustering sync");
     const uint32_t *report = ctx->check_host + kSmallReport;
     const uint32_t verdict = __atomic_load_n(report, __ATOMIC_ACQUIRE);
-    if (ahead) {
+    // Up to eight axes the box takes part in plan reuse as that of any call:
+    // it arms later calls and is counted.  (Nothing here is laid out by it, so
+    // the labels stand whatever box was expected.)
+    const int32_t *box = (const int32_t *)report + 1;
+    bool same = d <= kMaxDim && ctx->box_have && ctx->box_n == n && ctx->box_d == d;
+    for (int k = 0; k < d && same; k++) same = ctx->box_mn[k] == box[k] && ctx->box_mx[k] == box[d + k];
+    if (d <= kMaxDim && ctx->reuse && ctx->box_armed && !ctx->fixed && ctx->box_n == n && ctx->box_d == d) {
         ctx->reuse_calls++;
-        if (verdict) {
-            // planned from another box: run again from its own
+        if (verdict || !same) {
             ctx->box_armed = false;
             ctx->reuse_reruns++;
-            if (verdict == 1) return run_small(ctx, points, n, d, eps2, min_pts, labels, core_out, taken);
         }
     }
     if (verdict) {
@@ -1190,10 +1185,7 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
         return HCA_OK;
     }
     *taken = true;
-    if (!ahead && d <= kMaxDim) {
-        const int32_t *box = (const int32_t *)report + 1;
-        bool same = ctx->box_have && ctx->box_n == n && ctx->box_d == d;
-        for (int k = 0; k < d; k++) same = same && ctx->box_mn[k] == box[k] && ctx->box_mx[k] == box[d + k];
+    if (d <= kMaxDim) {
         ctx->box_armed = same;
         ctx->box_have = true;
         ctx->box_n = n;

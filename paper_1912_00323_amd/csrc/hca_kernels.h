@@ -65,8 +65,6 @@ struct SmallArgs {
     int32_t min_pts;
     int64_t eps2;
     uint64_t side;              // cube side of the general path (d <= kMaxDim)
-    uint32_t planned;           // compare the box with expect (d <= kMaxDim)
-    BoxExpect expect;
     uint32_t boxes;
     int32_t *partial;           // [boxes][2][d]
     uint32_t *adj;              // [ceil(n / 32)][np] bit k of word w of point i: point 32 w + k within eps

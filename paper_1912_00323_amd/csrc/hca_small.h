@@ -553,8 +553,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_join(SmallArgs A)
 // ---------------------------------------------------------------------------
 // Labels, by one block: the forest flattened, every member offered to its
 // root's smallest index, roots numbered in the order of those indices.  Also
-// the verdict for the host: 0 labels written, 1 the box differs from the one
-// planned with, 2 data for the general path.
+// the verdict for the host: 0 labels written, 1 data for the general path.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kSmallBlock) void k_small_labels(SmallArgs A)
 {
@@ -563,10 +562,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_labels(SmallArgs A)
     const uint32_t t = threadIdx.x, l = lane_id(), n = A.n, np = A.np;
     small_box(A, s_box);
     for (uint32_t i = t; i < np; i += kSmallBlock) s_min[i] = kNone;
-    uint32_t verdict = small_takes(A, s_box) ? 0u : 2u;
-    if (verdict == 0 && A.planned)
-        for (int k = 0; k < A.d; k++)
-            if (s_box[k] != A.expect.mn[k] || s_box[A.d + k] != A.expect.mx[k]) verdict = 1u;
+    const uint32_t verdict = small_takes(A, s_box) ? 0u : 1u;
     if (t < 2 * (uint32_t)A.d && A.d <= kMaxDim)
         __hip_atomic_store(A.report + 1 + t, (uint32_t)s_box[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (t == 0) __hip_atomic_store(A.report, verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -346,7 +346,7 @@ class Context:
         self._check(self._lib.hca_set_plan_reuse(self._ctx, 1 if on else 0))
 
     def plan_reuse_counts(self) -> tuple:
-        """(calls planned ahead, of which ran again) on this context."""
+        """(calls whose box was expected to repeat, of which had another) on this context."""
         calls, reruns = ctypes.c_int64(), ctypes.c_int64()
         self._check(self._lib.hca_plan_reuse_counts(self._ctx, ctypes.byref(calls), ctypes.byref(reruns)))
         return calls.value, reruns.value
