@@ -502,6 +502,21 @@ hca_status hip_fail(hca_ctx *ctx, hipError_t e, const char *what)
         if (e_ != hipSuccess) return hip_fail(ctx, e_, what); \
     } while (0)
 
+// Device memory; a failure leaves no error behind for the checks of later
+// launches, since calls may go on with less.  HCA_ALLOC_LIMIT=bytes: larger
+// allocations fail, as they do on a full device (for tests).
+hipError_t device_alloc(void **buf, size_t bytes)
+{
+    const char *limit = std::getenv("HCA_ALLOC_LIMIT");
+    if (limit && bytes > std::strtoull(limit, nullptr, 10)) bytes = 1ull << 60;
+    const hipError_t e = hipMalloc(buf, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *buf = nullptr;
+    }
+    return e;
+}
+
 hca_status ensure(hca_ctx *ctx, void **buf, size_t *have, size_t need, const char *what)
 {
     if (*have >= need) return HCA_OK;
@@ -511,15 +526,12 @@ hca_status ensure(hca_ctx *ctx, void **buf, size_t *have, size_t need, const cha
         *have = 0;
     }
     size_t want = need + need / 4;
-    hipError_t e = hipMalloc(buf, want);
+    hipError_t e = device_alloc(buf, want);
     if (e != hipSuccess) {
-        e = hipMalloc(buf, need);
+        e = device_alloc(buf, need);
         want = need;
     }
-    if (e != hipSuccess) {
-        *buf = nullptr;
-        return hip_fail(ctx, e, what);
-    }
+    if (e != hipSuccess) return hip_fail(ctx, e, what);
     *have = want;
     return HCA_OK;
 }
@@ -1157,8 +1169,11 @@ hca_status run_small(hca_ctx *ctx, const int32_t *points, uint32_t n, int32_t d,
         A.adj = cv.take<uint32_t>((size_t)((n + 31) / 32) * A.np);
         return cv.off;
     };
-    hca_status st = workspace(ctx, carve(nullptr));
-    if (st) return st;
+    if (workspace(ctx, carve(nullptr)) != HCA_OK) {
+        // no room for the bit matrix: the general path may need less
+        ctx->err.clear();
+        return HCA_OK;
+    }
     carve(ws_base(ctx));
     launch_small(A, s);
     HCA_HIP(hipGetLastError(), "kernel launch");
@@ -1540,6 +1555,7 @@ struct BatchGroup {
     // layout of the packed key shared by the data sets (from their boxes)
     uint32_t gw[kMaxDim] = {};
     bool wide = false;
+    bool half = false;                  // no memory for prefix ranges of more than half the axes
     uint32_t cubes_axis = 1;            // largest cube count along an axis of any data set
     Tune tune;                          // knobs of its launch sequence
     std::string tune_key;               // what the autotuner's cache knows it by
@@ -1802,7 +1818,7 @@ void batch_plan(BatchGroup &g, char *db, const Tune *t)
     for (const SegParam &sp : g.par) most = std::max(most, sp.min_pts);
     plan_linked(P, box_cubes(P) * (double)ns, (int32_t)std::min<uint32_t>(most, INT32_MAX));
     plan_sizes(P, P.key_bits, false, false, &g.Z, t);
-    plan_prefix(P, P.key_bits, &g.Z, t);
+    plan_prefix(P, P.key_bits, &g.Z, t, g.half);
 }
 
 hca_status run_sets(hca_ctx *ctx, const BatchSet *sets, int32_t nseg)
@@ -1848,6 +1864,16 @@ hca_status run_sets(hca_ctx *ctx, const BatchSet *sets, int32_t nseg)
                                s), "data-set table");
     }
     st = ensure(ctx, &ctx->ws, &ctx->ws_size, ws_need, "workspace");
+    if (st) {
+        ws_need = 0;
+        for (BatchGroup &g : groups) {
+            g.half = true;
+            batch_plan(g, db, nullptr);
+            ws_need = std::max(ws_need, ws_bytes(g.P, g.Z));
+        }
+        ctx->err.clear();
+        st = ensure(ctx, &ctx->ws, &ctx->ws_size, ws_need, "workspace");
+    }
     if (st) return st;
 
     // 5. one launch sequence per dimension, labels back to the caller; with
@@ -1948,6 +1974,12 @@ hca_status time_group(hca_batch *b, BatchGroup &g, const Tune &t, double *ms)
     char *db = (char *)b->dev;
     batch_plan(g, db, &t);
     hca_status st = ensure(ctx, &b->ws, &b->ws_size, ws_bytes(g.P, g.Z), "batch workspace");
+    if (st && !g.half) {
+        g.half = true;
+        batch_plan(g, db, &t);
+        ctx->err.clear();
+        st = ensure(ctx, &b->ws, &b->ws_size, ws_bytes(g.P, g.Z), "batch workspace");
+    }
     if (st) return st;
     double best = 1e30;
     for (int r = 0; r <= kTuneReps; r++) {
@@ -2143,13 +2175,21 @@ hca_status batch_plan_run(hca_batch *b)
         st = tune_group(b, g);
         if (st) return st;
     }
-    size_t off = 0;
-    for (BatchGroup &g : b->groups) {
-        batch_plan(g, db, &g.tune);
-        g.ws_off = off;
-        off = align256(off + ws_bytes(g.P, g.Z));
+    auto place = [&] {
+        size_t off = 0;
+        for (BatchGroup &g : b->groups) {
+            batch_plan(g, db, &g.tune);
+            g.ws_off = off;
+            off = align256(off + ws_bytes(g.P, g.Z));
+        }
+        return off;
+    };
+    st = ensure(ctx, &b->ws, &b->ws_size, place(), "batch workspace");
+    if (st) {
+        for (BatchGroup &g : b->groups) g.half = true;
+        ctx->err.clear();
+        st = ensure(ctx, &b->ws, &b->ws_size, place(), "batch workspace");
     }
-    st = ensure(ctx, &b->ws, &b->ws_size, off, "batch workspace");
     if (st) return st;
     for (BatchGroup &g : b->groups) {
         launch_sequence(ctx, g.P, g.Z, (char *)b->ws + g.ws_off, s);
