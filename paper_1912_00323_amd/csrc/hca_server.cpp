@@ -64,13 +64,15 @@ size_t footprint(int64_t n, int32_t d)
     return (size_t)((uint64_t)n * per_point + (1ull << 20));
 }
 
-// Estimated device time of a request alone (ms), from its rows and axes:
-// the per-point costs measured for the launch sequence on one MI355X (about
-// 0.4 ns per point for up to two axes, 2.7 for three, 5.6 for four, more
-// with search groups), used only to bound how much work one batch gathers.
+// Estimated device time that a request adds to a batch (ms), from its rows and
+// axes, used only to bound how much work one batch gathers.  Per point, measured
+// on one MI355X on blobs with radii of 0.005 to 0.03 of the cube (batches of six
+// sets of 400k points, single calls of 400k past four axes): 0.23 ns for two
+// axes, 0.55 for three, 1.6 for four, 2.6 to 3.8 for five to eight, 6 to 21
+// for twelve to 54.
 double estimate_ms(int64_t n, int32_t d)
 {
-    const double ns_per_pt = d <= 2 ? 0.4 : d == 3 ? 2.7 : d == 4 ? 5.6 : d <= 8 ? 12.0 : 200.0;
+    const double ns_per_pt = d <= 2 ? 0.25 : d == 3 ? 0.6 : d == 4 ? 1.7 : d <= 8 ? 3.0 : d <= 32 ? 9.0 : 18.0;
     return 0.02 + (double)n * ns_per_pt * 1e-6;
 }
 
