@@ -232,9 +232,9 @@ uint32_t env_core_budget()
 // Groups of several cubes: eight lanes per point and 256 candidates, against
 // one wave per four points (us, 5-D 1.2M points 804 -> 516, 8-D 500k 417 -> 320,
 // 6-D 400k 327 -> 170, 4-D 1M 272 -> 136).  Up to five axes and 2^18 points,
-// past five and 18k, the chunks stay, whose waves finish sooner when there are
-// few (5-D 100k 97, the lanes 121; 8-D 17k 74, 81; 7-D 15k 62, 71; but 8-D 20k
-// 88, 68, 7-D 61k 89, 75, 98k 211, 107), and past
+// past five and 2^16, the chunks stay, whose waves finish sooner when there are
+// few (5-D 100k 97, the lanes 121; 8-D 24k 65, 84, 27k 70, 95, 50k 94, 93; 7-D
+// 98k 211, 107), and past
 // minPts 12, where the lanes run out of candidates (5-D 1.2M points, minPts
 // 16: 1187, 1798).  HCA_CORE_LANES=1: the lanes whatever the sizes.
 constexpr int32_t kOctMinPts = 12;
@@ -250,7 +250,7 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
     }
     const char *force = std::getenv("HCA_CORE_LANES");
     if (P.m > 1 && !P.hd && want &&
-        ((P.n >= (P.d > 5 ? 9u << 11 : 1u << 18) && P.min_pts <= kOctMinPts) || (force && !std::strcmp(force, "1"))))
+        ((P.n >= (P.d > 5 ? 1u << 16 : 1u << 18) && P.min_pts <= kOctMinPts) || (force && !std::strcmp(force, "1"))))
         P.core_lanes = 3;
     P.core_budget = std::getenv("HCA_CORE_BUDGET") || P.core_lanes < 2 ? env_core_budget()
                     : P.core_lanes == 2                                ? 512u

@@ -1046,16 +1046,19 @@ __device__ __forceinline__ uint32_t count_walk(const Plan &P, uint32_t g, uint64
     const uint32_t l = lane_id();
     const uint32_t minpts = geo.min_pts;
     const uint32_t all = (1u << NP) - 1u;
+    constexpr uint32_t kSplitFrom = NP > 1 ? 4096 : 1024;
     const QBox<D> qb = chunk_box<D, NP>(pp, ~done);
     const NbrSrc src = nbr_source(P, g);
     for (uint32_t oc = 0; oc < src.slots && done != all; oc += kWave) {
         uint32_t total = load_neighbours<D>(P, g, gkey, src, oc, 0, false, qb, s_beg, s_pre, geo);
-        // Search groups of more than a chunk of points: their chunks in place of
-        // the groups, those within eps of the box only (a dense group holds
-        // thousands of points, most of them far from any one of its
-        // neighbours' points)
+        // Many candidates, in search groups of more than a chunk of points:
+        // their chunks in place of the groups, those within eps of the box only
+        // (a dense group holds thousands of points, most of them far from any
+        // one of its neighbours' points).  Fewer are sooner walked as they lie
+        // (8-D, 15k points in fours 104 us with all split, 97 from 1024 on, 77
+        // from 4096 on; 5-D, 1M points one by one 147, 147 and 152).
         const uint32_t a = s_beg[l], size = (l + 1 < (uint32_t)kWave ? s_pre[l + 1] : total) - s_pre[l];
-        const bool split = P.m > 1 && __ballot(size > (uint32_t)kWave) != 0;
+        const bool split = P.m > 1 && total >= kSplitFrom && __ballot(size > (uint32_t)kWave) != 0;
         uint32_t chunks = 1;
         __builtin_amdgcn_wave_barrier();
         if (split) {
