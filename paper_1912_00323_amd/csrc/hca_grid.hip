@@ -808,7 +808,13 @@ __global__ __launch_bounds__(kBlock) void k_nbr_lists(Plan P)
         for (uint32_t e = 0; e < P.paxes; e++) all *= P.list_w;
         for (uint32_t e = P.paxes; e < (uint32_t)D; e++) others *= P.list_w;
         nf = (all + 1) / 2;
-        pack = min((uint32_t)kListPack, kWave / nf);
+        // A wave takes several groups where their ranges are short. Where only
+        // the table's size kept the prefix from another axis they are long, and
+        // a wave takes one group: 5-D, prefixes of two axes, 45k points 87 -> 50
+        // us, 52k 94 -> 57; with prefixes as long as the offsets allow, several
+        // groups are the better (4-D 100k 100 us against 141, 7-D 300k 44, 71).
+        const bool cut = P.paxes + 1 < (uint32_t)D && all * P.list_w <= (uint32_t)kWave / 2;
+        pack = cut ? 1u : min((uint32_t)kListPack, kWave / nf);
         scan_max = max(64u, 2u * others);
         uint32_t off = 0, norm = 0, rank = 0;
         if (threadIdx.x < nf) {
