@@ -155,7 +155,11 @@ hca_status hca_cluster(hca_ctx *ctx, const int32_t *points, int64_t n, int32_t d
                        double eps, int32_t min_pts, int32_t *labels);
 
 /* As hca_cluster, and optionally: core (DEVICE pointer, n uint8 in input
- * order: 1 for core points) and stats (HOST pointer).  Either may be NULL. */
+ * order: 1 for core points) and stats (HOST pointer).  Either may be NULL.
+ * Labels do not depend on it, but the launch sequence may: calls that ask for
+ * stats do not take the all-pairs path for small calls, nor the search by
+ * groups that large sparse 4-D calls take, whose counters would not be those
+ * of cubes. */
 hca_status hca_cluster_ex(hca_ctx *ctx, const int32_t *points, int64_t n, int32_t d,
                           double eps, int32_t min_pts, int32_t *labels, uint8_t *core,
                           hca_stats *stats);
@@ -386,7 +390,9 @@ enum {
 
 /* Time phases of later calls with HIP events on the context's stream:
  * phase = -1 off (default), -2 every phase, k in [0, HCA_PHASES) phase k only.
- * HCA_E_INVAL for other values or a NULL context. */
+ * Small calls, which are clustered by all pairs and have no such phases, take
+ * the general path while this is on: their phase times are not a share of what
+ * they take without.  HCA_E_INVAL for other values or a NULL context. */
 hca_status hca_set_profiling(hca_ctx *ctx, int32_t phase);
 
 /* Milliseconds spent in each phase by the last call (0 for phases not timed):

@@ -2286,8 +2286,6 @@ __device__ __forceinline__ void queue_exact(const Plan &P, bool exact, uint32_t 
 constexpr int kMergeLanes = 16;          // lanes per cube
 constexpr uint32_t kLanePairs = 16;      // point pairs that a lane tests by itself
 
-// Cubes of core points only against the first cubes of their lists: 16
-// sampled pairs each, a lane per pair.
 // The forward offsets of a small stencil (at most 64 offsets) in a wave's
 // table, nearest first; returns their number.  Cubes are numbered in key
 // order, so B > A exactly when the first non-zero component is positive.
@@ -2317,6 +2315,8 @@ __device__ __forceinline__ uint32_t near_sample(uint32_t s, uint32_t size)
     return min(s < 2 ? s : size - min(size, s - 1u), size - 1u);
 }
 
+// Cubes of core points only against the first cubes of their lists (of a
+// plane: of their stencil): 16 sampled pairs each, a lane per pair.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_merge_near(Plan P)
 {
