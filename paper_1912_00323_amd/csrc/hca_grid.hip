@@ -616,8 +616,11 @@ __device__ __forceinline__ bool list_far(const Plan &P, const QBox<D> &ob, const
 // fit in all could still overflow in one wave, and every group was then
 // searched over the stencil: 7-D, 383k points, core marking 0.5 -> 15.5 ms.
 // Without shares every wave's first block queued up at one counter: 5-D, 149k
-// points, lists 45 -> 213 us.)
-constexpr uint32_t kListBlock = 1024;
+// points, lists 45 -> 213 us.)  The last blocks of all waves together stay under
+// a third of that part; within it larger blocks mean fewer moves (74 4-D sets,
+// 1.6M points in all: 1075 us with blocks of 1024, 1024 so, 999 with shares
+// alone).
+constexpr uint32_t kListBlock = 4096;
 struct ListRoom {
     uint32_t at, end;           // of the wave's share or block
     uint32_t pool;              // first entry past the shares
@@ -630,8 +633,8 @@ struct ListRoom {
 __device__ __forceinline__ bool list_room(const Plan &P, ListRoom &room, uint32_t &start, uint32_t k)
 {
     if (room.at + k <= room.end) return true;
-    const uint32_t have = room.at - start, need = have + k;
-    const uint32_t size = max(min(kListBlock, (P.nbr_cap - room.pool) / 4096u), need + kWave);
+    const uint32_t have = room.at - start, need = have + k, waves = gridDim.x * kWavesPerBlock;
+    const uint32_t size = max(min(kListBlock, (P.nbr_cap - room.pool) / (3u * waves)), need + kWave);
     uint32_t base = kNone;
     if (lane_id() == 0 && (uint64_t)room.pool + ld_agent32(&P.ctr->nbr_used) + need <= P.nbr_cap)
         base = room.pool + atomicAdd(&P.ctr->nbr_used, size);
