@@ -234,9 +234,9 @@ uint32_t env_core_budget()
 // 6-D 400k 327 -> 170, 4-D 1M 272 -> 136).  Up to five axes and 2^18 points,
 // past five and 2^16, the chunks stay, whose waves finish sooner when there are
 // few (5-D 100k 97, the lanes 121; 8-D 24k 65, 84, 27k 70, 95, 50k 94, 93; 7-D
-// 98k 211, 107), and past
-// minPts 12, where the lanes run out of candidates (5-D 1.2M points, minPts
-// 16: 1187, 1798).  HCA_CORE_LANES=1: the lanes whatever the sizes.
+// 98k 211, 107), and past minPts 12, where the lanes run out of candidates (5-D
+// 1.2M points, minPts 16: 1187, 1798).  The device has the last word, when it
+// knows the groups (by_octets).  HCA_CORE_LANES=1: the lanes whatever the sizes.
 constexpr int32_t kOctMinPts = 12;
 
 void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
@@ -248,10 +248,10 @@ void plan_core_lanes(Plan &P, int32_t radius, const Tune *t = nullptr)
         if (P.list_w == 0 && P.d <= 2 && radius <= kColR) P.core_lanes = 1;
         else if (P.list_w != 0 && P.d >= 3 && P.d <= 4) P.core_lanes = 2;
     }
-    const char *force = std::getenv("HCA_CORE_LANES");
-    if (P.m > 1 && !P.hd && want &&
-        ((P.n >= (P.d > 5 ? 1u << 16 : 1u << 18) && P.min_pts <= kOctMinPts) || (force && !std::strcmp(force, "1"))))
-        P.core_lanes = 3;
+    const char *e = std::getenv("HCA_CORE_LANES");
+    const bool force = e && !std::strcmp(e, "1");
+    if (P.m > 1 && !P.hd && want && (force || (P.n >= (P.d > 5 ? 1u << 16 : 1u << 18) && P.min_pts <= kOctMinPts)))
+        P.core_lanes = force ? 4 : 3;
     P.core_budget = std::getenv("HCA_CORE_BUDGET") || P.core_lanes < 2 ? env_core_budget()
                     : P.core_lanes == 2                                ? 512u
                                                                        : 256u;

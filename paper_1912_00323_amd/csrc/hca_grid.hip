@@ -1229,16 +1229,32 @@ __global__ __launch_bounds__(kBlock) void k_core(Plan P)
     flush_tests(P, kTestsCore, lt);
 }
 
+// Eight lanes per point, or (no lists, or lists that overflowed) a wave per
+// chunk of points?  The chunks also where groups hold two to five points on
+// average: such lists are long and their candidates far apart, so that most
+// points leave the lanes undecided (core marking, us, lanes and chunks: 8-D,
+// 158k points in groups of 1.6 729 and 314, 6-D 503k in 2.6 907 and 490, 7-D
+// 375k uniform in 1.3 1008 and 506; but blobs in groups of 5.5 on average 8-D
+// 196k 161 and 198, in 6.9 970k 427 and 1310, and lone points, which have few
+// candidates, 6-D 924k 123 and 617).
+__device__ __forceinline__ bool by_octets(const Plan &P)
+{
+    if (!P.nbr_cap || P.ctr->nbr_overflow) return false;
+    const uint64_t n = P.n, ng = ld_agent32(&P.ctr->n_groups);
+    return P.core_lanes == 4 || n >= 5 * ng || 8 * n <= 9 * ng;
+}
+
 // Group mode: the units are chunks of kPch consecutive sorted points, so the
 // thousands of points of a dense group are spread over many waves.  A chunk
 // may straddle groups; its points are walked group by group.  The per-cube
 // tallies (core points, smallest core input index) are accumulated with one
-// atomic per cube run of the chunk.  Held to 80 registers (six waves per
-// SIMD): the walks wait on memory, and more waves hide more of it.
+// atomic per cube run of the chunk (where k_core_flat ran before, it has done
+// the dense cubes').  Held to 80 registers (six waves per SIMD): the walks wait
+// on memory, and more waves hide more of it.
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock, 6) void k_core_chunks(Plan P)
 {
-    if (box_missed(P)) return;
+    if (box_missed(P) || (P.core_list && by_octets(P))) return;
     __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave], s_chunk[kWavesPerBlock][3][kWave];
     const uint32_t w = wave_in_block(), l = lane_id();
     const uint32_t n = P.n, minpts = (uint32_t)P.min_pts;
@@ -1286,14 +1302,15 @@ __global__ __launch_bounds__(kBlock, 6) void k_core_chunks(Plan P)
             P.core[pc + l] = core;
             if (P.rec) P.nrec[pc + l] = (uint8_t)(dense ? 0u : rec_count(mine));
         }
-        const uint32_t me = core ? P.sidx[pc + l] : kNone;
+        const bool tally = core && !(P.core_list && dense);
+        const uint32_t me = tally ? P.sidx[pc + l] : kNone;
         // one atomic per cube of the chunk (cubes are runs of lanes)
         uint64_t pend = __ballot(l < np);
         while (pend) {
             const uint32_t k0 = __ffsll((unsigned long long)pend) - 1;
             const uint32_t c = __shfl(cell, k0);
             const uint64_t same = __ballot(l < np && cell == c);
-            const uint32_t cores = (uint32_t)__popcll(__ballot(l < np && cell == c && core));
+            const uint32_t cores = (uint32_t)__popcll(__ballot(l < np && cell == c && tally));
             const uint32_t mn = wave_min(cell == c ? me : kNone);
             if (l == k0 && cores) {
                 atomicAdd(P.ncore + c, cores);
@@ -1720,10 +1737,6 @@ __global__ __launch_bounds__(kBlock) void k_core_list_lanes(Plan P)
 // minPts 10: chunks alone 870 us, lanes and a wave per point left 3357).
 constexpr int kOct = 8;
 
-// Eight lanes per point, or (no lists, or lists that overflowed) a wave per
-// chunk of points?
-__device__ __forceinline__ bool by_octets(const Plan &P) { return P.nbr_cap && P.ctr->nbr_overflow == 0; }
-
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_core_group_lanes(Plan P)
 {
@@ -1825,9 +1838,8 @@ __global__ __launch_bounds__(kBlock) void k_core_group_lanes(Plan P)
     flush_tests(P, kTestsCore, lt);
 }
 
-// The points that the lanes of group mode left, or without the lanes all
-// points of sparse cubes: a wave takes NP of them, which lie near each other in
-// the list, or a single one when there are few for each wave (5-D, 1M points:
+// The points that the lanes of group mode left: a wave takes NP of them, which
+// lie near each other in the list, or a single one when there are few for each wave (5-D, 1M points:
 // 142 us against 260 in fours; uniform 6-D, where nearly all are left: the
 // call 5.3 ms one by one, 3.1 in fours).
 constexpr uint32_t kRestSingle = 16;
@@ -1870,11 +1882,10 @@ __device__ __forceinline__ void core_group_points(const Plan &P, const uint32_t 
 template <int D, bool WIDE>
 __global__ __launch_bounds__(kBlock, 6) void k_core_group_rest(Plan P)
 {
-    if (box_missed(P)) return;
+    if (box_missed(P) || !by_octets(P)) return;
     __shared__ uint32_t s_beg[kWavesPerBlock][kWave], s_pre[kWavesPerBlock][kWave], s_chunk[kWavesPerBlock][3][kWave];
-    const bool lanes = by_octets(P);
-    const uint32_t count = ld_agent32(lanes ? &P.ctr->n_defer : &P.ctr->n_sparse);
-    const uint32_t *list = lanes ? P.core_defer : P.core_list;
+    const uint32_t count = ld_agent32(&P.ctr->n_defer);
+    const uint32_t *list = P.core_defer;
     uint32_t lt = 0;
     if (count <= kRestSingle * gridDim.x * kWavesPerBlock)
         core_group_points<D, WIDE, 1>(P, list, count, s_beg, s_pre, s_chunk, lt);
@@ -3844,7 +3855,6 @@ void launch_core(const Plan &P, int blocks, hipStream_t s)
         hipLaunchKernelGGL(k_core_flat<1>, dim3(fb), dim3(kFlatBlock), 0, s, P);
         HCA_DISPATCH_DW(k_core_group_lanes, P, blocks, s);
         HCA_DISPATCH_DW(k_core_group_rest, P, blocks, s);
-        return;
     }
     if (P.m > 1) HCA_DISPATCH_DW(k_core_chunks, P, blocks, s);
     else HCA_DISPATCH_DW(k_core, P, blocks, s);

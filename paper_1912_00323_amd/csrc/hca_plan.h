@@ -199,7 +199,8 @@ struct Plan {
     // (carved from the worklist, which is free until merging)
     uint32_t radius;
     uint32_t core_lanes;        // lane walk for core marking: 0 off, 1 column ranges (d <= 2), 2 neighbour lists (cubes,
-                                // d 3..4), 3 eight lanes per point (groups of several cubes)
+                                // d 3..4), 3 eight lanes per point (groups of several cubes),
+                                // 4 the same whatever the groups hold
     uint32_t core_budget;
     uint32_t *core_list;        // [n] sorted positions of points of sparse cubes
     uint32_t *core_defer;       // [n] the points left to the wave-wide walk
