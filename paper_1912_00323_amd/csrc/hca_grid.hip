@@ -1236,12 +1236,14 @@ __global__ __launch_bounds__(kBlock) void k_core(Plan P)
 // 158k points in groups of 1.6 729 and 314, 6-D 503k in 2.6 907 and 490, 7-D
 // 375k uniform in 1.3 1008 and 506; but blobs in groups of 5.5 on average 8-D
 // 196k 161 and 198, in 6.9 970k 427 and 1310, and lone points, which have few
-// candidates, 6-D 924k 123 and 617).
+// candidates, 6-D 924k 123 and 617).  So do larger groups of evenly spread
+// points, hardly two of them in a cube (6-D, 619k in groups of 8.3 1993 and
+// 1019, 7-D 428k in 7.7 2489 and 1196; blobs have 1.07 points a cube and more).
 __device__ __forceinline__ bool by_octets(const Plan &P)
 {
     if (!P.nbr_cap || P.ctr->nbr_overflow) return false;
-    const uint64_t n = P.n, ng = ld_agent32(&P.ctr->n_groups);
-    return P.core_lanes == 4 || n >= 5 * ng || 8 * n <= 9 * ng;
+    const uint64_t n = P.n, ng = ld_agent32(&P.ctr->n_groups), nc = ld_agent32(&P.ctr->n_cells);
+    return P.core_lanes == 4 || (n >= 5 * ng && 20 * nc <= 19 * n) || 8 * n <= 9 * ng;
 }
 
 // Group mode: the units are chunks of kPch consecutive sorted points, so the

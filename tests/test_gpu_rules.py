@@ -38,18 +38,23 @@ def test_few_cubes(ctx, n, eps, few, uniform):  # noqa: F811
     assert np.array_equal(core.astype(bool), counts >= 6) and np.array_equal(got, want)
 
 
-@pytest.mark.parametrize("eps,lanes", [(2000.0, True), (4800.0, False), (6500.0, False), (9000.0, True)])
-def test_points_per_group(ctx, eps, lanes):  # noqa: F811
+@pytest.mark.parametrize("eps,spread,lanes", [(2000.0, 0, True), (4800.0, 0, False), (6500.0, 0, False),
+                                              (9000.0, 0, False), (6500.0, 400, True)])
+def test_points_per_group(ctx, eps, spread, lanes):  # noqa: F811
     """Groups of several cubes: lone points and groups of five points or more on
-    average go by lanes, those between by chunks; some cubes are dense."""
+    average go by lanes, those between by chunks, and so do evenly spread points;
+    some cubes are dense."""
     n = (1 << 16) + 77
     rng = np.random.default_rng(6)
     pts = rng.integers(0, 40_000, size=(n, 6)).astype(np.int32)
     pts[:900] = 20_000 + pts[:900] // 64
+    if spread:
+        pts[900:] = pts[900 + np.arange(n - 900) // 12] + rng.integers(0, spread, size=(n - 900, 6))
     want, counts, _ = oracle.dbscan(pts, eps, 6, details=True)
     got, core, st = gpu_labels(ctx, pts, eps, 6, core=True, stats=True)
     print(f"[case] eps={eps} groups={st['n_groups']} ({n / st['n_groups']:.2f} points each)", flush=True)
-    assert (n >= 5 * st["n_groups"] or 8 * n <= 9 * st["n_groups"]) == lanes
+    many = n >= 5 * st["n_groups"] and 20 * st["n_cells"] <= 19 * n
+    assert (many or 8 * n <= 9 * st["n_groups"]) == lanes
     assert np.array_equal(core.astype(bool), counts >= 6)
     assert np.array_equal(got, want)
     assert st["n_core_points"] == int((counts >= 6).sum())
