@@ -616,10 +616,12 @@ __device__ __forceinline__ bool list_far(const Plan &P, const QBox<D> &ob, const
 // fit in all could still overflow in one wave, and every group was then
 // searched over the stencil: 7-D, 383k points, core marking 0.5 -> 15.5 ms.
 // Without shares every wave's first block queued up at one counter: 5-D, 149k
-// points, lists 45 -> 213 us.)  The last blocks of all waves together stay under
-// a third of that part; within it larger blocks mean fewer moves (74 4-D sets,
-// 1.6M points in all: 1075 us with blocks of 1024, 1024 so, 999 with shares
-// alone).
+// points, lists 45 -> 213 us.)  The blocks come from eight parts with a counter
+// each, a wave's own first, since waves use up their shares at about the same
+// time (13 4-D sets, 469k points in all: one counter 462 us, eight 401, fixed
+// shares alone 400).  The last blocks of all waves together stay under a third
+// of the parts; within that larger blocks mean fewer moves (74 4-D sets, 1.6M
+// points: blocks of 1024 and one counter 1075 us, now 986, fixed shares 992).
 constexpr uint32_t kListBlock = 4096;
 struct ListRoom {
     uint32_t at, end;           // of the wave's share or block
@@ -635,16 +637,25 @@ __device__ __forceinline__ bool list_room(const Plan &P, ListRoom &room, uint32_
     if (room.at + k <= room.end) return true;
     const uint32_t have = room.at - start, need = have + k, waves = gridDim.x * kWavesPerBlock;
     const uint32_t size = max(min(kListBlock, (P.nbr_cap - room.pool) / (3u * waves)), need + kWave);
-    uint32_t base = kNone;
-    if (lane_id() == 0 && (uint64_t)room.pool + ld_agent32(&P.ctr->nbr_used) + need <= P.nbr_cap)
-        base = room.pool + atomicAdd(&P.ctr->nbr_used, size);
+    const uint32_t part = (P.nbr_cap - room.pool) / kListParts;
+    uint32_t base = kNone, len = 0;
+    if (lane_id() == 0)
+        for (uint32_t r = 0; r < kListParts && base == kNone; r++) {
+            const uint32_t x = (blockIdx.x + r) % kListParts;
+            uint32_t *used = P.ctr->nbr_used + x * kCounterStride;
+            if ((uint64_t)ld_agent32(used) + need > part) continue;
+            const uint32_t a = atomicAdd(used, size);
+            if ((uint64_t)a + need > part) continue;
+            base = room.pool + x * part + a;
+            len = min(size, part - a);
+        }
     base = lane_value(base, 0);
-    if (base == kNone || (uint64_t)base + need > P.nbr_cap) return false;
+    if (base == kNone) return false;
     __threadfence_block();
     for (uint32_t i = lane_id(); i < have; i += kWave) P.nbr[base + i] = P.nbr[start + i];
     start = base;
     room.at = base + have;
-    room.end = (uint32_t)min((uint64_t)base + size, (uint64_t)P.nbr_cap);
+    room.end = base + lane_value(len, 0);
     return true;
 }
 

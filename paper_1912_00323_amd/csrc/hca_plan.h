@@ -15,6 +15,7 @@ constexpr uint32_t kLabelSplit = 6u << 20;    // from so many points on (2-D, la
                                               // binned: points in random order 4M 70 and 58, 8M 186 and 97, 16M 385
                                               // and 183; sorted along one axis 4M 38 and 73, 8M 73 and 104, 16M 127
                                               // and 185, where the rest of the call makes up for it)
+constexpr uint32_t kListParts = 8;             // parts of the list array with a counter each
 constexpr int kRec = 16;                       // neighbours recorded per point by core marking
 // More than kMaxDim axes: candidates a point of the first core pass looks at
 // before it is left to the next pass; the host may lower it per call.
@@ -84,7 +85,7 @@ struct Counters {
     uint32_t pad_tally[2];      // (core and noise counts: see tally)
     uint32_t n_clusters;
     uint32_t nbr_overflow;      // groups whose neighbour list did not fit
-    uint32_t nbr_used;          // entries of the list array handed out in blocks
+    uint32_t pad_list;
     uint32_t hmask;             // hash slots in use - 1 (a power of two - 1)
     uint32_t nbr_ticket;        // tiles of the backward-list scan
     uint32_t hd_left[kHdPasses];    // more than kMaxDim axes: points left undecided by each core pass
@@ -107,6 +108,7 @@ struct Counters {
     // kWorkRegions lines so that thousands of blocks do not all add to one
     // address
     uint32_t tally[2][kWorkRegions * kCounterStride];
+    uint32_t nbr_used[kListParts * kCounterStride]; // entries of each part of the list array handed out in blocks
     uint32_t label_at[kLabelRanges];    // labels in the list of each range of input positions
 };
 
